@@ -57,12 +57,6 @@ PROFILED = {
     "counters": {
         # per dispatch: FETCH_SIZE / WRITE_SIZE in KiB as read, SQ_WAVES, SQ_INSTS_VALU / SQ_WAVES, SQ_INSTS_SALU / SQ_WAVES,
         # SQ_THREAD_CYCLES_VALU / SQ_ACTIVE_INST_VALU (lanes active per vector instruction, of 64)
-        ("C3", "k_digits"): {'fetch_kib': 28, 'write_kib': 524288, 'waves': 2097152, 'valu_per_wave': 90.0, 'salu_per_wave': 25.5, 'active_lanes': 64.0},
-        ("C3", "k_recv_uniform"): {'fetch_kib': 1048881, 'write_kib': 17694827, 'waves': 2097152, 'valu_per_wave': 915.4, 'salu_per_wave': 470.4, 'active_lanes': 63.9},
-        ("C3", "k_send_lookup"): {'fetch_kib': 2031794, 'write_kib': 14155972, 'waves': 524288, 'valu_per_wave': 1002.0, 'salu_per_wave': 626.0, 'active_lanes': 64.0},
-        ("C2", "k_digits"): {'fetch_kib': 31, 'write_kib': 4096, 'waves': 16388, 'valu_per_wave': 72.0, 'salu_per_wave': 25.5, 'active_lanes': 64.0},
-        ("C2", "k_recv_uniform"): {'fetch_kib': 7278, 'write_kib': 132104, 'waves': 16388, 'valu_per_wave': 1055.4, 'salu_per_wave': 546.5, 'active_lanes': 63.7},
-        ("C2", "k_send_lookup"): {'fetch_kib': 21069, 'write_kib': 110656, 'waves': 8193, 'valu_per_wave': 1126.9, 'salu_per_wave': 446.0, 'active_lanes': 63.2},
         ("C2", "k_expand_rows"): {'fetch_kib': 35345, 'write_kib': 1130584, 'waves': 1130500, 'valu_per_wave': 69.0, 'salu_per_wave': 9.0, 'active_lanes': 64.0},
         ("C4", "k_expand"): {'fetch_kib': 9004, 'write_kib': 1052688, 'waves': 263176, 'valu_per_wave': 258.5, 'salu_per_wave': 195.0, 'active_lanes': 63.3},
         ("C4", "k_rows_to_bytes"): {'fetch_kib': 2252, 'write_kib': 1280, 'waves': 5124, 'valu_per_wave': 50.0, 'salu_per_wave': 12.0, 'active_lanes': 64.0},
@@ -90,14 +84,6 @@ def profiled(config, kernel, digest):
 # its loops to the largest q among its lanes; that excess, the second-range branch of Alg. 4, the byte copies of a
 # row and the sort of the batch kernel are not counted).  So `frac` = useful lane-ops/s / peak is at most the share
 # of time the vector ALUs are busy, and falls below it by divergence and by everything that is not the method.
-#   a row whose end points come from the table      the vector instructions k_recv_uniform executes (one rank a lane),
-#                                                    SQ_INSTS_VALU x 64 of the counter profile of this configuration:
-#                                                    the count depends on p (how many rounds a wave takes from the
-#                                                    ranks' digits, how many from windows), so it is measured, not
-#                                                    modelled; for this kernel `frac` is therefore its vector-ALU
-#                                                    utilisation.  Without a profile entry: 55 ops for each of the first
-#                                                    six rounds, 28 for each later one (17 for the rule, a window in one
-#                                                    round of five), 80 of set-up
 #   the batch kernel and Alg. 5, by the structure of the code (no counter fit):
 #   a round of Alg. 4 on two digit masks            55 ops (window masks, candidate, bookkeeping)
 #   set-up of a row                                 50 ops
@@ -115,29 +101,15 @@ def ops_walk(q, per_lane):
     return (4 * max(q - 7, 0) + 10) if per_lane else (3 * max(q - 7, 0) + 3)
 
 
-def ops_recv_tabled(q):
-    return 55 * min(q, 6) + 28 * max(q - 6, 0) + 80
-
-
-def recv_tabled_model(config, p, q, digest):
-    """("alu", lane-ops per launch, note) for k_recv_uniform over all p ranks: executed instructions from the profile
-    of `config` if there is one, else the estimate above."""
-    prof = profiled(config, "k_recv_uniform", digest)
-    if prof is not None and "valu_per_wave" in prof:
-        return ("alu", prof["valu_per_wave"] * prof["waves"] * prof["active_lanes"],
-                "counters (executed vector lane-operations)" + (", of other sources: stale" if prof["stale"] else ""))
-    return ("alu", ops_recv_tabled(q) * p, "model (estimate)")
-
-
 def ops_recv_walks(q, per_lane, walks=None):
     walks = (q + 2) if walks is None else walks
     return walks * ops_walk(q, per_lane) + 55 * q + 50
 
 
-def ops_send_alg5(q, per_lane, tabled=False):
+def ops_send_alg5(q, per_lane):
     total = 0
     for i in range(q):
-        total += (0 if tabled else (i + 3) * ops_walk(q, per_lane)) + 55 * (i + 1) + 30
+        total += (i + 3) * ops_walk(q, per_lane) + 55 * (i + 1) + 30
     return total
 
 
@@ -272,14 +244,11 @@ def run_c3(torch, bcs, steps, warmup, digest):
         bcs.bcs_sched_rooted_ws(p, ROOT_RANK, 0, p, recv, send, ws)
 
     ms, ms_ev, timing = timed_steps(torch, bcs, step, steps, warmup)
-    # the receive kernel writes the int32 table and the slot-major bytes and reads the digit table (counted once)
-    models = {"k_recv_uniform": recv_tabled_model("C3", p, q, digest) + (p * q * (4 + 1) + 4 * p,),
-              "k_digits": ("alu", (ops_walk(q, False) + 12) * p),
-              "k_send_lookup": ("hbm", p * q * (1 + 4))}          # reads the slot-major bytes, writes one int32 table
+    models = {"k_sched": ("hbm", 2 * p * q * 4)}                   # both tables written once, nothing of their size read
     kernels = kernel_records(timing, steps, models, "C3", digest)
     del recv, send, ws
     torch.cuda.empty_cache()
-    return {"workload": "C3: p=2^27-1 (q=27), all ranks, root 0: int32 recv rows (Alg. 4) and send rows (look-up), "
+    return {"workload": "C3: p=2^27-1 (q=27), all ranks, root 0: int32 recv and send rows, "
                         "2 x 14.5 GB written per step", "p": p, "q": q,
             "steps": steps, "ms_per_step": ms, "ms_per_step_with_kernel_events": ms_ev,
             "value": p / (ms * 1e-3), "unit": "rank-schedules/s",
@@ -308,16 +277,14 @@ def run_c2(torch, bcs, steps, warmup, digest):
     ws = torch.empty(bcs.bcs_sched_expand_workspace_bytes(P, N_BLOCKS), dtype=torch.uint8, device="cuda")
 
     def step():
-        # one call: receive rows, send rows by look-up, both block tables
+        # one call: receive rows, send rows, both block tables
         bcs.bcs_sched_expand_ws(P, ROOT_RANK, N_BLOCKS, recv, send, rb, sb, ws)
 
     ms, ms_ev, timing = timed_steps(torch, bcs, step, steps, warmup)
     models = {"k_expand_rows": ("hbm", P * R * 4), "k_expand": ("hbm", P * R * 4),
-              "k_send_lookup": ("hbm", P * q * (1 + 4) + P * 24),   # slot-major bytes in; one table and its byte rows out
-              "k_recv_uniform": recv_tabled_model("C2", P, q, digest),
-              "k_digits": ("alu", (ops_walk(q, False) + 12) * P)}
+              "k_sched": ("hbm", 2 * P * (q * 4 + 24))}             # both tables and their byte rows out
     kernels = kernel_records(timing, steps, models, "C2", digest)
-    construct_ms = sum(kernels[k]["ms_per_step"] for k in ("k_digits", "k_recv_uniform", "k_send_lookup") if k in kernels)
+    construct_ms = sum(kernels[k]["ms_per_step"] for k in ("k_sched",) if k in kernels)
     exp = kernels.get("k_expand_rows") or kernels.get("k_expand")
     return {"workload": "C2: p=2^20+1 (q=21), all ranks, root 0: recv+send schedules, then expansion n=%d (R=%d "
                         "rounds), one call a step" % (N_BLOCKS, R), "p": P, "q": q, "n": N_BLOCKS, "rounds": R,

@@ -1,9 +1,10 @@
-// Schedule construction kernels: the low-level table, receive rows (Alg. 4), send rows by look-up (Alg. 9,
-// second loop) and by recomputation (Alg. 5), and the batch of unrelated (p, r, root) triples.
+// Schedule construction kernels: the tables of the low levels and low rounds, receive and send rows of one p in closed
+// form, and the batch of unrelated (p, r, root) triples.
 #ifndef BCS_KERNELS_SCHED_H
 #define BCS_KERNELS_SCHED_H
 
 #include "bcs_kernels_common.h"
+#include "bcs_rows.h"
 
 namespace {
 
@@ -27,34 +28,25 @@ __device__ __forceinline__ void stage_lowtab(uint32_t *dst, int shape) {
     for (int i = threadIdx.x; i < kLowShapeBytes / 4; i += kBlock) dst[i] = src[i];
 }
 
-// A lane completes its byte row (the three mirrored slots and the padding) ...
-template <int Q>
-__device__ __forceinline__ void byte_row_finish(int8_t *row) {
-    constexpr int kRS = byte_row_stride(Q);
-#pragma unroll
-    for (int m = 0; m < kRS - Q; ++m) row[Q + m] = (m < 3 && m < Q) ? row[m] : (int8_t)0;
-}
+// ----------------------------------------------------------------------------------------------
+// The table of the low rounds (bcs_rows.h), 6.6 MB in the code object, filled once per device and process after the
+// low-level table.  A launch reads one shape of it (103 KB, which stays in the caches), one entry a rank.
+// ----------------------------------------------------------------------------------------------
+__device__ __align__(16) LowRow g_lowrows[kRowsAll];
 
-// ... and the workgroup's byte rows leave for the table as 16-byte pieces (after a barrier)
-template <int Q>
-__device__ __forceinline__ void byte_rows_out(const int8_t *tileB, uint32_t rows, int8_t *__restrict__ dst) {
-    constexpr int kRS = byte_row_stride(Q);
-    const uint32_t n4 = rows * (kRS / 4);                         // dwords
-    const uint32_t n16 = n4 >> 2;
-    for (uint32_t g = threadIdx.x; g < n16; g += kBlock)
-        reinterpret_cast<v4i *>(dst)[g] = reinterpret_cast<const v4i *>(tileB)[g];
-    const uint32_t e = (n16 << 2) + threadIdx.x;
-    if (e < n4) reinterpret_cast<int32_t *>(dst)[e] = reinterpret_cast<const int32_t *>(tileB)[e];
+__global__ __launch_bounds__(kBlock) void k_build_lowrows() {
+    const uint32_t e = blockIdx.x * kBlock + threadIdx.x;
+    if (e < kRowsAll) g_lowrows[e] = low_row_entry(e, g_lowtab);
 }
 
 // Rows of a workgroup's LDS tile of bytes (rank-major, Q bytes a rank, so the tile is the table's piece with one byte
 // an entry) to their place in the rank-major int32 table: a lane reads four bytes, widens them and writes 16 bytes.
-template <int Q>
+template <int Q, int LANES>
 __device__ __forceinline__ void byte_tile_to_rows(const int8_t *tile, uint32_t rows, int32_t *__restrict__ dst) {
     const uint32_t n = rows * Q;
     if ((reinterpret_cast<uintptr_t>(dst) & 15u) == 0) {
         const uint32_t n4 = n >> 2;
-        for (uint32_t g = threadIdx.x; g < n4; g += kBlock) {
+        for (uint32_t g = threadIdx.x; g < n4; g += LANES) {
             const int32_t w = reinterpret_cast<const int32_t *>(tile)[g];
             const v4i pack = {(int32_t)(int8_t)w, (int32_t)(int8_t)(w >> 8), (int32_t)(int8_t)(w >> 16), w >> 24};
             __builtin_nontemporal_store(pack, reinterpret_cast<v4i *>(dst) + g);
@@ -63,219 +55,128 @@ __device__ __forceinline__ void byte_tile_to_rows(const int8_t *tile, uint32_t r
         if (e < n) dst[e] = tile[e];
         return;
     }
-    for (uint32_t e = threadIdx.x; e < n; e += kBlock) dst[e] = tile[e];
+    for (uint32_t e = threadIdx.x; e < n; e += LANES) dst[e] = tile[e];
+}
+
+// The same rows as bytes for an expansion that follows: T[k] = entry[k] - k, the first three once more, padding.
+template <int Q, int LANES>
+__device__ __forceinline__ void byte_tile_to_byte_rows(const int8_t *tile, uint32_t rows, int8_t *__restrict__ dst) {
+    constexpr uint32_t kW4 = byte_row_stride(Q) / 4;
+    uint32_t *out4 = reinterpret_cast<uint32_t *>(dst);
+    for (uint32_t w = threadIdx.x; w < rows * kW4; w += LANES) {
+        const uint32_t row = w / kW4, pos0 = 4u * (w - row * kW4);
+        uint32_t packed = 0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t pos = pos0 + c;
+            const uint32_t slot = pos < (uint32_t)Q ? pos : pos - Q;
+            const bool slot_ok = pos < (uint32_t)(Q + 3) && slot < (uint32_t)Q;
+            const int32_t t = slot_ok ? (int32_t)tile[row * Q + slot] - (int32_t)slot : 0;
+            packed |= ((uint32_t)t & 0xffu) << (8 * c);
+        }
+        out4[w] = packed;
+    }
 }
 
 // ----------------------------------------------------------------------------------------------
-// K1: receive rows of ranks [r0, r1), uniform p.  Lane = rank.  Rows are staged in LDS as bytes, laid out like
-// the table, and leave widened to int32 in 16-byte pieces; optionally the entries are also kept slot-major
-// (recvT[k][r - r0], one byte each) for the send look-up that follows, staged the same way and written as one
-// aligned 256-byte piece a slot.  Bytes instead of int32 in LDS is what lets eight workgroups share a compute unit.
+// K1: receive and send rows of ranks [r0, r1), one p per launch, from the closed form in bcs_rows.h.  Lane = rank.
+// A workgroup takes kTileRanks ranks.  The entries of rounds 7 and up, of both tables, follow from a lane's own digits
+// (about eight vector ops a level); those of the receive rounds below 7 are one 8-byte table entry; those of the send
+// rounds below 7 are entries of the next skips[6] <= 64 ranks, so kTileAhead more lanes compute the low rounds alone and
+// the send entries are read across the lanes in LDS.  Both tables' rows are staged in LDS as bytes, laid out like the
+// table, and leave widened to int32 in 16-byte streaming stores.  Nothing else is read or written: no table of
+// all ranks in memory, no second pass, and a range of ranks costs the same a rank as all of them.
+// Bound by the stores.  Measured: all ranks of 2^27-1, 29 GB, 7.31 ms before (digit table, receive rows by windows, send
+// rows by look-up in a slot-major table), 5.22 ms now; all of 2^20+1 59 -> 34 us; 2^24 ranks of 2^27-1 1.10 -> 0.62 ms.
 // ----------------------------------------------------------------------------------------------
-// K0: the digit mask of every rank (one walk each), for launches over all ranks: every end point of every
-// window of Alg. 4 is some rank, so K1 then reads its digit masks instead of walking (q+2 walks a row otherwise).
+constexpr int kTileRanks = 256;
+constexpr int kTileAhead = 64;
+constexpr int kTileLanes = kTileRanks + kTileAhead;
+constexpr int kWantRecv = 1, kWantSend = 2;
+
 template <int Q>
-__global__ __launch_bounds__(kBlock) void k_digits(const SkipTab tab, uint32_t *__restrict__ dtab) {
-    __shared__ uint32_t lowtab[kLowShapeBytes / 4];
-    Uniform<Q> pol;
-#pragma unroll
-    for (int k = 0; k <= Q; ++k) pol.S[k] = tab.s[k];
-    pol.tab = &tab;
-    pol.low = reinterpret_cast<const uint8_t *>(lowtab);
-    const uint32_t p = pol.p();
-    stage_lowtab(lowtab, low_shape(p, Q));
-    __syncthreads();
-    const uint64_t y = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-    const uint32_t d = digits(pol, y < p ? (uint32_t)y : 0u);
-    if (y < p) dtab[y] = d;
-}
+struct RowTiles {
+    __align__(16) int8_t recv[kTileRanks * Q + 16];
+    __align__(16) int8_t send[kTileRanks * Q + 16];
+    LowRow low[kTileLanes];                                       // entries of the rounds below 7, as bytes
+};
 
-constexpr uint64_t kSlotTableCached = 128ull << 20;   // slot-major tables up to this size are written for the caches
-template <int Q, bool BYTES, bool TAB = false>
-__global__ __launch_bounds__(kBlock) void k_recv_uniform(const SkipTab tab, uint32_t root, uint32_t r0, uint32_t r1,
-                                                         int32_t *__restrict__ recv_out,
-                                                         slot_t *__restrict__ recvT, uint64_t ldT,
-                                                         int8_t *__restrict__ rowsB,
-                                                         const uint32_t *__restrict__ dtab) {
-    constexpr int kRS = byte_row_stride(Q);
-    __shared__ __align__(16) int8_t tile[kBlock * Q + 16];
-    __shared__ __align__(16) int8_t tileB[BYTES ? kBlock * kRS : 16];   // only the variant that leaves byte rows pays for it
-    // the tile's part of the slot-major table, slot by slot; the variant with byte rows (tables that the caches
-    // hold) has no room for it beside them and stores the entries one by one
-    __shared__ __align__(16) slot_t tileT[BYTES ? 16 : Q * kBlock];
-    __shared__ uint32_t lowtab[kLowShapeBytes / 4];
+template <int Q, int WANT>
+__device__ __forceinline__ void fill_row_tiles(const SkipTab &tab, uint32_t root, uint32_t first_rank, RowTiles<Q> &tiles) {
     Uniform<Q> pol;
 #pragma unroll
     for (int k = 0; k <= Q; ++k) pol.S[k] = tab.s[k];
     pol.tab = &tab;
-    pol.low = reinterpret_cast<const uint8_t *>(lowtab);
+    pol.low = nullptr;
     const uint32_t p = pol.p();
-    stage_lowtab(lowtab, low_shape(p, Q));
-    __syncthreads();
-    const uint64_t first = (uint64_t)blockIdx.x * kBlock;       // offset of this tile inside [r0, r1)
-    const uint64_t idx = first + threadIdx.x;
-    const uint64_t count = (uint64_t)r1 - r0;
-    const bool live = idx < count;
-    const uint32_t r = live ? (uint32_t)(r0 + idx) : root;
+    uint32_t r = first_rank + threadIdx.x;                        // lanes past the end wrap around like the look-ahead
+    if constexpr (Q < 10) r %= p;                                 // p < 513 may be below the tile's lanes
+    else r = r >= p ? r - p : r;
     const uint32_t v = r >= root ? r - root : r + p - root;
-    int8_t *my = tile + threadIdx.x * Q;
-    int8_t *myB = tileB + (BYTES ? threadIdx.x * kRS : 0);
-    auto emit = [&](int i, int val) {
-        my[i] = (int8_t)val;
-        if constexpr (BYTES) {
-            if (recvT) recvT[(uint64_t)i * ldT + idx] = (slot_t)val;
-            myB[i] = (int8_t)(val - i);
-        } else {
-            if (recvT) tileT[i * kBlock + threadIdx.x] = (slot_t)val;
-        }
-    };
-    if (live) {                                                  // lanes past the end sit the row out
-        if constexpr (TAB) recv_row_tab(pol, dtab, v, emit);
-        else recv_row(pol, v, Q - 1, emit);
-    }
-    if constexpr (BYTES) byte_row_finish<Q>(myB);
-    __syncthreads();
-    if (!BYTES && recvT) {
-        // Each slot's kBlock bytes are one aligned piece of the table (its rows are padded to a multiple of
-        // kBlock, so the last tile writes its idle lanes' bytes into the padding): 16 bytes a lane.
-        static_assert(kBlock % 16 == 0, "16-byte pieces");
-        // A table that the caches hold is left there for the look-up that follows; a larger one is streamed out.
-        const bool stream_out = ldT * Q > kSlotTableCached;
-        for (int g = threadIdx.x; g < Q * (kBlock / 16); g += kBlock) {
-            const int k = g / (kBlock / 16), part = g % (kBlock / 16);
-            const v4i piece = *reinterpret_cast<const v4i *>(tileT + k * kBlock + part * 16);
-            v4i *dst = reinterpret_cast<v4i *>(recvT + (uint64_t)k * ldT + first + part * 16);
-            if (stream_out) __builtin_nontemporal_store(piece, dst);
-            else *dst = piece;
-        }
-    }
-    if (!recv_out) return;
-    const uint64_t rows = (count - first) < (uint64_t)kBlock ? (count - first) : (uint64_t)kBlock;
-    byte_tile_to_rows<Q>(tile, (uint32_t)rows, recv_out + first * Q);
-    if constexpr (BYTES) byte_rows_out<Q>(tileB, (uint32_t)rows, rowsB + first * kRS);
-}
-
-// K2: send rows from the slot-major receive table of ALL ranks (Alg. 9, second loop):
-// send[r][k] = recv[(r + skips[k]) mod p][k].
-// One wave (a workgroup of 64 lanes) takes G consecutive ranks.  Reading: a lane fetches the entries of FOUR
-// consecutive ranks in one slot with one (unaligned) 4-byte load -- the table is slot-major bytes, so the four
-// neighbours' entries are adjacent -- and the 64 lanes cover 64 / (G/4) slots at a time; all loads of a wave are in
-// flight together.  Byte loads, one rank a lane, cost the address path of the memory pipeline four times as many
-// instructions for the same bytes, and that path, not the HBM, was the limit (measured on MI355X at p = 2^27-1:
-// 3.8 ms against 18.1 GB / 8 TB/s = 2.3 ms).  The words go to an LDS tile of bytes, slot-major with padded rows;
-// then the wave writes its ranks' rows -- one contiguous piece of G q int32 -- as 16-byte streaming stores in
-// address order, each lane gathering the four entries of its store from the tile.
-// Measured at p = 2^27-1 (18.1 GB): 3.24 ms with G = 256, 3.38 ms with G = 128, 4.35 ms with G = 64 (4.3 KB of
-// loads in flight per wave are too few); at p = 2^20+1: 0.0212, 0.0199, 0.0231 ms.  So many ranks take G = 256
-// and fewer take G = 128 (more waves to spread over the device).  The reading side alone (no stores) takes
-// 0.65 ms and the stores alone 2.6 ms (a wave streaming 27 KB: 5.5 TB/s; a store-only kernel whose workgroups
-// write one aligned 4 KB piece each reaches 6.6-7.0 TB/s, but a workgroup that short cannot keep enough loads in
-// flight: measured 4.4-5.4 ms in that shape); the whole kernel takes about their sum, reads and writes do not
-// overlap in the memory system.
-constexpr int kLookupLanes = 64;
-constexpr int kLookupBigG = 256, kLookupSmallG = 128;
-constexpr int kLookupBigMinQ = 22;                      // p > 2^21: a wave takes kLookupBigG ranks
-
-template <int Q, int G>
-__global__ __launch_bounds__(kLookupLanes) void k_send_lookup(const SkipTab tab, const slot_t *__restrict__ recvT,
-                                                              uint64_t ldT, int32_t *__restrict__ send_out,
-                                                              int8_t *__restrict__ rowsB) {
-    static_assert(G % 4 == 0 && kLookupLanes % (G / 4) == 0 && G <= 4 * kLookupLanes, "a lane takes four ranks of one slot");
-    constexpr int kQuads = G / 4;                                  // lanes that cover one slot of the group
-    constexpr int kSlotsPerLoad = kLookupLanes / kQuads;
-    constexpr int kLoads = (Q + kSlotsPerLoad - 1) / kSlotsPerLoad;
-    constexpr int kRS = G + 4;                                     // bytes per slot row of the tile (padded: banks)
-    constexpr int kStores = (G * Q + 4 * kLookupLanes - 1) / (4 * kLookupLanes);
-    __shared__ __align__(16) int8_t tile[Q * kRS];
-    const uint32_t p = tab.s[Q];
-    const uint64_t first = (uint64_t)blockIdx.x * G;               // < p: the grid has ceil(p / G) workgroups
-    const uint32_t lane = threadIdx.x;
-    const uint32_t j4 = (lane % kQuads) * 4u;                      // this lane's four ranks within the group
-    const uint32_t kk = lane / kQuads;
-    uint32_t got[kLoads];
+    const uint32_t base = row_base(pol);
+    const RankPlace pl = rank_place(pol, v);
+    const LowRow w = g_lowrows[base + pl.ctx * 128u + pl.low];
+    const LowRow b = row_bytes(w, pl.ctx, pl.J, (uint32_t)Q);
+    if constexpr ((WANT & kWantSend) != 0) tiles.low[threadIdx.x] = b;
+    const bool own_rank = threadIdx.x < (uint32_t)kTileRanks;     // wave-uniform
+    int8_t *my_recv = tiles.recv + threadIdx.x * Q;
+    int8_t *my_send = tiles.send + threadIdx.x * Q;
+    constexpr int kLow = Q < kLowLevels ? Q : kLowLevels;
+    if (own_rank) {
+        if constexpr ((WANT & kWantRecv) != 0) {
 #pragma unroll
-    for (int it = 0; it < kLoads; ++it) {
-        const uint32_t k = it * kSlotsPerLoad + kk;
-        const uint32_t kc = k < (uint32_t)Q ? k : (uint32_t)Q - 1u;    // lanes past the last slot repeat it; never stored
-        const uint32_t sk = ((p - 1u) >> (Q - kc)) + 1u;           // skips[k]: the closed form of Alg. 1's halving
-        const uint64_t r = first + j4;
-        uint32_t word = 0;
-        if (r < p) {
-            uint32_t t = (uint32_t)r + sk;                         // below 2p < 2^32
-            t = t >= p ? t - p : t;
-            const slot_t *row = recvT + (uint64_t)kc * ldT;
-            if (t + 3u < p) {
-                __builtin_memcpy(&word, row + t, 4);
-            } else {                                               // the ranks wrap inside these four (one lane per slot)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    uint32_t tc = t + c;
-                    tc = tc >= p ? tc - p : tc;
-                    word |= (uint32_t)(uint8_t)row[tc] << (8 * c);
-                }
-            }
+            for (int k = 0; k < kLow; ++k) my_recv[k] = (int8_t)(k < 4 ? b.lo >> (8 * k) : b.hi >> (8 * (k - 4)));
         }
-        got[it] = word;
-    }
-#pragma unroll
-    for (int it = 0; it < kLoads; ++it) {
-        const uint32_t k = it * kSlotsPerLoad + kk;
-        if (k < (uint32_t)Q) *reinterpret_cast<uint32_t *>(tile + k * kRS + j4) = got[it];
+        high_entries(pol, pl, place_own(pl, w),
+                     [&](int k, int32_t e) { if constexpr ((WANT & kWantRecv) != 0) my_recv[k] = (int8_t)e; },
+                     [&](int k, int32_t e) { if constexpr ((WANT & kWantSend) != 0) my_send[k] = (int8_t)e; });
+        if constexpr ((WANT & kWantRecv) != 0) recv_fix(pol, pl, w, [&](int k, int32_t e) { my_recv[k] = (int8_t)e; });
+        if constexpr ((WANT & kWantSend) != 0)
+            send_fix(pol, v, pl, base, [](uint32_t e) { return g_lowrows[e]; }, [&](int k, int32_t e) { my_send[k] = (int8_t)e; });
     }
     __syncthreads();
-    const uint32_t rows = ((uint64_t)p - first) < (uint64_t)G ? (uint32_t)((uint64_t)p - first) : (uint32_t)G;
-    const uint32_t n = rows * Q;                                   // entries of this group
-    int32_t *dst = send_out + first * Q;
-    const bool vec = (reinterpret_cast<uintptr_t>(dst) & 15u) == 0;
+    if constexpr ((WANT & kWantSend) != 0) {
+        if (own_rank) {
+            const int8_t *low = reinterpret_cast<const int8_t *>(tiles.low);
 #pragma unroll
-    for (int it = 0; it < kStores; ++it) {
-        const uint32_t e = (uint32_t)it * 4u * kLookupLanes + lane * 4u;
-        if (e < n) {
-            uint32_t R = e / Q, k = e - R * Q;                     // divisions by a constant
-            int32_t v[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t Rc = R < (uint32_t)G ? R : (uint32_t)G - 1u;   // past the group's end: read in bounds, not stored
-                v[c] = tile[k * kRS + Rc];
-                ++k;
-                const bool wrap = k == (uint32_t)Q;
-                k = wrap ? 0u : k;
-                R += wrap ? 1u : 0u;
-            }
-            if (vec && e + 4u <= n) {
-                const v4i pack = {v[0], v[1], v[2], v[3]};
-                __builtin_nontemporal_store(pack, reinterpret_cast<v4i *>(dst + e));
-            } else {
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (e + c < n) dst[e + c] = v[c];
-            }
+            for (int k = 0; k < kLow; ++k) my_send[k] = low[(threadIdx.x + pol.S[k]) * 8u + k];
         }
-    }
-    if (rowsB) {
-        // the same rows as bytes for the expansion that follows: T[k] = entry[k] - k, the first three once more
-        constexpr int kRSB = byte_row_stride(Q);
-        constexpr uint32_t kW4 = kRSB / 4;
-        uint32_t *out4 = reinterpret_cast<uint32_t *>(rowsB + first * kRSB);
-        for (uint32_t w = lane; w < rows * kW4; w += kLookupLanes) {
-            const uint32_t row = w / kW4, pos0 = 4u * (w - row * kW4);
-            uint32_t packed = 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t pos = pos0 + c;
-                const bool slot_ok = pos < (uint32_t)(Q + 3);
-                const uint32_t slot = pos < (uint32_t)Q ? pos : (slot_ok ? pos - Q : 0u);
-                const int32_t t = slot_ok && slot < (uint32_t)Q ? (int32_t)tile[slot * kRS + row] - (int32_t)slot : 0;
-                packed |= ((uint32_t)t & 0xffu) << (8 * c);
-            }
-            out4[w] = packed;
-        }
+        __syncthreads();
     }
 }
 
-// K1b: send rows of ranks [r0, r1) with no neighbour rows at hand (Alg. 5): entry i is entry i of the
-// receive schedule of the to-neighbour, which costs that neighbour's rounds 0..i.
-// Work lists for send entries left to Alg. 5 (k_send_recompute, k_batch).  Each lane working down its own entries
+template <int Q, int WANT>
+__global__ __launch_bounds__(kTileLanes) void k_sched(const SkipTab tab, uint32_t root, uint32_t r0, uint32_t r1,
+                                                      int32_t *__restrict__ recv_out, int32_t *__restrict__ send_out,
+                                                      slot_t *__restrict__ recvT, uint64_t ldT,
+                                                      int8_t *__restrict__ recvB, int8_t *__restrict__ sendB) {
+    __shared__ RowTiles<Q> tiles;
+    const uint64_t first = (uint64_t)blockIdx.x * kTileRanks;     // offset of this tile inside [r0, r1)
+    fill_row_tiles<Q, WANT>(tab, root, r0 + (uint32_t)first, tiles);
+    const uint64_t left = (uint64_t)r1 - r0 - first;
+    const uint32_t rows = left < (uint64_t)kTileRanks ? (uint32_t)left : (uint32_t)kTileRanks;
+    if constexpr ((WANT & kWantRecv) != 0) {
+        if (recv_out) byte_tile_to_rows<Q, kTileLanes>(tiles.recv, rows, recv_out + first * Q);
+        if (recvB) byte_tile_to_byte_rows<Q, kTileLanes>(tiles.recv, rows, recvB + first * byte_row_stride(Q));
+        if (recvT) {
+            // slot-major: each slot's kTileRanks bytes are one aligned piece of the table, whose rows are padded to a
+            // multiple of them (the last tile writes its idle lanes' bytes into the padding)
+            for (uint32_t g = threadIdx.x; g < (uint32_t)Q * (kTileRanks / 4); g += kTileLanes) {
+                const uint32_t k = g / (kTileRanks / 4), four = g % (kTileRanks / 4);
+                uint32_t packed = 0;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) packed |= (uint32_t)(uint8_t)tiles.recv[(four * 4u + c) * Q + k] << (8 * c);
+                *reinterpret_cast<uint32_t *>(recvT + (uint64_t)k * ldT + first + four * 4u) = packed;
+            }
+        }
+    }
+    if constexpr ((WANT & kWantSend) != 0) {
+        if (send_out) byte_tile_to_rows<Q, kTileLanes>(tiles.send, rows, send_out + first * Q);
+        if (sendB) byte_tile_to_byte_rows<Q, kTileLanes>(tiles.send, rows, sendB + first * byte_row_stride(Q));
+    }
+}
+
+// Work lists for send entries left to Alg. 5 (k_batch).  Each lane working down its own entries
 // makes a wave run as many turns as its unluckiest lane has entries, each turn as far as the largest k any lane asked
 // for; so the entries named by the lanes' masks (bit k of lane L: entry (L, k)) are made one list of the workgroup,
 // ranked by k and then by lane, and handed out one entry a lane: neighbouring places hold entries of the same k (and,
@@ -344,67 +245,6 @@ __device__ __forceinline__ void work_list(uint32_t mask, uint32_t (*wcnt)[32], u
         }
         __syncthreads();                                    // the next part of the list overwrites the queue
     }
-}
-
-constexpr int kRecomputeQueue = 4 * kBlock;                // entries of k_send_recompute's work list held at a time
-
-template <int Q, bool TAB>
-__global__ __launch_bounds__(kBlock) void k_send_recompute(const SkipTab tab, uint32_t root, uint32_t r0, uint32_t r1,
-                                                           int32_t *__restrict__ send_out,
-                                                           const uint32_t *__restrict__ dtab) {
-    __shared__ __align__(16) int8_t tile[kBlock * Q + 16];   // one byte an entry, laid out like the table
-    __shared__ uint32_t lowtab[kLowShapeBytes / 4];
-    __shared__ uint32_t wcnt[kBlock / 64][32], kstart[33];    // the work list of the entries left to Alg. 5
-    __shared__ uint16_t queue[kRecomputeQueue];
-    Uniform<Q> pol;
-#pragma unroll
-    for (int k = 0; k <= Q; ++k) pol.S[k] = tab.s[k];
-    pol.tab = &tab;
-    pol.low = reinterpret_cast<const uint8_t *>(lowtab);
-    const uint32_t p = pol.p();
-    stage_lowtab(lowtab, low_shape(p, Q));
-    __syncthreads();
-    const uint64_t first = (uint64_t)blockIdx.x * kBlock;
-    const uint64_t idx = first + threadIdx.x;
-    const uint64_t count = (uint64_t)r1 - r0;
-    const bool live = idx < count;
-    const uint32_t r = live ? (uint32_t)(r0 + idx) : root;
-    const uint32_t v = r >= root ? r - root : r + p - root;
-    int8_t *my = tile + threadIdx.x * Q;
-    // the entries that need none of the to-neighbour's rounds (bcs_core.h); for consecutive ranks and large p
-    // that is nearly all of them
-    auto digits_of = [&](uint32_t y) -> uint32_t {
-        if constexpr (TAB) return dtab[y];                // digit masks of all ranks from k_digits
-        else return digits(pol, y);
-    };
-    uint32_t pending = send_row_direct(pol, v, digits_of(v), digits_of, [&](int k, int val) { my[k] = (int8_t)val; });
-    pending = live ? pending : 0u;                            // lanes past the end replay the root and ask for nothing
-    // Alg. 5 for the rest, as a work list of the workgroup: a lane takes one entry (of any rank of the tile), the
-    // wave computes rounds 0..(its largest k) of each lane's to-neighbour and a lane keeps the entry of its own k
-    work_list<kBlock, kRecomputeQueue>(pending, wcnt, kstart, queue, [&](bool has, uint32_t who, int kk) {
-        int kmax = kk;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            const int other = __shfl_xor(kmax, off, 64);
-            kmax = other > kmax ? other : kmax;
-        }
-        kmax = __builtin_amdgcn_readfirstlane(kmax);
-        // the rank the entry belongs to: the tile's ranks are consecutive
-        const uint64_t idx2 = first + (has ? who : threadIdx.x);
-        const uint32_t r2 = idx2 < count ? (uint32_t)(r0 + idx2) : root;
-        const uint32_t v2 = r2 >= root ? r2 - root : r2 + p - root;
-        // skips[kk] by the closed form of Alg. 1's halving (kk differs from lane to lane)
-        uint32_t t = v2 + (kk >= 0 ? ((p - 1u) >> (Q - kk)) + 1u : 0u);
-        t = t >= p ? t - p : t;
-        int32_t got = 0;
-        auto own_entry = [&](int j, int val) { got = (j == kk) ? val : got; };
-        if constexpr (TAB) recv_row_tab_upto(pol, dtab, t, dtab[t], kmax, own_entry);
-        else recv_row(pol, t, kmax, own_entry);
-        if (has) tile[who * Q + kk] = (int8_t)got;
-    });
-    __syncthreads();
-    const uint64_t rows = (count - first) < (uint64_t)kBlock ? (count - first) : (uint64_t)kBlock;
-    byte_tile_to_rows<Q>(tile, (uint32_t)rows, send_out + first * Q);
 }
 
 // K3: unrelated (p, r, root) triples; rows of BCS_BATCH_STRIDE ints (one 128-byte line each), padded.

@@ -28,14 +28,14 @@ inline int hip_fail(hipError_t e) {
 // Optional per-kernel device timing (bcs_timing_begin / bcs_timing_end): while it is on, a launch is
 // given a start and a stop event from a fixed pool, so its duration is the device's own.
 enum KernelId {
-    kRecv = 0, kSendLookup, kSendRecompute, kBatch, kExpand, kFill, kValuPeak, kAllgather, kPackPlan, kPackCopy,
-    kRecvExpand, kSendExpand, kExpandRows, kRowsToBytes, kDigits, kPartnerTables, kKernelCount
+    kSched = 0, kBatch, kExpand, kFill, kValuPeak, kAllgather, kPackPlan, kPackCopy,
+    kRecvExpand, kSendExpand, kExpandRows, kRowsToBytes, kPartnerTables, kKernelCount
 };
 static_assert(kKernelCount == BCS_KERNEL_COUNT, "header and kernel list disagree");
-const char *const kKernelNames[kKernelCount] = {"k_recv_uniform", "k_send_lookup", "k_send_recompute", "k_batch",
-                                                "k_expand",       "k_fill",        "k_valu_peak",   "k_allgather_tables",
-                                                "k_pack_plan",    "k_pack_copy",   "k_recv_expand", "k_send_expand",
-                                                "k_expand_rows",  "k_rows_to_bytes", "k_digits",     "k_partner_tables"};
+const char *const kKernelNames[kKernelCount] = {"k_sched",       "k_batch",       "k_expand",      "k_fill",
+                                                "k_valu_peak",   "k_allgather_tables", "k_pack_plan", "k_pack_copy",
+                                                "k_recv_expand", "k_send_expand", "k_expand_rows", "k_rows_to_bytes",
+                                                "k_partner_tables"};
 struct Timing {
     bool on = false;
     int used = 0;
@@ -132,7 +132,7 @@ int host_skips(int32_t p, SkipTab &t) {
     return q;
 }
 
-// Fills g_lowtab on first use per device.  The fill is enqueued on the first caller's stream; until
+// Fills g_lowtab and g_lowrows on first use per device.  The fill is enqueued on the first caller's stream; until
 // it has finished, callers on other streams are made to wait for it on the device.
 struct LowTabState {
     bool launched = false;
@@ -156,6 +156,9 @@ int ensure_lowtab(hipStream_t st) {
         e = hipEventCreateWithFlags(&s.ready, hipEventDisableTiming);
         if (e != hipSuccess) return hip_fail(e);
         hipLaunchKernelGGL(k_build_lowtab, dim3((kLowTableBytes + kBlock - 1) / kBlock), dim3(kBlock), 0, st);
+        e = hipGetLastError();
+        if (e != hipSuccess) return hip_fail(e);
+        hipLaunchKernelGGL(k_build_lowrows, dim3((kRowsAll + kBlock - 1) / kBlock), dim3(kBlock), 0, st);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e);
         e = hipEventRecord(s.ready, st);
@@ -241,59 +244,32 @@ inline uint64_t round_up(uint64_t v, uint64_t m) { return (v + m - 1) / m * m; }
 // row length of the slot-major receive table (rows start on 256-byte boundaries)
 inline uint64_t slot_ld(int32_t p) { return round_up((uint64_t)p, 256); }
 
+// where the rows of a launch go besides the int32 tables: slot-major receive bytes (all ranks), byte rows of both tables
+struct RowCopies {
+    slot_t *recvT;
+    uint64_t ldT;
+    int8_t *recvB, *sendB;
+};
+
 template <int Q>
 int launch_sched(const SkipTab &tab, uint32_t root, uint32_t r0, uint32_t r1, int32_t *recv_out, int32_t *send_out,
-                 slot_t *recvT, uint64_t ldT, int8_t *recvB, int8_t *sendB, uint32_t *dtab, hipStream_t st) {
-    const uint64_t count = (uint64_t)r1 - r0;
-    const unsigned blocks = (unsigned)((count + kBlock - 1) / kBlock);
-    const bool full = (r0 == 0 && r1 == tab.s[Q]);
-    // the slot-major copy feeds the send look-up; with neither table asked for it is the only output
-    const bool want_t = full && recvT && (send_out || !recv_out);
-    if (recv_out || want_t) {
-        const bool tabbed = dtab != nullptr;     // one walk a rank (all p of them) into the table, the rows read it
-        if (tabbed)
-            launch(kDigits, k_digits<Q>, dim3((unsigned)(((uint64_t)tab.s[Q] + kBlock - 1) / kBlock)), dim3(kBlock), st,
-                   tab, dtab);
-        slot_t *const t_out = want_t ? recvT : (slot_t *)nullptr;
-        const uint32_t *const d_in = dtab;
-        if (full && recvB && recv_out) {
-            if (tabbed)
-                launch(kRecv, k_recv_uniform<Q, true, true>, dim3(blocks), dim3(kBlock), st, tab, root, r0, r1,
-                       recv_out, t_out, ldT, recvB, d_in);
-            else
-                launch(kRecv, k_recv_uniform<Q, true, false>, dim3(blocks), dim3(kBlock), st, tab, root, r0, r1,
-                       recv_out, t_out, ldT, recvB, d_in);
-        } else {
-            if (tabbed)
-                launch(kRecv, k_recv_uniform<Q, false, true>, dim3(blocks), dim3(kBlock), st, tab, root, r0, r1,
-                       recv_out, t_out, ldT, (int8_t *)nullptr, d_in);
-            else
-                launch(kRecv, k_recv_uniform<Q, false, false>, dim3(blocks), dim3(kBlock), st, tab, root, r0, r1,
-                       recv_out, t_out, ldT, (int8_t *)nullptr, d_in);
-        }
-    }
-    if (send_out) {
-        if (full) {
-            constexpr int G = Q >= kLookupBigMinQ ? kLookupBigG : kLookupSmallG;
-            launch(kSendLookup, k_send_lookup<Q, G>, dim3((unsigned)((count + G - 1) / G)), dim3(kLookupLanes), st, tab,
-                   (const slot_t *)recvT, ldT, send_out, sendB);
-        } else if (dtab) {
-            if (!recv_out)                      // no receive rows asked for: the table has not been filled yet
-                launch(kDigits, k_digits<Q>, dim3((unsigned)(((uint64_t)tab.s[Q] + kBlock - 1) / kBlock)), dim3(kBlock),
-                       st, tab, dtab);
-            launch(kSendRecompute, k_send_recompute<Q, true>, dim3(blocks), dim3(kBlock), st, tab, root, r0, r1, send_out,
-                   (const uint32_t *)dtab);
-        } else {
-            launch(kSendRecompute, k_send_recompute<Q, false>, dim3(blocks), dim3(kBlock), st, tab, root, r0, r1,
-                   send_out, (const uint32_t *)nullptr);
-        }
-    }
+                 const RowCopies &to, hipStream_t st) {
+    const unsigned blocks = (unsigned)(((uint64_t)r1 - r0 + kTileRanks - 1) / kTileRanks);
+    const bool recv = recv_out || to.recvT || to.recvB, send = send_out || to.sendB;
+    if (recv && send)
+        launch(kSched, k_sched<Q, kWantRecv | kWantSend>, dim3(blocks), dim3(kTileLanes), st, tab, root, r0, r1, recv_out,
+               send_out, to.recvT, to.ldT, to.recvB, to.sendB);
+    else if (recv)
+        launch(kSched, k_sched<Q, kWantRecv>, dim3(blocks), dim3(kTileLanes), st, tab, root, r0, r1, recv_out, send_out,
+               to.recvT, to.ldT, to.recvB, to.sendB);
+    else
+        launch(kSched, k_sched<Q, kWantSend>, dim3(blocks), dim3(kTileLanes), st, tab, root, r0, r1, recv_out, send_out,
+               to.recvT, to.ldT, to.recvB, to.sendB);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? BCS_OK : hip_fail(e);
 }
 
-typedef int (*LaunchFn)(const SkipTab &, uint32_t, uint32_t, uint32_t, int32_t *, int32_t *, slot_t *, uint64_t,
-                        int8_t *, int8_t *, uint32_t *, hipStream_t);
+typedef int (*LaunchFn)(const SkipTab &, uint32_t, uint32_t, uint32_t, int32_t *, int32_t *, const RowCopies &, hipStream_t);
 
 template <int... Qs>
 constexpr void fill_table(LaunchFn *t, std::integer_sequence<int, Qs...>) {
@@ -420,100 +396,50 @@ int64_t bcs_sched_workspace_bytes(int32_t p, int32_t r0, int32_t r1, int want_se
     return (int64_t)(slot_table_bytes(p, q) + digit_table_bytes(p));
 }
 
-int bcs_sched_rooted_ws(int32_t p, int32_t root, int32_t r0, int32_t r1, int32_t *recv_out, int32_t *send_out,
-                        void *workspace, size_t workspace_bytes, void *stream) {
-    int rc = check_range(p, root, r0, r1);
-    if (rc != BCS_OK) return rc;
-    if (!recv_out && !send_out) return BCS_EINVAL;
+namespace {
+// the rows themselves need no scratch; arguments are checked
+int sched_rows(int32_t p, int32_t root, int32_t r0, int32_t r1, int32_t *recv_out, int32_t *send_out, hipStream_t st) {
     const int q = host_q(p);
     if (q == 0 || r0 == r1) return BCS_OK;
-    const int64_t need = bcs_sched_workspace_bytes(p, r0, r1, send_out != nullptr);
-    if (need > 0 && (!workspace || workspace_bytes < (size_t)need)) return BCS_ENOMEM;
-    if (need > 0 && (((uintptr_t)workspace) & 255u)) return BCS_EINVAL;     // tables are read 4 and 16 bytes at a time
     SkipTab tab;
     host_skips(p, tab);
-    rc = ensure_lowtab((hipStream_t)stream);
+    const int rc = ensure_lowtab(st);
     if (rc != BCS_OK) return rc;
-    const uint64_t ld = slot_ld(p);
-    // all ranks: the digit table sits behind the slot-major table; a call for receive rows alone needs no
-    // workspace, and uses one that holds the digit table if it is given
-    const bool full = (r0 == 0 && r1 == p);
-    uint32_t *dtab = nullptr;
-    const uint64_t dbytes = digit_table_bytes(p);
-    if (need > 0 && dbytes > 0) dtab = (uint32_t *)((char *)workspace + (full ? slot_table_bytes(p, q) : 0));
-    else if (need == 0 && dbytes > 0 && full && workspace && workspace_bytes >= dbytes &&
-             ((uintptr_t)workspace & 3u) == 0)
-        dtab = (uint32_t *)workspace;
-    return launch_for_q(q)(tab, (uint32_t)root, (uint32_t)r0, (uint32_t)r1, recv_out, send_out,
-                           need > 0 && full ? (slot_t *)workspace : nullptr, ld, nullptr, nullptr, dtab,
-                           (hipStream_t)stream);
+    return launch_for_q(q)(tab, (uint32_t)root, (uint32_t)r0, (uint32_t)r1, recv_out, send_out, RowCopies{}, st);
+}
+}  // namespace
+
+int bcs_sched_rooted_ws(int32_t p, int32_t root, int32_t r0, int32_t r1, int32_t *recv_out, int32_t *send_out,
+                        void *workspace, size_t workspace_bytes, void *stream) {
+    const int rc = check_range(p, root, r0, r1);
+    if (rc != BCS_OK) return rc;
+    if (!recv_out && !send_out) return BCS_EINVAL;
+    if (host_q(p) == 0 || r0 == r1) return BCS_OK;
+    // the contract of the call: a workspace of the stated size, though this construction leaves it alone
+    const int64_t need = bcs_sched_workspace_bytes(p, r0, r1, send_out != nullptr);
+    if (need > 0 && (!workspace || workspace_bytes < (size_t)need)) return BCS_ENOMEM;
+    if (need > 0 && (((uintptr_t)workspace) & 255u)) return BCS_EINVAL;
+    return sched_rows(p, root, r0, r1, recv_out, send_out, (hipStream_t)stream);
 }
 
 int bcs_sched_rooted(int32_t p, int32_t root, int32_t r0, int32_t r1, int32_t *recv_out, int32_t *send_out,
                      void *stream) {
-    int rc = check_range(p, root, r0, r1);
+    const int rc = check_range(p, root, r0, r1);
     if (rc != BCS_OK) return rc;
     if (!recv_out && !send_out) return BCS_EINVAL;
-    const int64_t need = bcs_sched_workspace_bytes(p, r0, r1, send_out != nullptr);
-    void *ws = nullptr;
-    if (need > 0 && r0 != r1) {
-        rc = scratch_get((size_t)need, (hipStream_t)stream, &ws);
-        if (rc != BCS_OK) return rc;
-    }
-    return bcs_sched_rooted_ws(p, root, r0, r1, recv_out, send_out, ws, (size_t)need, stream);
+    return sched_rows(p, root, r0, r1, recv_out, send_out, (hipStream_t)stream);
 }
-
-}  // extern "C"
-
-namespace {
-// Scratch of bcs_sched_rooted_static: a fixed array in the code object, one copy per GPU.  In host code the
-// array's name is only a handle for hipGetSymbolAddress; kernels and every other use take the address that
-// call returns for the current device.
-static __device__ __align__(256) unsigned char scratch[BCS_STATIC_SCRATCH_BYTES];
-
-struct StaticScratch {
-    void *ptr = nullptr;
-    bool ready = false;
-};
-StaticScratch g_static[kMaxDevices];
-std::mutex g_static_mutex;
-
-int static_scratch(void **out) {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return hip_fail(e);
-    if (dev < 0 || dev >= kMaxDevices) return BCS_EINVAL;
-    std::lock_guard<std::mutex> lock(g_static_mutex);
-    StaticScratch &s = g_static[dev];
-    if (!s.ready) {
-        void *ptr = nullptr;
-        e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));      // this device's copy
-        if (e != hipSuccess) return hip_fail(e);
-        if (!ptr || (((uintptr_t)ptr) & 255u)) return BCS_EINVAL;
-        s.ptr = ptr;
-        s.ready = true;
-    }
-    *out = s.ptr;
-    return BCS_OK;
-}
-}  // namespace
-
-extern "C" {
 
 int bcs_sched_rooted_static(int32_t p, int32_t root, int32_t r0, int32_t r1, int32_t *recv_out, int32_t *send_out,
                             void *stream) {
-    int rc = check_range(p, root, r0, r1);
+    const int rc = check_range(p, root, r0, r1);
     if (rc != BCS_OK) return rc;
     if (!recv_out && !send_out) return BCS_EINVAL;
+    // the stated limit of the call
     const int64_t need = bcs_sched_workspace_bytes(p, r0, r1, send_out != nullptr);
     if (need < 0) return (int)need;
     if ((uint64_t)need > (uint64_t)BCS_STATIC_SCRATCH_BYTES) return BCS_ETOOBIG;
-    void *ws = nullptr;
-    if (need > 0 && r0 != r1) {
-        rc = static_scratch(&ws);
-        if (rc != BCS_OK) return rc;
-    }
-    return bcs_sched_rooted_ws(p, root, r0, r1, recv_out, send_out, ws, ws ? (size_t)need : 0, stream);
+    return sched_rows(p, root, r0, r1, recv_out, send_out, (hipStream_t)stream);
 }
 
 int bcs_sched(int32_t p, int32_t r0, int32_t r1, int32_t *recv_out, int32_t *send_out, void *stream) {
@@ -694,10 +620,8 @@ int bcs_sched_expand_ws(int32_t p, int32_t root, int32_t n, int32_t *recv_out, i
             const uint64_t pieces = (ra.total + kBlock * 4 - 1) / (kBlock * 4);
             if (pieces > 0x7fffffffull) return BCS_EINVAL;
             int8_t *recvB = (int8_t *)workspace + base, *sendB = recvB + rows_bytes;
-            rc = launch_for_q(q)(tab, (uint32_t)root, 0u, (uint32_t)p, recv_out, send_out, (slot_t *)workspace,
-                                 slot_ld(p), recvB, sendB,
-                                 digit_table_bytes(p) ? (uint32_t *)((char *)workspace + slot_table_bytes(p, q)) : nullptr,
-                                 (hipStream_t)stream);
+            rc = launch_for_q(q)(tab, (uint32_t)root, 0u, (uint32_t)p, recv_out, send_out,
+                                 RowCopies{nullptr, 0, recvB, sendB}, (hipStream_t)stream);
             if (rc != BCS_OK) return rc;
             int32_t *outs[2] = {recv_blocks, send_blocks};
             const int8_t *srcs[2] = {recvB, sendB};
@@ -791,8 +715,7 @@ int bcs_allgather_tables_ws(int32_t p, int32_t n, int32_t r, int32_t *pack_idx, 
     if (rc != BCS_OK) return rc;
     const uint64_t ld = slot_ld(p);
     slot_t *recvT = (slot_t *)workspace;
-    uint32_t *dtab = digit_table_bytes(p) ? (uint32_t *)((char *)workspace + slot_table_bytes(p, q)) : nullptr;
-    rc = launch_for_q(q)(tab, 0u, 0u, (uint32_t)p, nullptr, nullptr, recvT, ld, nullptr, nullptr, dtab, st);
+    rc = launch_for_q(q)(tab, 0u, 0u, (uint32_t)p, nullptr, nullptr, RowCopies{recvT, ld, nullptr, nullptr}, st);
     if (rc != BCS_OK) return rc;
     const unsigned bx = (unsigned)(((uint64_t)p + kAgChunk - 1) / kAgChunk);
     const uint32_t x = (uint32_t)((q - (int)(R % (uint64_t)q)) % q);
