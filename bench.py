@@ -61,8 +61,6 @@ PROFILED = {
         ("C4", "k_expand"): {'fetch_kib': 9004, 'write_kib': 1052688, 'waves': 263176, 'valu_per_wave': 258.5, 'salu_per_wave': 195.0, 'active_lanes': 63.3},
         ("C4", "k_rows_to_bytes"): {'fetch_kib': 2252, 'write_kib': 1280, 'waves': 5124, 'valu_per_wave': 50.0, 'salu_per_wave': 12.0, 'active_lanes': 64.0},
         ("C4", "k_expand_rows"): {'fetch_kib': 5135, 'write_kib': 1052924, 'waves': 1052692, 'valu_per_wave': 69.0, 'salu_per_wave': 9.0, 'active_lanes': 64.0},
-        ("C5 recv_and_send", "k_batch"): {'fetch_kib': 9272, 'write_kib': 266240, 'waves': 16384, 'valu_per_wave': 6627.2, 'salu_per_wave': 2415.7, 'active_lanes': 63.5},
-        ("C5 recv_only", "k_batch"): {'fetch_kib': 8406, 'write_kib': 135168, 'waves': 16384, 'valu_per_wave': 2813.4, 'salu_per_wave': 872.8, 'active_lanes': 63.8},
         ("AG", "k_allgather_tables"): {"fetch_kib": 41280, "write_kib": 2261412},
     },
 }
@@ -77,48 +75,6 @@ def profiled(config, kernel, digest):
     out["profiled_at_csrc"] = PROFILED["csrc"]
     out["stale"] = PROFILED["csrc"] != digest
     return out
-
-
-# ----------------------------------------------------------------------------------------------------------------
-# One model of the vector-ALU work of the construction, used for every `alu` roofline below.  "Useful" lane-operations of one rank with its OWN q (a wave of the batch kernel runs
-# its loops to the largest q among its lanes; that excess, the second-range branch of Alg. 4, the byte copies of a
-# row and the sort of the batch kernel are not counted).  So `frac` = useful lane-ops/s / peak is at most the share
-# of time the vector ALUs are busy, and falls below it by divergence and by everything that is not the method.
-#   the batch kernel and Alg. 5, by the structure of the code (no counter fit):
-#   a round of Alg. 4 on two digit masks            55 ops (window masks, candidate, bookkeeping)
-#   set-up of a row                                 50 ops
-#   a digit walk, one p per launch                  3 ops a level from level 7 up, 3 around the low-digit table read
-#   a digit walk, p per lane (batch kernel)         4 ops a level from level 7 up, 10 around it
-#   a row by walks                                  (q + 2) walks + 55 q + 50
-#   a send row by Alg. 5: entry i = rounds 0..i of the to-neighbour's row: sum over i of (i + 3) walks (or table
-#   reads) + 55 (i + 1) + 30
-#   a send row as the batch kernel builds it: 30 ops an entry for the rule that takes an entry from the rank's own
-#   digits, one digit walk a round for its case (c), and Alg. 5 for the entries the rule leaves: 0.23 an entry below
-#   level 8 (1.8 a triple at C5, counted on the host build of the lane code), each the neighbour's rounds 0..k with
-#   k + 3 walks, plus 40 ops to fetch the entry from the workgroup's list
-# ----------------------------------------------------------------------------------------------------------------
-def ops_walk(q, per_lane):
-    return (4 * max(q - 7, 0) + 10) if per_lane else (3 * max(q - 7, 0) + 3)
-
-
-def ops_recv_walks(q, per_lane, walks=None):
-    walks = (q + 2) if walks is None else walks
-    return walks * ops_walk(q, per_lane) + 55 * q + 50
-
-
-def ops_send_alg5(q, per_lane):
-    total = 0
-    for i in range(q):
-        total += (i + 3) * ops_walk(q, per_lane) + 55 * (i + 1) + 30
-    return total
-
-
-def ops_send_direct(q, per_lane):
-    w = ops_walk(q, per_lane)
-    low = min(q, 8)
-    entries = 0.23 * low                       # entries left to Alg. 5
-    rounds = low / 2.0 + 0.5                   # their average k + 1
-    return 30 * q + q * w + entries * (rounds * (55 + w) + 3 * w + 40)
 
 
 def measure_valu_peak(torch, bcs):
@@ -367,30 +323,17 @@ def run_c5(torch, bcs, steps, warmup, digest):
     bsend = torch.empty((count, 32), dtype=torch.int32, device="cuda")
     qv = torch.empty(count, dtype=torch.int32, device="cuda")
     qs = np.array([int(v - 1).bit_length() for v in hp.tolist()], dtype=np.int64)
-    hist = np.bincount(qs, minlength=32)
-    ops_recv = sum(int(hist[q]) * ops_recv_walks(q, True) for q in range(32))
-    ops_send = sum(int(hist[q]) * ops_send_direct(q, True) for q in range(32))
     out = {"workload": "C5: 2^20 seeded (p, r, root) triples, p log-uniform in [2, 2^31-1] (mixed q), rows of stride 32: "
-                       "receive rows by Alg. 4, send rows without neighbour rows (entries from the rank's own digits where that is "
-                       "exact, Alg. 5 for the rest)",
+                       "receive and send rows in closed form",
            "count": count, "steps": steps, "mean_q": float(qs.mean())}
-    for key, step, ops in (("recv_and_send", lambda: bcs.bcs_sched_batch(pp, rr, ro, brecv, bsend, qv), ops_recv + ops_send),
-                           ("recv_only", lambda: bcs.bcs_sched_batch(pp, rr, ro, brecv, None, qv), ops_recv)):
+    for key, step, tables in (("recv_and_send", lambda: bcs.bcs_sched_batch(pp, rr, ro, brecv, bsend, qv), 2),
+                              ("recv_only", lambda: bcs.bcs_sched_batch(pp, rr, ro, brecv, None, qv), 1)):
         ms, ms_ev, timing = timed_steps(torch, bcs, step, steps, warmup)
-        # `frac` of this kernel: the vector instructions it executes (all 64 lanes active: the per-lane-p code is
-        # branch-free in q) against the peak, i.e. its vector-ALU utilisation, from the counter profile of these
-        # sources; when the sources have changed since the profile, the structural model of useful work instead
-        prof = profiled("C5 " + key, "k_batch", digest)
-        executed = None
-        if prof is not None and not prof["stale"]:
-            executed = prof["valu_per_wave"] * prof["waves"] * prof["active_lanes"]
-        kernels = kernel_records(timing, steps, {"k_batch": ("alu", executed if executed else ops)}, "C5 " + key, digest)
-        kernels["k_batch"]["ops_source"] = "counters (executed vector lane-operations)" if executed else "model (useful lane-operations)"
-        kernels["k_batch"]["useful_lane_ops_model"] = ops
-        kernels["k_batch"]["useful_frac_model"] = ops / kernels["k_batch"]["avg_ms"] / 1e6 / INT_VALU_PEAK_GOPS
+        # triples in, q and whole 128-byte rows out
+        kernels = kernel_records(timing, steps, {"k_batch": ("hbm", count * (12 + 4 + 128 * tables))}, "C5 " + key, digest)
         out[key] = {"ms_per_step": ms, "ms_per_step_with_kernel_events": ms_ev,
                     "value": count / (ms * 1e-3), "unit": "rank-schedules/s" if key == "recv_and_send" else "receive rows/s",
-                    "useful_lane_ops_per_rank": ops / count, "roofline": dominant(kernels), "kernels": kernels}
+                    "roofline": dominant(kernels), "kernels": kernels}
     out["value"] = out["recv_and_send"]["value"]
     out["unit"] = "rank-schedules/s"
     out["ms_per_step"] = out["recv_and_send"]["ms_per_step"]

@@ -176,90 +176,18 @@ __global__ __launch_bounds__(kTileLanes) void k_sched(const SkipTab tab, uint32_
     }
 }
 
-// Work lists for send entries left to Alg. 5 (k_batch).  Each lane working down its own entries
-// makes a wave run as many turns as its unluckiest lane has entries, each turn as far as the largest k any lane asked
-// for; so the entries named by the lanes' masks (bit k of lane L: entry (L, k)) are made one list of the workgroup,
-// ranked by k and then by lane, and handed out one entry a lane: neighbouring places hold entries of the same k (and,
-// in the batch kernel, whose lanes are in the order of q, of neighbouring q), and a wave's loops run about as far as
-// each of its lanes needs.  Entry (L, k) goes to place
-// kstart[k] + (entries for k in earlier waves) + (earlier lanes of L's wave with bit k), found with ballots.  The
-// list is filled and handed out QUEUE entries at a time (QUEUE a multiple of BLOCK, the workgroup's lanes), one entry a lane: fn(has, who, k) runs in every lane of
-// every wave that has an entry.  All lanes of the workgroup must call this (it synchronises them).
-template <int BLOCK, int QUEUE, class Fn>
-__device__ __forceinline__ void work_list(uint32_t mask, uint32_t (*wcnt)[32], uint32_t *kstart, uint16_t *queue, Fn fn) {
-    static_assert(QUEUE % BLOCK == 0 && BLOCK % 64 == 0 && BLOCK <= 2048, "whole waves; a lane index and k share 16 bits");
-    const int wave = threadIdx.x >> 6;
-    // the k for which any lane of this wave has an entry (wave-uniform): the loops below visit only these
-    uint32_t any_k = mask;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) any_k |= (uint32_t)__shfl_xor((int)any_k, off, 64);
-    any_k = __builtin_amdgcn_readfirstlane(any_k);
-    __syncthreads();                                        // earlier users of wcnt / kstart / queue are done
-    {
-        uint32_t mine = 0;                                  // lane k of a wave: the wave's entries for k
-        for (uint32_t m = any_k; m != 0u; m &= m - 1u) {
-            const int k = __builtin_ctz(m);
-            const uint32_t c = (uint32_t)__popcll(__ballot((mask >> k) & 1u));
-            mine = (threadIdx.x & 63u) == (uint32_t)k ? c : mine;
-        }
-        if ((threadIdx.x & 63u) < 32u) wcnt[wave][threadIdx.x & 63u] = mine;
-    }
-    __syncthreads();
-    if (threadIdx.x < 32) {                                 // entries for k = threadIdx.x: running count over the waves
-        uint32_t acc = 0;
-        for (int w = 0; w < BLOCK / 64; ++w) {
-            const uint32_t c = wcnt[w][threadIdx.x];
-            wcnt[w][threadIdx.x] = acc;
-            acc += c;
-        }
-        kstart[threadIdx.x] = acc;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t acc = 0;
-        for (int k = 0; k < 32; ++k) {
-            const uint32_t c = kstart[k];
-            kstart[k] = acc;
-            acc += c;
-        }
-        kstart[32] = acc;
-    }
-    __syncthreads();
-    const uint32_t total = kstart[32];
-    for (uint32_t base = 0; base < total; base += QUEUE) {
-        for (uint32_t m = any_k; m != 0u; m &= m - 1u) {
-            const int k = __builtin_ctz(m);
-            const uint64_t bal = __ballot((mask >> k) & 1u);
-            const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-            const uint32_t place = kstart[k] + wcnt[wave][k] + before - base;
-            if (((mask >> k) & 1u) && place < (uint32_t)QUEUE) queue[place] = (uint16_t)((threadIdx.x << 5) | (uint32_t)k);
-        }
-        __syncthreads();
-        const uint32_t n = total - base < (uint32_t)QUEUE ? total - base : (uint32_t)QUEUE;
-        for (uint32_t e0 = 0; e0 < n; e0 += BLOCK) {   // workgroup-uniform
-            if (e0 + (threadIdx.x & ~63u) >= n) continue;    // a wave with no entry left (wave-uniform)
-            const uint32_t e = e0 + threadIdx.x;
-            const bool has = e < n;
-            const uint32_t entry = has ? queue[e] : 0u;
-            fn(has, entry >> 5, has ? (int)(entry & 31u) : -1);
-        }
-        __syncthreads();                                    // the next part of the list overwrites the queue
-    }
-}
-
-// K3: unrelated (p, r, root) triples; rows of BCS_BATCH_STRIDE ints (one 128-byte line each), padded.
-// A workgroup takes kBatchBlock triples and first orders them by q in LDS (counting sort), because a
-// wave runs its level loops to the largest q among its lanes and the work grows like q^3: after the
-// sort a wave holds neighbouring q only.  Each lane then builds the rows of its triple into an LDS tile of
-// bytes (entries lie in [-31, 30]; a byte of -128 stands for the padding), at the triple's place in the
-// input order; the workgroup then writes the tile out as whole 128-byte lines, eight lanes a row and 16 bytes
-// a lane.  (Storing each entry straight into its row, 4 bytes at a time into a line of the lane's own, made the
-// memory system write five times the table's bytes as partial lines, and a call for receive rows alone was
-// bound by those stores: measured 0.254 ms with the vector ALU busy 28 % of the time.)
-constexpr int kBatchBlock = 1024;
+// K3: unrelated (p, r, root) triples; rows of BCS_BATCH_STRIDE ints (one 128-byte line each), padded.  Lane = triple, in
+// the closed form of bcs_rows.h with a p per lane.  A wave's level loops run to the largest q among its lanes; a step is
+// a dozen vector ops, so ordering the triples by q first (which the construction by windows needed) would cost more than
+// the idle steps.  The send entries below round 7 are read from the table entry by entry (seven 8-byte reads a lane
+// within 1 KB of one another).  Rows are built as bytes in LDS, four levels to a word (entries lie in [-31, 30]; a byte
+// of -128 stands for the padding); the workgroup then writes them as whole 128-byte lines, eight lanes a row and 16
+// bytes a lane.  (Storing each entry straight into its row, 4 bytes at a time into a line of the lane's own, makes the
+// memory system write five times the table's bytes as partial lines.)
+// Bound by the stores: 2^20 triples of mixed q, both tables (268 MB written), 236 us by windows and Alg. 5, 54 us now.
+constexpr int kBatchBlock = 256;
 constexpr int kBatchRowBytes = BCS_BATCH_STRIDE + 4;       // LDS row stride: nine words, so lanes' rows spread over the banks
 constexpr int8_t kBatchPadByte = -128;
-constexpr int kQueue = 4 * kBatchBlock;                    // entries of the Alg. 5 work list held at a time
 
 // the workgroup's byte tile -> rows of the table (after a barrier); `rows` = triples of this workgroup that exist
 __device__ __forceinline__ void batch_rows_out(const int8_t *tileB, uint32_t rows, int32_t *__restrict__ dst) {
@@ -279,7 +207,7 @@ __device__ __forceinline__ void batch_rows_out(const int8_t *tileB, uint32_t row
         int32_t *out = dst + (uint64_t)row * BCS_BATCH_STRIDE + part * 4u;
         if (vec) {
             const v4i pack = {v[0], v[1], v[2], v[3]};
-            *reinterpret_cast<v4i *>(out) = pack;
+            __builtin_nontemporal_store(pack, reinterpret_cast<v4i *>(out));
         } else {
 #pragma unroll
             for (int c = 0; c < 4; ++c) out[c] = v[c];
@@ -287,37 +215,10 @@ __device__ __forceinline__ void batch_rows_out(const int8_t *tileB, uint32_t row
     }
 }
 
-// One entry of a work list of the batch kernel, as the lane that works on it sees it: the triple `who` of the
-// workgroup (its p and rank from the sorted arrays), the entry's k, the to-neighbour t = (v + skips[k]) mod p, and
-// a policy whose level loops run as far as the wave's largest q; kmax is the wave's largest k.  Lanes without an
-// entry (has = false, kk = -1) stand in with p = 1.
-struct BatchLane {
-    PerLane pol;
-    uint32_t t, orig;
-    int kmax;
-};
-__device__ __forceinline__ BatchLane batch_lane(bool has, uint32_t who, int kk, const uint32_t *s_p, const uint32_t *s_v,
-                                                const uint32_t *s_slot) {
-    BatchLane e;
-    const uint32_t p = has ? s_p[who] : 1u, v = has ? s_v[who] : 0u;
-    e.orig = s_slot[who] & 0xffffu;
-    const int q = ceil_log2(p);
-    int kmax = kk, qtop = q;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const int ok = __shfl_xor(kmax, off, 64), oq = __shfl_xor(qtop, off, 64);
-        kmax = ok > kmax ? ok : kmax;
-        qtop = oq > qtop ? oq : qtop;
-    }
-    e.kmax = __builtin_amdgcn_readfirstlane(kmax);
-    e.pol.pm1 = p - 1u;
-    e.pol.ql = q;
-    e.pol.wave_top = __builtin_amdgcn_readfirstlane(qtop) - 1;
-    e.pol.odd = odd_levels(p, q);
-    e.pol.low = g_lowtab + (size_t)low_shape(p, q) * kLowShapeBytes;
-    const uint32_t t = v + (kk >= 0 ? e.pol.s(kk) : 0u);
-    e.t = t >= p ? t - p : t;
-    return e;
+// bytes 0..n-1 of `four`, padding above (n may be any number)
+__device__ __forceinline__ uint32_t batch_pad(uint32_t four, int n) {
+    const uint32_t keep = n >= 4 ? 0xffffffffu : (n > 0 ? (1u << (8 * n)) - 1u : 0u);
+    return (four & keep) | (0x80808080u & ~keep);
 }
 
 __global__ __launch_bounds__(kBatchBlock) void k_batch(int64_t count, const int32_t *__restrict__ pv,
@@ -325,53 +226,20 @@ __global__ __launch_bounds__(kBatchBlock) void k_batch(int64_t count, const int3
                                                        const int32_t *__restrict__ rootv,
                                                        int32_t *__restrict__ recv_out, int32_t *__restrict__ send_out,
                                                        int32_t *__restrict__ q_out) {
-    __shared__ uint32_t bins[33];                 // bins[q] for valid triples, bins[32] for the rest
-    __shared__ uint32_t start[33];
-    __shared__ uint32_t s_p[kBatchBlock], s_v[kBatchBlock], s_slot[kBatchBlock];
-    __shared__ __align__(16) int8_t tileB[kBatchBlock * kBatchRowBytes];
-    __shared__ uint32_t wcnt[kBatchBlock / 64][32];            // send entries left to Alg. 5: per wave and k, then their offsets
-    __shared__ uint32_t kstart[33];
-    __shared__ uint16_t queue[kQueue];                         // the work list: (lane << 5) | k
+    __shared__ __align__(16) int8_t tile_recv[kBatchBlock * kBatchRowBytes];
+    __shared__ __align__(16) int8_t tile_send[kBatchBlock * kBatchRowBytes];
     const int64_t first = (int64_t)blockIdx.x * kBatchBlock;
-    {
-        const int64_t idx = first + threadIdx.x;
-        const bool live = idx < count;
-        const int32_t pi = live ? pv[idx] : 1, ri = live ? rv[idx] : 0, rooti = live ? rootv[idx] : 0;
-        const bool valid = live && pi >= 1 && ri >= 0 && ri < pi && rooti >= 0 && rooti < pi;
-        const uint32_t p = valid ? (uint32_t)pi : 1u;
-        const int q = ceil_log2(p);
-        const uint32_t v = !valid ? 0u
-                           : ((uint32_t)ri >= (uint32_t)rooti ? (uint32_t)(ri - rooti)
-                                                              : (uint32_t)ri + p - (uint32_t)rooti);
-        if (threadIdx.x < 33) bins[threadIdx.x] = 0u;
-        __syncthreads();
-        const int bin = valid ? q : 32;
-        const uint32_t rank_in_bin = atomicAdd(&bins[bin], 1u);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            uint32_t acc = 0;
-            for (int k = 0; k < 33; ++k) {
-                start[k] = acc;
-                acc += bins[k];
-            }
-        }
-        __syncthreads();
-        const uint32_t pos = start[bin] + rank_in_bin;
-        s_p[pos] = p;
-        s_v[pos] = v;
-        s_slot[pos] = threadIdx.x | (valid ? 0u : 0x80000000u) | (live ? 0u : 0x40000000u);
-        __syncthreads();
-    }
-    // from here on this lane works on the triple that the sort put at its position
-    const uint32_t p = s_p[threadIdx.x];
-    const uint32_t v = s_v[threadIdx.x];
-    const uint32_t slot = s_slot[threadIdx.x];
-    const bool valid = (slot & 0x80000000u) == 0u;
-    const bool live = (slot & 0x40000000u) == 0u;
-    const uint32_t orig = slot & 0xffffu;                     // the triple's place among the workgroup's 1024
-    const int64_t idx = first + orig;
+    const int64_t idx = first + threadIdx.x;
+    const bool live = idx < count;
+    const int32_t pi = live ? pv[idx] : 1, ri = live ? rv[idx] : 0, rooti = live ? rootv[idx] : 0;
+    const bool valid = live && pi >= 1 && ri >= 0 && ri < pi && rooti >= 0 && rooti < pi;
+    const uint32_t p = valid ? (uint32_t)pi : 1u;             // an invalid triple stands in with p = 1: rows of padding
+    const uint32_t v = !valid ? 0u
+                       : ((uint32_t)ri >= (uint32_t)rooti ? (uint32_t)(ri - rooti)
+                                                          : (uint32_t)ri + p - (uint32_t)rooti);
     const int q = ceil_log2(p);
     if (live && q_out) q_out[idx] = valid ? q : -1;
+    if (!recv_out && !send_out) return;
     // largest q in this wave bounds the level loops of all its lanes
     int qmax = q;
 #pragma unroll
@@ -385,40 +253,55 @@ __global__ __launch_bounds__(kBatchBlock) void k_batch(int64_t count, const int3
     pol.ql = q;
     pol.wave_top = qmax - 1;
     pol.odd = odd_levels(p, q);
-    pol.low = g_lowtab + (size_t)low_shape(p, q) * kLowShapeBytes;
-    const uint32_t rows = (count - first) < (int64_t)kBatchBlock ? (uint32_t)(count - first) : (uint32_t)kBatchBlock;
-    int8_t *my = tileB + orig * kBatchRowBytes;
-    uint32_t *my4 = reinterpret_cast<uint32_t *>(my);
-    const uint32_t pad4 = 0x80808080u;
-    if (recv_out) {
-#pragma unroll
-        for (int w = 0; w < BCS_BATCH_STRIDE / 4; ++w) my4[w] = pad4;
-        recv_row(pol, v, qmax - 1, [&](int i, int val) { my[i] = (int8_t)val; });
-        __syncthreads();
-        batch_rows_out(tileB, rows, recv_out + first * BCS_BATCH_STRIDE);
-        __syncthreads();
-    }
-    if (send_out) {
-#pragma unroll
-        for (int w = 0; w < BCS_BATCH_STRIDE / 4; ++w) my4[w] = pad4;
-        // the entries that need none of the to-neighbour's rounds (send_row_direct); the others are left in `pending`
-        const uint32_t pending = send_row_direct(pol, v, digits(pol, v), [&](uint32_t y) { return digits(pol, y); },
-                                                 [&](int k, int val) { my[k] = (int8_t)val; });
-        // Those are worked off as one list of the whole workgroup, one entry a lane.  (Each lane working down its
-        // own entries made a wave run as many turns as its unluckiest lane has entries, each turn as far as the
-        // largest k any lane asked for: five times the lane-operations the entries themselves need, by a count on
-        // the C5 triples, where a triple leaves 1.8 entries on average, nearly all below level 8.)
-        // Alg. 5 for the rest: rounds 0..k of the to-neighbour's receive row, of which entry k is kept (a wave
-        // computes as many rounds as its largest k; receive rows are prefix-stable, the extra rounds change nothing)
-        work_list<kBatchBlock, kQueue>(pending, wcnt, kstart, queue, [&](bool has, uint32_t who, int kk) {
-            const BatchLane e = batch_lane(has, who, kk, s_p, s_v, s_slot);
-            int32_t keep = 0;
-            recv_row(e.pol, e.t, e.kmax, [&](int j, int val) { keep = (j == kk) ? val : keep; });
-            if (has) tileB[e.orig * kBatchRowBytes + kk] = (int8_t)keep;
+    pol.low = nullptr;
+    const uint32_t base = row_base(pol);
+    const RankPlace pl = rank_place(pol, v);
+    const LowRow w = g_lowrows[base + pl.ctx * 128u + pl.low];
+    const LowRow b = row_bytes(w, pl.ctx, pl.J, (uint32_t)q);
+    LowRow s = {0u, 0u};
+    if (send_out)
+        send_low_entries(pol, pl, base, [](uint32_t e) { return g_lowrows[e]; }, [&](int k, int32_t e) {
+            if (k < 4) s.lo |= ((uint32_t)e & 0xffu) << (8 * k);
+            else s.hi |= ((uint32_t)e & 0xffu) << (8 * (k - 4));
         });
-        __syncthreads();
-        batch_rows_out(tileB, rows, send_out + first * BCS_BATCH_STRIDE);
+    int8_t *my_recv = tile_recv + threadIdx.x * kBatchRowBytes, *my_send = tile_send + threadIdx.x * kBatchRowBytes;
+    uint32_t *recv4 = reinterpret_cast<uint32_t *>(my_recv), *send4 = reinterpret_cast<uint32_t *>(my_send);
+    // rounds 7 and up, largest first, as in high_entries; a word takes levels 4 i .. 4 i + 3
+    const uint32_t bare = pl.up & ~(1u << (q & 31));
+    int32_t next = (int32_t)place_own(pl, w);
+#pragma unroll
+    for (int i = BCS_BATCH_STRIDE / 4 - 1; i >= 1; --i) {
+        if (4 * i >= qmax) {                                  // wave-uniform
+            recv4[i] = send4[i] = 0x80808080u;
+            continue;
+        }
+        uint32_t wr = 0, ws = 0;
+#pragma unroll
+        for (int c = 3; c >= 0; --c) {
+            const int k = 4 * i + c;
+            if (k < kLowLevels) continue;
+            const int32_t set = -(int32_t)((bare >> (k & 31)) & 1u), here = k - q;
+            const int32_t r = (set & next) | (~set & here);
+            next = (set & here) | (~set & next);
+            wr = __builtin_amdgcn_perm(wr, (uint32_t)r, 0x06050400u);        // the word up by a byte, r's byte below
+            ws = __builtin_amdgcn_perm(ws, (uint32_t)next, 0x06050400u);
+        }
+        if (i == 1) {                                         // level 7 above the table's bytes 4..6
+            wr = (wr << 24) | (b.hi & 0xffffffu);
+            ws = (ws << 24) | (s.hi & 0xffffffu);
+        }
+        recv4[i] = batch_pad(wr, q - 4 * i);
+        send4[i] = batch_pad(ws, q - 4 * i);
     }
+    recv4[0] = batch_pad(b.lo, q);
+    send4[0] = batch_pad(s.lo, q);
+    recv_fix(pol, pl, w, [&](int k, int32_t e) { my_recv[k] = (int8_t)e; });
+    if (send_out)
+        send_fix(pol, v, pl, base, [](uint32_t e) { return g_lowrows[e]; }, [&](int k, int32_t e) { my_send[k] = (int8_t)e; });
+    __syncthreads();
+    const uint32_t rows = (count - first) < (int64_t)kBatchBlock ? (uint32_t)(count - first) : (uint32_t)kBatchBlock;
+    if (recv_out) batch_rows_out(tile_recv, rows, recv_out + first * BCS_BATCH_STRIDE);
+    if (send_out) batch_rows_out(tile_send, rows, send_out + first * BCS_BATCH_STRIDE);
 }
 
 }  // namespace

@@ -205,13 +205,6 @@ BCS_HD LowRow row_bytes(const LowRow &w, uint32_t ctx, uint32_t J, uint32_t q) {
     return r;
 }
 
-// lowest clear digit of `up` (with the lap digit) at or above k, at most q
-BCS_HD uint32_t clear_digit(uint32_t up, uint32_t k, uint32_t q) {
-    const uint32_t c = (~up >> k) << k;
-    const uint32_t z = c ? (uint32_t)__builtin_ctz(c) : 32u;
-    return z < q ? z : q;
-}
-
 // Receive entries from round 7 up that the digits alone do not give; fix(i, value).  w: v's row of the table.
 template <class Pol, class Fix>
 BCS_HD void recv_fix(const Pol &pol, const RankPlace &pl, const LowRow &w, Fix fix) {
@@ -220,6 +213,61 @@ BCS_HD void recv_fix(const Pol &pol, const RankPlace &pl, const LowRow &w, Fix f
     uint32_t i = kLowLevels;
     for (; i + 1u < pl.J && pl.low < odd_between(pol.odd_mask(), i + 1u, pl.J); ++i) fix((int)i, (int)(i + 1u - q));
     if (i < pl.J) fix((int)i, (int)(row_lacks(w) - q));
+}
+
+// lowest clear digit of `up` (with the lap digit) at or above k, at most q
+BCS_HD uint32_t clear_digit(uint32_t up, uint32_t k, uint32_t q) {
+    const uint32_t c = (~up >> k) << k;
+    const uint32_t z = c ? (uint32_t)__builtin_ctz(c) : 32u;
+    return z < q ? z : q;
+}
+
+// The block after v's: how many ranks v's block holds and the context that follows it.
+struct NextBlock {
+    uint32_t size, ctx, J;
+};
+
+template <class Pol>
+BCS_HD NextBlock next_block(const Pol &pol, const RankPlace &pl) {
+    const uint32_t q = (uint32_t)pol.q(), p = pol.p();
+    NextBlock nb;
+    if (q <= (uint32_t)kLowLevels) {                                      // the ring is one block
+        nb.size = p;
+        nb.ctx = pl.ctx;
+        nb.J = pl.J;
+        return nb;
+    }
+    const uint32_t bare = pl.up & ~(1u << (q & 31u));
+    const bool upper = (bare >> kLowLevels) & 1u;
+    const uint32_t z = clear_digit(bare, kLowLevels, q);                   // upper: where the next head's digit is
+    const uint32_t cut = odd_between(pol.odd_mask(), kLowLevels, z);       // 0 for digit 7 clear (z = 7)
+    nb.size = ((p - 1u) >> (q - (uint32_t)kLowLevels)) + 1u - cut;
+    nb.ctx = upper ? (z == q ? (uint32_t)kCtxD : 0u) + cut : pl.ctx + 2u * (uint32_t)kCtxD;   // digit 7 clear: it gets set
+    nb.J = upper ? z : pl.J;
+    return nb;
+}
+
+// Send entries below round 7 without other lanes' help: entry k is the low round k of rank v + skips[k], which lies in
+// v's block or in the next one.
+template <class Pol, class Read, class Emit>
+BCS_HD void send_low_entries(const Pol &pol, const RankPlace &pl, uint32_t base, Read read, Emit emit) {
+    const uint32_t q = (uint32_t)pol.q();
+    const NextBlock nb = next_block(pol, pl);
+    auto extra_of = [&](uint32_t ctx, uint32_t J) {
+        return q <= (uint32_t)kLowLevels || ctx - (uint32_t)kCtxD < (uint32_t)kCtxD ? q : J;
+    };
+    const uint32_t here = base + pl.ctx * 128u, next = base + nb.ctx * 128u;
+    const uint32_t extra_here = extra_of(pl.ctx, pl.J), extra_next = extra_of(nb.ctx, nb.J);
+#pragma unroll
+    for (uint32_t k = 0; k < (uint32_t)kLowLevels; ++k) {
+        const uint32_t s = k < q ? ((pol.p() - 1u) >> (q - k)) + 1u : 0u;   // lanes with fewer rounds: some entry, not used
+        const uint32_t to = pl.low + s;
+        const bool over = to >= nb.size;
+        const LowRow w = read(over ? next + to - nb.size : here + to);
+        const uint32_t block = (k < 4u ? w.lo >> (8u * k) : w.hi >> (8u * k - 32u)) & 7u;
+        const uint32_t add = row_pos(w) == k ? (over ? extra_next : extra_here) : 0u;
+        emit((int)k, (int32_t)(block + add - q));
+    }
 }
 
 // Rounds 7 and up from the digits, largest first; own = v's baseblock.  Three vector ops a level for both entries.

@@ -40,8 +40,14 @@ void rows(const Pol &pol, uint32_t v, int32_t *recv, int32_t *send) {
     const LowRow w = g_rows[base + (q >= 7 ? pl.ctx * 128u : 0u) + pl.low];
     const LowRow b = row_bytes(w, pl.ctx, pl.J, q);
     auto byte = [](const LowRow &x, uint32_t k) { return (int32_t)(int8_t)((k < 4 ? x.lo >> (8 * k) : x.hi >> (8 * k - 32)) & 0xffu); };
+    int32_t across[7];                                       // the batch kernel's way to the low send entries
+    send_low_entries(pol, pl, base, [&](uint32_t e) { return g_rows[e]; }, [&](int k, int32_t e) { across[k] = e; });
     for (uint32_t k = 0; k < q && k < 7; ++k) {
         recv[k] = byte(b, k);
+        if (!Pol::kScalarSkips) {
+            send[k] = across[k];
+            continue;
+        }
         const uint32_t t = (uint32_t)(((uint64_t)v + pol.s((int)k)) % pol.p());
         const RankPlace pt = rank_place(pol, t);
         send[k] = byte(row_bytes(g_rows[base + (q >= 7 ? pt.ctx * 128u : 0u) + pt.low], pt.ctx, pt.J, q), k);
