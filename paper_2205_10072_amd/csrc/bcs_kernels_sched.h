@@ -39,17 +39,17 @@ __global__ __launch_bounds__(kBlock) void k_build_lowrows() {
     if (e < kRowsAll) g_lowrows[e] = low_row_entry(e, g_lowtab);
 }
 
-// Rows of a workgroup's LDS tile of bytes (rank-major, Q bytes a rank, so the tile is the table's piece with one byte
-// an entry) to their place in the rank-major int32 table: a lane reads four bytes, widens them and writes 16 bytes.
-template <int Q, int LANES>
-__device__ __forceinline__ void byte_tile_to_rows(const int8_t *tile, uint32_t rows, int32_t *__restrict__ dst) {
-    const uint32_t n = rows * Q;
+// n entries of the rank-major int32 table from a workgroup's LDS tile of bytes, which is laid out like the table's piece
+// with one byte an entry: a lane reads four bytes, widens them and writes 16 bytes.
+template <int LANES>
+__device__ __forceinline__ void byte_tile_to_table(const int8_t *tile, uint32_t n, bool stream, int32_t *__restrict__ dst) {
     if ((reinterpret_cast<uintptr_t>(dst) & 15u) == 0) {
         const uint32_t n4 = n >> 2;
         for (uint32_t g = threadIdx.x; g < n4; g += LANES) {
             const int32_t w = reinterpret_cast<const int32_t *>(tile)[g];
             const v4i pack = {(int32_t)(int8_t)w, (int32_t)(int8_t)(w >> 8), (int32_t)(int8_t)(w >> 16), w >> 24};
-            __builtin_nontemporal_store(pack, reinterpret_cast<v4i *>(dst) + g);
+            if (stream) __builtin_nontemporal_store(pack, reinterpret_cast<v4i *>(dst) + g);
+            else reinterpret_cast<v4i *>(dst)[g] = pack;
         }
         const uint32_t e = (n4 << 2) + threadIdx.x;
         if (e < n) dst[e] = tile[e];
@@ -80,99 +80,95 @@ __device__ __forceinline__ void byte_tile_to_byte_rows(const int8_t *tile, uint3
 
 // ----------------------------------------------------------------------------------------------
 // K1: receive and send rows of ranks [r0, r1), one p per launch, from the closed form in bcs_rows.h.  Lane = rank.
-// A workgroup takes kTileRanks ranks.  The entries of rounds 7 and up, of both tables, follow from a lane's own digits
-// (about eight vector ops a level); those of the receive rounds below 7 are one 8-byte table entry; those of the send
-// rounds below 7 are entries of the next skips[6] <= 64 ranks, so kTileAhead more lanes compute the low rounds alone and
-// the send entries are read across the lanes in LDS.  Both tables' rows are staged in LDS as bytes, laid out like the
-// table, and leave widened to int32 in 16-byte streaming stores.  Nothing else is read or written: no table of
-// all ranks in memory, no second pass, and a range of ranks costs the same a rank as all of them.
-// Bound by the stores.  Measured: all ranks of 2^27-1, 29 GB, 7.31 ms before (digit table, receive rows by windows, send
-// rows by look-up in a slot-major table), 5.22 ms now; all of 2^20+1 59 -> 34 us; 2^24 ranks of 2^27-1 1.10 -> 0.62 ms.
+// The entries of rounds 7 and up follow from a lane's own digits (about eight vector ops a level); those of the receive
+// rounds below 7 are one 8-byte table entry, those of the send rounds below 7 seven such entries (of the ranks up to 64
+// further on).  Rows are staged in LDS as bytes, laid out like the table, and leave widened to int32 in 16-byte stores.
+// Nothing else of the tables' size is read or written: no table of all ranks in memory, no second pass, and a range of
+// ranks costs the same a rank as all of them.
+// Bound by the stores, and what a workgroup writes decides how fast they go.  Store-only kernels, whose workgroups take
+// pieces of two 4 GB tables in turn, reach 6.3-7.0 TB/s with 4 KB pieces (64 to 256 lanes), 6.2-6.5 with 8 KB, and
+// 5.6-5.8 with 6.9, 13.8 or 27.6 KB (64, 128 or 256 rows at q = 27).  So the tables are cut by entries, not by rows: a
+// workgroup is one wave and takes 4 KB of ONE table, neighbouring workgroups take the two tables in turn, and a row that
+// lies across two pieces is built twice.  2^24 ranks of 2^27-1 (3.6 GB): 0.55 ms so, 0.64 with 12 KB and 128 lanes or with
+// whole rows; the construction without the stores takes 0.42 ms.  Plain stores beat streaming ones (by 17 % where the tables
+// fit the memory-side cache) except where byte rows are left for an expansion, which then finds them in the caches.
+// Measured: all ranks of 2^27-1, 29 GB, 7.30 ms before (digit table, receive rows by windows, send rows by look-up in a
+// slot-major table), 4.38 ms now; all of 2^20+1 57 -> 31 us; 2^24 ranks of 2^27-1 1.11 -> 0.54 ms.
 // ----------------------------------------------------------------------------------------------
-constexpr int kTileRanks = 256;
-constexpr int kTileAhead = 64;
-constexpr int kTileLanes = kTileRanks + kTileAhead;
-constexpr int kWantRecv = 1, kWantSend = 2;
+constexpr int kSchedLanes = 64;
+constexpr uint32_t kWantRecv = 1, kWantSend = 2;
+
+// entries of one table that a workgroup writes (by_rows: whole rows, for the slot-major copy)
+inline uint32_t sched_piece(int q, bool by_rows) {
+    const bool fits = (kSchedLanes - 1) * q >= 1024;                        // a piece may begin inside a row; q >= 17
+    return by_rows || !fits ? (uint32_t)(kSchedLanes * q) : 1024u;
+}
 
 template <int Q>
-struct RowTiles {
-    __align__(16) int8_t recv[kTileRanks * Q + 16];
-    __align__(16) int8_t send[kTileRanks * Q + 16];
-    LowRow low[kTileLanes];                                       // entries of the rounds below 7, as bytes
-};
-
-template <int Q, int WANT>
-__device__ __forceinline__ void fill_row_tiles(const SkipTab &tab, uint32_t root, uint32_t first_rank, RowTiles<Q> &tiles) {
+__global__ __launch_bounds__(kSchedLanes) void k_sched(const SkipTab tab, uint32_t root, uint32_t r0, uint32_t r1,
+                                                       uint32_t want, uint32_t piece, int32_t *__restrict__ recv_out,
+                                                       int32_t *__restrict__ send_out, slot_t *__restrict__ recvT,
+                                                       uint64_t ldT, int8_t *__restrict__ recvB,
+                                                       int8_t *__restrict__ sendB) {
+    // a row begins up to Q - 1 entries before the piece: the piece's first entry sits at a 16-byte boundary behind them
+    __shared__ __align__(16) int8_t tile_all[32 + kSchedLanes * Q + 16];
+    int8_t *const tile = tile_all + 32;
+    constexpr int kLow = Q < kLowLevels ? Q : kLowLevels;
+    const bool both = want == (kWantRecv | kWantSend);
+    const bool send = both ? (blockIdx.x & 1u) != 0u : want == kWantSend;
+    const uint64_t e0 = (uint64_t)(both ? blockIdx.x >> 1 : blockIdx.x) * piece;      // first entry of the piece
+    const uint32_t first = (uint32_t)(e0 / Q);                                         // its row, an offset inside [r0, r1)
+    const uint32_t ahead = (uint32_t)(e0 - (uint64_t)first * Q);                       // entries of that row before it
+    const uint32_t count = r1 - r0, left = count - first;                              // left > 0: the grid covers the table
     Uniform<Q> pol;
 #pragma unroll
     for (int k = 0; k <= Q; ++k) pol.S[k] = tab.s[k];
     pol.tab = &tab;
     pol.low = nullptr;
     const uint32_t p = pol.p();
-    uint32_t r = first_rank + threadIdx.x;                        // lanes past the end wrap around like the look-ahead
-    if constexpr (Q < 10) r %= p;                                 // p < 513 may be below the tile's lanes
-    else r = r >= p ? r - p : r;
+    const uint32_t r = r0 + first + (threadIdx.x < left ? threadIdx.x : 0u);           // lanes past the end repeat a rank
     const uint32_t v = r >= root ? r - root : r + p - root;
     const uint32_t base = row_base(pol);
     const RankPlace pl = rank_place(pol, v);
     const LowRow w = g_lowrows[base + pl.ctx * 128u + pl.low];
-    const LowRow b = row_bytes(w, pl.ctx, pl.J, (uint32_t)Q);
-    if constexpr ((WANT & kWantSend) != 0) tiles.low[threadIdx.x] = b;
-    const bool own_rank = threadIdx.x < (uint32_t)kTileRanks;     // wave-uniform
-    int8_t *my_recv = tiles.recv + threadIdx.x * Q;
-    int8_t *my_send = tiles.send + threadIdx.x * Q;
-    constexpr int kLow = Q < kLowLevels ? Q : kLowLevels;
-    if (own_rank) {
-        if constexpr ((WANT & kWantRecv) != 0) {
+    const uint32_t own = place_own(pl, w);
+    int8_t *my = tile + (int)(threadIdx.x * Q) - (int)ahead;
+    auto read = [](uint32_t e) { return g_lowrows[e]; };
+    auto keep = [&](int k, int32_t e) { my[k] = (int8_t)e; };
+    auto drop = [](int, int32_t) {};
+    if (send) {
+        send_low_entries(pol, pl, base, read, [&](int k, int32_t e) { if (k < kLow) my[k] = (int8_t)e; });
+        high_entries(pol, pl, own, drop, keep);
+        send_fix(pol, v, pl, base, read, keep);
+    } else {
+        const LowRow b = row_bytes(w, pl.ctx, pl.J, (uint32_t)Q);
 #pragma unroll
-            for (int k = 0; k < kLow; ++k) my_recv[k] = (int8_t)(k < 4 ? b.lo >> (8 * k) : b.hi >> (8 * (k - 4)));
-        }
-        high_entries(pol, pl, place_own(pl, w),
-                     [&](int k, int32_t e) { if constexpr ((WANT & kWantRecv) != 0) my_recv[k] = (int8_t)e; },
-                     [&](int k, int32_t e) { if constexpr ((WANT & kWantSend) != 0) my_send[k] = (int8_t)e; });
-        if constexpr ((WANT & kWantRecv) != 0) recv_fix(pol, pl, w, [&](int k, int32_t e) { my_recv[k] = (int8_t)e; });
-        if constexpr ((WANT & kWantSend) != 0)
-            send_fix(pol, v, pl, base, [](uint32_t e) { return g_lowrows[e]; }, [&](int k, int32_t e) { my_send[k] = (int8_t)e; });
+        for (int k = 0; k < kLow; ++k) my[k] = (int8_t)(k < 4 ? b.lo >> (8 * k) : b.hi >> (8 * (k - 4)));
+        high_entries(pol, pl, own, keep, drop);
+        recv_fix(pol, pl, w, keep);
     }
     __syncthreads();
-    if constexpr ((WANT & kWantSend) != 0) {
-        if (own_rank) {
-            const int8_t *low = reinterpret_cast<const int8_t *>(tiles.low);
-#pragma unroll
-            for (int k = 0; k < kLow; ++k) my_send[k] = low[(threadIdx.x + pol.S[k]) * 8u + k];
-        }
-        __syncthreads();
+    int32_t *const out = send ? send_out : recv_out;
+    int8_t *const outB = send ? sendB : recvB;
+    const uint64_t rest = (uint64_t)count * Q - e0;
+    if (out) byte_tile_to_table<kSchedLanes>(tile, rest < piece ? (uint32_t)rest : piece, outB != nullptr, out + e0);
+    if (outB) {
+        // the rows that begin in the piece
+        const uint32_t skip = ahead ? 1u : 0u;
+        const uint32_t end = (ahead + piece + Q - 1u) / Q;                             // at most kSchedLanes
+        byte_tile_to_byte_rows<Q, kSchedLanes>(tile + (int)(skip * Q) - (int)ahead, (end < left ? end : left) - skip,
+                                               outB + ((uint64_t)first + skip) * byte_row_stride(Q));
     }
-}
-
-template <int Q, int WANT>
-__global__ __launch_bounds__(kTileLanes) void k_sched(const SkipTab tab, uint32_t root, uint32_t r0, uint32_t r1,
-                                                      int32_t *__restrict__ recv_out, int32_t *__restrict__ send_out,
-                                                      slot_t *__restrict__ recvT, uint64_t ldT,
-                                                      int8_t *__restrict__ recvB, int8_t *__restrict__ sendB) {
-    __shared__ RowTiles<Q> tiles;
-    const uint64_t first = (uint64_t)blockIdx.x * kTileRanks;     // offset of this tile inside [r0, r1)
-    fill_row_tiles<Q, WANT>(tab, root, r0 + (uint32_t)first, tiles);
-    const uint64_t left = (uint64_t)r1 - r0 - first;
-    const uint32_t rows = left < (uint64_t)kTileRanks ? (uint32_t)left : (uint32_t)kTileRanks;
-    if constexpr ((WANT & kWantRecv) != 0) {
-        if (recv_out) byte_tile_to_rows<Q, kTileLanes>(tiles.recv, rows, recv_out + first * Q);
-        if (recvB) byte_tile_to_byte_rows<Q, kTileLanes>(tiles.recv, rows, recvB + first * byte_row_stride(Q));
-        if (recvT) {
-            // slot-major: each slot's kTileRanks bytes are one aligned piece of the table, whose rows are padded to a
-            // multiple of them (the last tile writes its idle lanes' bytes into the padding)
-            for (uint32_t g = threadIdx.x; g < (uint32_t)Q * (kTileRanks / 4); g += kTileLanes) {
-                const uint32_t k = g / (kTileRanks / 4), four = g % (kTileRanks / 4);
-                uint32_t packed = 0;
+    if (!send && recvT) {
+        // slot-major, a launch by whole rows: each slot's kSchedLanes bytes are one aligned piece of the table, whose rows
+        // are padded to a multiple of them (the last tile writes its idle lanes' bytes into the padding)
+        for (uint32_t g = threadIdx.x; g < (uint32_t)Q * (kSchedLanes / 4); g += kSchedLanes) {
+            const uint32_t k = g / (kSchedLanes / 4), four = g % (kSchedLanes / 4);
+            uint32_t packed = 0;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) packed |= (uint32_t)(uint8_t)tiles.recv[(four * 4u + c) * Q + k] << (8 * c);
-                *reinterpret_cast<uint32_t *>(recvT + (uint64_t)k * ldT + first + four * 4u) = packed;
-            }
+            for (int c = 0; c < 4; ++c) packed |= (uint32_t)(uint8_t)tile[(four * 4u + c) * Q + k] << (8 * c);
+            *reinterpret_cast<uint32_t *>(recvT + (uint64_t)k * ldT + first + four * 4u) = packed;
         }
-    }
-    if constexpr ((WANT & kWantSend) != 0) {
-        if (send_out) byte_tile_to_rows<Q, kTileLanes>(tiles.send, rows, send_out + first * Q);
-        if (sendB) byte_tile_to_byte_rows<Q, kTileLanes>(tiles.send, rows, sendB + first * byte_row_stride(Q));
     }
 }
 

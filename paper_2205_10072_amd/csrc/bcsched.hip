@@ -254,17 +254,12 @@ struct RowCopies {
 template <int Q>
 int launch_sched(const SkipTab &tab, uint32_t root, uint32_t r0, uint32_t r1, int32_t *recv_out, int32_t *send_out,
                  const RowCopies &to, hipStream_t st) {
-    const unsigned blocks = (unsigned)(((uint64_t)r1 - r0 + kTileRanks - 1) / kTileRanks);
-    const bool recv = recv_out || to.recvT || to.recvB, send = send_out || to.sendB;
-    if (recv && send)
-        launch(kSched, k_sched<Q, kWantRecv | kWantSend>, dim3(blocks), dim3(kTileLanes), st, tab, root, r0, r1, recv_out,
-               send_out, to.recvT, to.ldT, to.recvB, to.sendB);
-    else if (recv)
-        launch(kSched, k_sched<Q, kWantRecv>, dim3(blocks), dim3(kTileLanes), st, tab, root, r0, r1, recv_out, send_out,
-               to.recvT, to.ldT, to.recvB, to.sendB);
-    else
-        launch(kSched, k_sched<Q, kWantSend>, dim3(blocks), dim3(kTileLanes), st, tab, root, r0, r1, recv_out, send_out,
-               to.recvT, to.ldT, to.recvB, to.sendB);
+    const uint32_t want = (recv_out || to.recvT || to.recvB ? kWantRecv : 0u) | (send_out || to.sendB ? kWantSend : 0u);
+    const uint32_t piece = sched_piece(Q, to.recvT != nullptr);
+    const uint64_t pieces = (((uint64_t)r1 - r0) * Q + piece - 1) / piece;
+    const unsigned blocks = (unsigned)(want == (kWantRecv | kWantSend) ? 2u * pieces : pieces);      // at most 2^27
+    launch(kSched, k_sched<Q>, dim3(blocks), dim3(kSchedLanes), st, tab, root, r0, r1, want, piece, recv_out, send_out,
+           to.recvT, to.ldT, to.recvB, to.sendB);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? BCS_OK : hip_fail(e);
 }
