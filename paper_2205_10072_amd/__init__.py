@@ -33,7 +33,7 @@ SYMBOLS = (
     "bcs_pack_plan_rounds", "bcs_pack_round_planned", "bcs_unpack_round_planned",
     "bcs_allgather_partners", "bcs_census_partners",
 )
-KERNEL_COUNT = 13
+KERNEL_COUNT = 11
 VALU_PEAK_OPS_PER_ITER = 32
 
 _lib = None

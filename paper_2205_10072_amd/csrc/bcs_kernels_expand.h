@@ -1,5 +1,4 @@
-// Expansion kernels (the index arithmetic of Alg. 6): block tables from int32 schedule rows, from byte rows,
-// and fused with the construction of the rows for short rows.
+// Expansion kernels (the index arithmetic of Alg. 6): block tables from int32 schedule rows and from byte rows.
 #ifndef BCS_KERNELS_EXPAND_H
 #define BCS_KERNELS_EXPAND_H
 
@@ -180,9 +179,15 @@ struct ExpandRowsArgs {
     int32_t nm1;
 };
 
-__global__ __launch_bounds__(kBlock) void k_expand_rows(const ExpandRowsArgs a, const int8_t *__restrict__ rowsB,
-                                                        int32_t *__restrict__ out) {
-    const uint64_t e = ((uint64_t)blockIdx.x * kBlock + threadIdx.x) * 4u;
+// With both tables at hand (rowsB1, out1 not null) neighbouring workgroups take pieces of the two in turn.
+__global__ __launch_bounds__(kBlock) void k_expand_rows(const ExpandRowsArgs a, const int8_t *__restrict__ rowsB0,
+                                                        const int8_t *__restrict__ rowsB1, int32_t *__restrict__ out0,
+                                                        int32_t *__restrict__ out1) {
+    const bool second = out1 != nullptr && (blockIdx.x & 1u) != 0u;
+    const int8_t *__restrict__ rowsB = second ? rowsB1 : rowsB0;
+    int32_t *__restrict__ out = second ? out1 : out0;
+    const uint32_t piece = out1 != nullptr ? blockIdx.x >> 1 : blockIdx.x;
+    const uint64_t e = ((uint64_t)piece * kBlock + threadIdx.x) * 4u;
     if (e >= a.total) return;
     const uint32_t q = a.q, R = a.R;
     uint64_t row;
@@ -251,155 +256,6 @@ __global__ __launch_bounds__(kBlock) void k_rows_to_bytes(uint32_t rows, uint32_
         packed |= ((uint32_t)t & 0xffu) << (8 * c);
     }
     reinterpret_cast<uint32_t *>(rowsB)[g] = packed;
-}
-
-// ----------------------------------------------------------------------------------------------
-// K1+K4 and K2+K4 fused: a workgroup that has just built (or looked up) the schedule rows of its 256
-// ranks expands them straight from LDS, so the rows are not read back from memory and the integer
-// work of the construction overlaps with the stores of the expansion.  The tile is kept in the
-// mirrored T layout of k_expand (row stride odd, so the lanes' row writes do not collide); the 256
-// rows of a tile are one contiguous piece of the expanded table that starts on a 16-byte boundary.
-// Used for short rows (see use_fused).
-// ----------------------------------------------------------------------------------------------
-template <int Q>
-struct FusedTile {
-    static constexpr int kWidth = (Q + (int)kExpPad) | 1;
-};
-
-// after the rows T[k] = entry - k are in place: add the three mirrors of every row (see k_expand)
-template <int Q>
-__device__ __forceinline__ void tile_mirrors(int32_t *tile, uint32_t x, uint32_t R) {
-    constexpr int W = FusedTile<Q>::kWidth;
-    static_assert(Q >= (int)kExpMinQ, "the mirrored layout needs three slots");
-    int32_t *my = tile + threadIdx.x * W;
-#pragma unroll
-    for (int m = 0; m < 3; ++m) {
-        my[Q + m] = my[m];
-        my[Q + 3 + m] = my[Q - 3 + m];
-    }
-    __syncthreads();
-    if (threadIdx.x + 1 < kBlock) {
-        const int32_t *next = my + W;
-#pragma unroll
-        for (int m = 0; m < 3; ++m) {
-            uint32_t slot = x + m;
-            slot = slot >= (uint32_t)Q ? slot - (uint32_t)Q : slot;
-            my[Q + 6 + m] = next[slot] - (int32_t)R;
-        }
-    }
-    __syncthreads();
-}
-
-// rank-major schedule rows of the tile: entry = T + slot
-template <int Q>
-__device__ __forceinline__ void tile_rows_out(const int32_t *tile, uint32_t rows, int32_t *__restrict__ dst) {
-    constexpr int W = FusedTile<Q>::kWidth;
-    const uint32_t n = rows * Q;
-    for (uint32_t e = threadIdx.x; e < n; e += kBlock) {
-        const uint32_t row = e / Q, col = e - row * Q;
-        dst[e] = tile[row * W + col] + (int32_t)col;
-    }
-}
-
-// the expanded entries of the tile's rows: `rows` x R entries starting at flat index first_row * R
-template <int Q, bool NT>
-__device__ __forceinline__ void tile_expand(const int32_t *tile, uint32_t rows, uint64_t first_row,
-                                            const ExpandArgs &a, int32_t *__restrict__ out) {
-    constexpr uint32_t W = FusedTile<Q>::kWidth;
-    const uint32_t R = a.R;
-    const uint64_t count = (uint64_t)rows * R;
-    int32_t *dst = out + first_row * R;
-    const uint32_t t = threadIdx.x * 4u;
-    uint32_t rd = __umulhi(t, a.magic_R);                             // t < 2^14, R <= kFusedMaxR
-    uint32_t j = t - rd * R;
-    const uint32_t kv = a.x + t + rd * a.wrap_k;                    // congruent to x + j mod q
-    uint32_t k = kv - (uint32_t)Q * __umulhi(kv, a.magic_q);
-    const int32_t lo = -1, hi = a.nm1;
-#pragma unroll 1
-    for (uint64_t e = t; e < count; e += (uint64_t)kBlock * 4u) {
-        const uint32_t left = R - j;
-        const int32_t *wp = tile + rd * W + k + (left < 4u ? 6u : 0u);
-        int32_t v[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int32_t raw = wp[c] + (int32_t)(j + c);
-            const int32_t m = raw > lo ? raw : lo;
-            v[c] = m < hi ? m : hi;
-        }
-        if (e + 4 <= count) {
-            const v4i pack = {v[0], v[1], v[2], v[3]};
-            if constexpr (NT) __builtin_nontemporal_store(pack, reinterpret_cast<v4i *>(dst + e));
-            else *reinterpret_cast<v4i *>(dst + e) = pack;
-        } else {
-            for (int c = 0; c < 4; ++c)
-                if (e + c < count) dst[e + c] = v[c];
-        }
-        rd += a.step_rows;
-        j += a.step_j;
-        k += a.step_k;
-        if (j >= R) {
-            j -= R;
-            ++rd;
-            k += a.wrap_k;
-        }
-        k = k >= (uint32_t)Q ? k - (uint32_t)Q : k;
-        k = k >= (uint32_t)Q ? k - (uint32_t)Q : k;
-    }
-}
-
-template <int Q>
-__global__ __launch_bounds__(kBlock) void k_recv_expand(const SkipTab tab, uint32_t root, const ExpandArgs ea,
-                                                        int32_t *__restrict__ recv_out, slot_t *__restrict__ recvT,
-                                                        uint64_t ldT, int32_t *__restrict__ blocks_out) {
-    constexpr int W = FusedTile<Q>::kWidth;
-    __shared__ int32_t tile[kBlock * W];
-    __shared__ uint32_t lowtab[kLowShapeBytes / 4];
-    Uniform<Q> pol;
-#pragma unroll
-    for (int k = 0; k <= Q; ++k) pol.S[k] = tab.s[k];
-    pol.tab = &tab;
-    pol.low = reinterpret_cast<const uint8_t *>(lowtab);
-    const uint32_t p = pol.p();
-    stage_lowtab(lowtab, low_shape(p, Q));
-    __syncthreads();
-    const uint64_t first = (uint64_t)blockIdx.x * kBlock;
-    const uint64_t idx = first + threadIdx.x;
-    const bool live = idx < p;
-    const uint32_t r = live ? (uint32_t)idx : root;
-    const uint32_t v = r >= root ? r - root : r + p - root;
-    int32_t *my = tile + threadIdx.x * W;
-    recv_row(pol, v, Q - 1, [&](int i, int val) {
-        my[i] = val - i;
-        if (live) recvT[(uint64_t)i * ldT + idx] = (slot_t)val;
-    });
-    tile_mirrors<Q>(tile, ea.x, ea.R);
-    const uint32_t rows = (uint32_t)(((uint64_t)p - first) < (uint64_t)kBlock ? ((uint64_t)p - first) : (uint64_t)kBlock);
-    tile_rows_out<Q>(tile, rows, recv_out + first * Q);
-    tile_expand<Q, true>(tile, rows, first, ea, blocks_out);
-}
-
-template <int Q>
-__global__ __launch_bounds__(kBlock) void k_send_expand(const SkipTab tab, const ExpandArgs ea,
-                                                        const slot_t *__restrict__ recvT, uint64_t ldT,
-                                                        int32_t *__restrict__ send_out,
-                                                        int32_t *__restrict__ blocks_out) {
-    constexpr int W = FusedTile<Q>::kWidth;
-    __shared__ int32_t tile[kBlock * W];
-    const uint32_t p = tab.s[Q];
-    const uint64_t first = (uint64_t)blockIdx.x * kBlock;
-    const uint64_t idx = first + threadIdx.x;
-    const uint32_t me = idx < p ? (uint32_t)idx : 0u;               // idle lanes replay rank 0
-    int32_t *my = tile + threadIdx.x * W;
-#pragma unroll
-    for (int k = 0; k < Q; ++k) {
-        uint32_t t = me + tab.s[k];
-        t = t >= p ? t - p : t;
-        my[k] = recvT[(uint64_t)k * ldT + t] - k;
-    }
-    tile_mirrors<Q>(tile, ea.x, ea.R);
-    const uint32_t rows = (uint32_t)(((uint64_t)p - first) < (uint64_t)kBlock ? ((uint64_t)p - first) : (uint64_t)kBlock);
-    tile_rows_out<Q>(tile, rows, send_out + first * Q);
-    tile_expand<Q, true>(tile, rows, first, ea, blocks_out);
 }
 
 __global__ __launch_bounds__(kBlock) void k_expand_small(const ExpandArgs a, const int32_t *__restrict__ in,

@@ -29,13 +29,12 @@ inline int hip_fail(hipError_t e) {
 // given a start and a stop event from a fixed pool, so its duration is the device's own.
 enum KernelId {
     kSched = 0, kBatch, kExpand, kFill, kValuPeak, kAllgather, kPackPlan, kPackCopy,
-    kRecvExpand, kSendExpand, kExpandRows, kRowsToBytes, kPartnerTables, kKernelCount
+    kExpandRows, kRowsToBytes, kPartnerTables, kKernelCount
 };
 static_assert(kKernelCount == BCS_KERNEL_COUNT, "header and kernel list disagree");
 const char *const kKernelNames[kKernelCount] = {"k_sched",       "k_batch",       "k_expand",      "k_fill",
                                                 "k_valu_peak",   "k_allgather_tables", "k_pack_plan", "k_pack_copy",
-                                                "k_recv_expand", "k_send_expand", "k_expand_rows", "k_rows_to_bytes",
-                                                "k_partner_tables"};
+                                                "k_expand_rows", "k_rows_to_bytes", "k_partner_tables"};
 struct Timing {
     bool on = false;
     int used = 0;
@@ -257,9 +256,12 @@ int launch_sched(const SkipTab &tab, uint32_t root, uint32_t r0, uint32_t r1, in
     const uint32_t want = (recv_out || to.recvT || to.recvB ? kWantRecv : 0u) | (send_out || to.sendB ? kWantSend : 0u);
     const uint32_t piece = sched_piece(Q, to.recvT != nullptr);
     const uint64_t pieces = (((uint64_t)r1 - r0) * Q + piece - 1) / piece;
-    const unsigned blocks = (unsigned)(want == (kWantRecv | kWantSend) ? 2u * pieces : pieces);      // at most 2^27
-    launch(kSched, k_sched<Q>, dim3(blocks), dim3(kSchedLanes), st, tab, root, r0, r1, want, piece, recv_out, send_out,
-           to.recvT, to.ldT, to.recvB, to.sendB);
+    // a launch takes fewer than 2^32 lanes: both tables together up to 274 GB, else one after the other
+    const bool both = want == (kWantRecv | kWantSend), together = both && 2u * pieces * kSchedLanes <= 0xffffffffull;
+    for (uint32_t part = together ? want : 1u; part <= (together ? want : 2u); ++part)
+        if (together || (want & part))
+            launch(kSched, k_sched<Q>, dim3((unsigned)(together ? 2u * pieces : pieces)), dim3(kSchedLanes), st, tab, root, r0,
+                   r1, part, piece, recv_out, send_out, to.recvT, to.ldT, to.recvB, to.sendB);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? BCS_OK : hip_fail(e);
 }
@@ -297,52 +299,6 @@ ExpandArgs expand_args(uint64_t rows, uint64_t R, int q, int32_t n, const void *
     ea.magic_q = q >= 2 ? (uint32_t)((1ull << 32) / (uint64_t)q + 1ull) : 0u;
     ea.magic_w = (uint32_t)((1ull << 32) / (uint64_t)(q + kExpPad) + 1ull);
     return ea;
-}
-
-// Fused construction + expansion of all ranks (tiles of 256 rows).  Measured on MI355X against the
-// separate kernels for p = 2^12 .. 2^22 and n = 1 .. 1024: 15-40 % less time while rows are short (the
-// schedule rows are a large share of the traffic, and two launches replace four); for longer rows the
-// flat stream of k_expand, whose workgroups are small and many, writes faster than a tile at a time.
-constexpr uint64_t kFusedShortR = 96;              // rows up to this length: fused for any p
-constexpr uint64_t kFusedMaxR = 128;               // rows up to this length: fused when p >= kFusedMinP
-constexpr uint32_t kFusedMinP = 1u << 16;
-
-inline bool use_fused(int32_t p, int q, uint64_t R, bool aligned) {
-    if (q < (int)kExpMinQ || R < kExpMinR || !aligned) return false;
-    return R <= kFusedShortR || (R <= kFusedMaxR && (uint32_t)p >= kFusedMinP);
-}
-
-template <int Q>
-int launch_fused(const SkipTab &tab, uint32_t root, const ExpandArgs &ea, int32_t *recv_out, int32_t *send_out,
-                 slot_t *recvT, uint64_t ldT, int32_t *recv_blocks, int32_t *send_blocks, hipStream_t st) {
-    if constexpr (Q >= (int)kExpMinQ) {
-        const unsigned blocks = (unsigned)(((uint64_t)tab.s[Q] + kBlock - 1) / kBlock);
-        launch(kRecvExpand, k_recv_expand<Q>, dim3(blocks), dim3(kBlock), st, tab, root, ea, recv_out, recvT, ldT,
-               recv_blocks);
-        launch(kSendExpand, k_send_expand<Q>, dim3(blocks), dim3(kBlock), st, tab, ea, (const slot_t *)recvT, ldT,
-               send_out, send_blocks);
-        hipError_t e = hipGetLastError();
-        return e == hipSuccess ? BCS_OK : hip_fail(e);
-    } else {
-        return BCS_EINVAL;
-    }
-}
-
-typedef int (*FusedFn)(const SkipTab &, uint32_t, const ExpandArgs &, int32_t *, int32_t *, slot_t *, uint64_t,
-                       int32_t *, int32_t *, hipStream_t);
-
-template <int... Qs>
-constexpr void fill_fused(FusedFn *t, std::integer_sequence<int, Qs...>) {
-    ((t[Qs] = &launch_fused<Qs + 1>), ...);
-}
-
-FusedFn fused_for_q(int q) {
-    struct Table {
-        FusedFn fn[kMaxQ];
-        Table() { fill_fused(fn, std::make_integer_sequence<int, kMaxQ>{}); }
-    };
-    static const Table table;
-    return table.fn[q - 1];
 }
 
 int check_range(int32_t p, int32_t root, int32_t r0, int32_t r1) {
@@ -574,7 +530,7 @@ int bcs_expand_ws(int32_t p, int32_t n, int32_t r0, int32_t r1, const int32_t *r
             launch(kRowsToBytes, k_rows_to_bytes, dim3((rc * w4 + kBlock - 1) / kBlock), dim3(kBlock), st, rc, (uint32_t)q,
                    RS, (uint32_t)((1ull << 32) / w4 + 1ull), ins[t] + (uint64_t)c0 * q, (int8_t *)workspace);
             launch(kExpandRows, k_expand_rows, dim3((unsigned)pieces), dim3(kBlock), st, ra, (const int8_t *)workspace,
-                   outs[t] + (uint64_t)c0 * R);
+                   (const int8_t *)nullptr, outs[t] + (uint64_t)c0 * R, (int32_t *)nullptr);
         }
     }
     hipError_t e = hipGetLastError();
@@ -591,6 +547,58 @@ int64_t bcs_sched_expand_workspace_bytes(int32_t p, int32_t n) {
     return base + (extra > 0 ? extra : 0);
 }
 
+namespace {
+// Schedules of all ranks with byte rows in the workspace, and the expansion of the byte rows.
+// Short calls are bound by launches: both tables at once, two launches.  Long ones go table by table, so that a table's
+// byte rows are still cached when they are expanded.  Measured, together against table by table: block tables of 0.2 MB 13
+// against 18 us, 65 MB 35 against 43 us, 218 MB 119 us both, 1158 MB 388 against 371 us.  Byte rows that exceed the
+// workspace or kByteRowsMax are made and expanded a chunk of ranks at a time; any workspace that holds the schedules'
+// scratch will do.  (Rows of up to 128 entries used to be expanded by the workgroup that built them, 256 ranks each: 43 us
+// at 65 MB, 143 at 218 MB.)
+constexpr uint64_t kTogetherBytes = 128ull << 20;   // of one block table
+
+int sched_expand_rows(int32_t p, uint32_t root, int32_t n, int q, uint64_t R, int32_t *recv_out, int32_t *send_out,
+                      int32_t *recv_blocks, int32_t *send_blocks, int8_t *ws, size_t ws_bytes, hipStream_t st) {
+    const uint64_t RS = (uint64_t)byte_row_stride(q), rows_bytes = byte_rows_bytes(p, q);
+    const bool together = 2 * rows_bytes <= ws_bytes && (uint64_t)p * R * 4u <= kTogetherBytes;
+    const uint64_t cap = ws_bytes < kByteRowsMax ? ws_bytes : kByteRowsMax;
+    const uint64_t fit = (cap / RS - 1u) & ~(uint64_t)3;               // a multiple of 4 rows: pieces start on 16 bytes
+    const uint32_t chunk = together || (uint64_t)p <= fit ? (uint32_t)p : (uint32_t)fit;
+    if (chunk == 0) return BCS_ENOMEM;
+    if (((uint64_t)chunk * R + kBlock * 4 - 1) / (kBlock * 4) > 0x7fffffffull) return BCS_EINVAL;
+    SkipTab tab;
+    host_skips(p, tab);
+    int rc = ensure_lowtab(st);
+    if (rc != BCS_OK) return rc;
+    const LaunchFn rows = launch_for_q(q);
+    if (together) {
+        int8_t *const sendB = ws + rows_bytes;
+        rc = rows(tab, root, 0u, (uint32_t)p, recv_out, send_out, RowCopies{nullptr, 0, ws, sendB}, st);
+        if (rc != BCS_OK) return rc;
+        const ExpandRowsArgs ra = expand_rows_args((uint64_t)p, R, q, n);
+        const unsigned pieces = (unsigned)((ra.total + kBlock * 4 - 1) / (kBlock * 4));
+        launch(kExpandRows, k_expand_rows, dim3(2 * pieces), dim3(kBlock), st, ra, (const int8_t *)ws, (const int8_t *)sendB,
+               recv_blocks, send_blocks);
+    } else {
+        for (int t = 0; t < 2; ++t) {
+            int32_t *const out = t ? send_out : recv_out, *const blocks = t ? send_blocks : recv_blocks;
+            for (uint32_t c0 = 0; c0 < (uint32_t)p; c0 += chunk) {
+                const uint32_t c1 = (uint32_t)p - c0 < chunk ? (uint32_t)p : c0 + chunk;
+                int32_t *const to = out + (uint64_t)c0 * q;
+                rc = rows(tab, root, c0, c1, t ? nullptr : to, t ? to : nullptr,
+                          RowCopies{nullptr, 0, t ? nullptr : ws, t ? ws : nullptr}, st);
+                if (rc != BCS_OK) return rc;
+                const ExpandRowsArgs ra = expand_rows_args((uint64_t)(c1 - c0), R, q, n);
+                launch(kExpandRows, k_expand_rows, dim3((unsigned)((ra.total + kBlock * 4 - 1) / (kBlock * 4))), dim3(kBlock),
+                       st, ra, (const int8_t *)ws, (const int8_t *)nullptr, blocks + (uint64_t)c0 * R, (int32_t *)nullptr);
+            }
+        }
+    }
+    hipError_t e = hipGetLastError();
+    return e == hipSuccess ? BCS_OK : hip_fail(e);
+}
+}  // namespace
+
 int bcs_sched_expand_ws(int32_t p, int32_t root, int32_t n, int32_t *recv_out, int32_t *send_out,
                         int32_t *recv_blocks, int32_t *send_blocks, void *workspace, size_t workspace_bytes,
                         void *stream) {
@@ -601,50 +609,17 @@ int bcs_sched_expand_ws(int32_t p, int32_t root, int32_t n, int32_t *recv_out, i
     if (!recv_blocks || !send_blocks) return BCS_EINVAL;
     if (q > 0 && (!recv_out || !send_out)) return BCS_EINVAL;
     if (workspace && workspace_bytes > 0 && (((uintptr_t)workspace) & 255u)) return BCS_EINVAL;
+    const int64_t base = q > 0 ? bcs_sched_workspace_bytes(p, 0, p, 1) : 0;
+    if (base > 0 && (!workspace || workspace_bytes < (size_t)base)) return BCS_ENOMEM;
     const bool aligned = ((((uintptr_t)recv_blocks) | ((uintptr_t)send_blocks)) & 15u) == 0;
-    if (!use_fused(p, q, R, aligned)) {
-        const int64_t base = q > 0 ? bcs_sched_workspace_bytes(p, 0, p, 1) : 0;
-        const uint64_t rows_bytes = q > 0 ? byte_rows_bytes(p, q) : 0;
-        if (byte_rows_apply(p, q, R) && aligned && workspace && workspace_bytes >= (size_t)base + 2 * rows_bytes) {
-            // long rows: the schedule kernels also leave byte rows, which the expansion then reads from cache
-            SkipTab tab;
-            host_skips(p, tab);
-            int rc = ensure_lowtab((hipStream_t)stream);
-            if (rc != BCS_OK) return rc;
-            const ExpandRowsArgs ra = expand_rows_args((uint64_t)p, R, q, n);
-            const uint64_t pieces = (ra.total + kBlock * 4 - 1) / (kBlock * 4);
-            if (pieces > 0x7fffffffull) return BCS_EINVAL;
-            int8_t *recvB = (int8_t *)workspace + base, *sendB = recvB + rows_bytes;
-            rc = launch_for_q(q)(tab, (uint32_t)root, 0u, (uint32_t)p, recv_out, send_out,
-                                 RowCopies{nullptr, 0, recvB, sendB}, (hipStream_t)stream);
-            if (rc != BCS_OK) return rc;
-            int32_t *outs[2] = {recv_blocks, send_blocks};
-            const int8_t *srcs[2] = {recvB, sendB};
-            for (int t = 0; t < 2; ++t) {
-                launch(kExpandRows, k_expand_rows, dim3((unsigned)pieces), dim3(kBlock), (hipStream_t)stream, ra,
-                       srcs[t], outs[t]);
-            }
-            hipError_t e = hipGetLastError();
-            return e == hipSuccess ? BCS_OK : hip_fail(e);
-        }
-        if (q > 0) {
-            const int rc = bcs_sched_rooted_ws(p, root, 0, p, recv_out, send_out, workspace, workspace_bytes, stream);
-            if (rc != BCS_OK) return rc;
-        }
-        // what the workspace holds beyond the schedules' scratch serves the expansion (chunks of byte rows)
-        const bool more = workspace && workspace_bytes > (size_t)base;
-        return bcs_expand_ws(p, n, 0, p, recv_out, send_out, recv_blocks, send_blocks,
-                             more ? (char *)workspace + base : nullptr, more ? workspace_bytes - (size_t)base : 0, stream);
+    if (q >= (int)kExpMinQ && R >= kExpMinR && aligned)
+        return sched_expand_rows(p, (uint32_t)root, n, q, R, recv_out, send_out, recv_blocks, send_blocks,
+                                 (int8_t *)workspace, workspace_bytes, (hipStream_t)stream);
+    if (q > 0) {
+        const int rc = sched_rows(p, root, 0, p, recv_out, send_out, (hipStream_t)stream);
+        if (rc != BCS_OK) return rc;
     }
-    const int64_t need = bcs_sched_workspace_bytes(p, 0, p, 1);
-    if (!workspace || workspace_bytes < (size_t)need) return BCS_ENOMEM;
-    SkipTab tab;
-    host_skips(p, tab);
-    const int rc = ensure_lowtab((hipStream_t)stream);
-    if (rc != BCS_OK) return rc;
-    const ExpandArgs ea = expand_args((uint64_t)p, R, q, n, recv_blocks);
-    return fused_for_q(q)(tab, (uint32_t)root, ea, recv_out, send_out, (slot_t *)workspace,
-                          slot_ld(p), recv_blocks, send_blocks, (hipStream_t)stream);
+    return bcs_expand(p, n, 0, p, recv_out, send_out, recv_blocks, send_blocks, stream);
 }
 
 int bcs_sched_expand(int32_t p, int32_t root, int32_t n, int32_t *recv_out, int32_t *send_out, int32_t *recv_blocks,
