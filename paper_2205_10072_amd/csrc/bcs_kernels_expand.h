@@ -65,10 +65,17 @@ __device__ __forceinline__ void expand_store(int32_t *__restrict__ out, uint64_t
 
 // NT: streaming (non-temporal) stores.  Measured on MI355X they win while the schedule reads are a
 // visible share of the traffic (short rows) and lose to plain stores for long rows.
+// blockIdx.y: which of the two tables.
+struct ExpandTables {
+    const int32_t *in[2];
+    int32_t *out[2];
+};
+
 template <bool NT>
-__global__ __launch_bounds__(kBlock) void k_expand(const ExpandArgs a, const int32_t *__restrict__ in,
-                                                   int32_t *__restrict__ out) {
+__global__ __launch_bounds__(kBlock) void k_expand(const ExpandArgs a, const ExpandTables tables) {
     extern __shared__ int32_t tile[];     // (rows touched + 1) x (q + 9)
+    const int32_t *__restrict__ in = tables.in[blockIdx.y];
+    int32_t *__restrict__ out = tables.out[blockIdx.y];
     const uint32_t q = a.q, R = a.R, w = q + kExpPad;
     const uint64_t e0 = (uint64_t)blockIdx.x * kExpChunk;          // first entry of this workgroup
     uint64_t row0;
@@ -258,9 +265,10 @@ __global__ __launch_bounds__(kBlock) void k_rows_to_bytes(uint32_t rows, uint32_
     reinterpret_cast<uint32_t *>(rowsB)[g] = packed;
 }
 
-__global__ __launch_bounds__(kBlock) void k_expand_small(const ExpandArgs a, const int32_t *__restrict__ in,
-                                                         int32_t *__restrict__ out) {
+__global__ __launch_bounds__(kBlock) void k_expand_small(const ExpandArgs a, const ExpandTables tables) {
     __shared__ int32_t tile[kExpSmallLds];
+    const int32_t *__restrict__ in = tables.in[blockIdx.y];
+    int32_t *__restrict__ out = tables.out[blockIdx.y];
     const uint32_t q = a.q, R = a.R;
     const uint64_t e0 = (uint64_t)blockIdx.x * kExpChunk;
     const uint64_t row0 = e0 / R;

@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 #include <stdint.h>
+#include <initializer_list>
 #include <mutex>
 #include <utility>
 
@@ -282,7 +283,7 @@ LaunchFn launch_for_q(int q) {
     return table.fn[q - 1];
 }
 
-ExpandArgs expand_args(uint64_t rows, uint64_t R, int q, int32_t n, const void *out) {
+ExpandArgs expand_args(uint64_t rows, uint64_t R, int q, int32_t n) {
     ExpandArgs ea;
     ea.total = rows * R;
     ea.rows = rows;
@@ -294,12 +295,14 @@ ExpandArgs expand_args(uint64_t rows, uint64_t R, int q, int32_t n, const void *
     ea.step_j = (uint32_t)((kBlock * 4u) % R);
     ea.step_k = ea.step_j % (uint32_t)q;
     ea.wrap_k = (uint32_t)q - (uint32_t)(R % (uint64_t)q);
-    ea.aligned = (((uintptr_t)out) & 15u) == 0 ? 1 : 0;
     ea.magic_R = (uint32_t)((1ull << 32) / R + 1ull);
     ea.magic_q = q >= 2 ? (uint32_t)((1ull << 32) / (uint64_t)q + 1ull) : 0u;
     ea.magic_w = (uint32_t)((1ull << 32) / (uint64_t)(q + kExpPad) + 1ull);
     return ea;
 }
+
+// Bytes of one block table up to which both tables of a call are expanded by one launch (the calls say what it gives).
+constexpr uint64_t kTogetherBytes = 128ull << 20;
 
 int check_range(int32_t p, int32_t root, int32_t r0, int32_t r1) {
     if (p < 1 || root < 0 || root >= p || r0 < 0 || r0 > r1 || r1 > p) return BCS_EINVAL;
@@ -427,29 +430,34 @@ int bcs_expand(int32_t p, int32_t n, int32_t r0, int32_t r1, const int32_t *recv
     const uint64_t R = (uint64_t)n - 1 + q;
     if (rows == 0 || R == 0) return BCS_OK;
     hipStream_t st = (hipStream_t)stream;
-    const int32_t *ins[2] = {recv, send};
-    int32_t *outs[2] = {recv_blocks, send_blocks};
-    for (int t = 0; t < 2; ++t) {
-        if (!ins[t]) continue;
-        if (q == 0) {
-            launch(kFill, k_fill, dim3(1024), dim3(kBlock), st, outs[t], rows * R, (int32_t)BCS_NO_BLOCK);
-            continue;
-        }
-        const ExpandArgs ea = expand_args(rows, R, q, n, outs[t]);
-        const uint64_t blocks = (ea.total + kExpChunk - 1) / kExpChunk;
-        if (blocks > 0x7fffffffull) return BCS_EINVAL;
+    if (q == 0) {
+        for (int32_t *out : {recv_blocks, send_blocks})
+            if (out) launch(kFill, k_fill, dim3(1024), dim3(kBlock), st, out, rows * R, (int32_t)BCS_NO_BLOCK);
+        hipError_t e0 = hipGetLastError();
+        return e0 == hipSuccess ? BCS_OK : hip_fail(e0);
+    }
+    // Both tables in one launch: a call of a few thousand ranks is bound by its launches (2 x 7.7 MB: 13.1 us with one for
+    // each table, 9.3 us now; 2 x 81 MB 34.7 and 30.2 us).  From some hundred MB on it gives nothing (2 x 509 MB: 165 and
+    // 170 us).
+    ExpandArgs ea = expand_args(rows, R, q, n);
+    const ExpandTables both = {{recv, send}, {recv_blocks, send_blocks}};
+    auto aligned = [&](int t) { return (((uintptr_t)both.out[t]) & 15u) == 0 ? 1 : 0; };
+    const uint64_t blocks = (ea.total + kExpChunk - 1) / kExpChunk;
+    if (blocks > 0x7fffffffull) return BCS_EINVAL;
+    const bool together = recv && send && aligned(0) == aligned(1) && ea.total * sizeof(int32_t) <= kTogetherBytes;
+    for (int t = 0; t < (together ? 1 : 2); ++t) {
+        if (!both.in[t]) continue;
+        const ExpandTables tables = together ? both : ExpandTables{{both.in[t], nullptr}, {both.out[t], nullptr}};
+        const dim3 grid((unsigned)blocks, together ? 2u : 1u);
+        ea.aligned = aligned(t);
         if (R >= kExpMinR && (uint32_t)q >= kExpMinQ) {
             // rows a chunk can touch, plus one that a lane past the end may address but never uses
             const uint64_t max_rows = (R - 1 + kExpChunk - 1) / R + 2;
             const unsigned lds_bytes = (unsigned)(max_rows * (uint64_t)(q + kExpPad) * sizeof(int32_t));
-            if (R <= kExpNtMaxR)
-                launch_lds(kExpand, k_expand<true>, dim3((unsigned)blocks), dim3(kBlock), lds_bytes, st, ea, ins[t],
-                           outs[t]);
-            else
-                launch_lds(kExpand, k_expand<false>, dim3((unsigned)blocks), dim3(kBlock), lds_bytes, st, ea, ins[t],
-                           outs[t]);
+            if (R <= kExpNtMaxR) launch_lds(kExpand, k_expand<true>, grid, dim3(kBlock), lds_bytes, st, ea, tables);
+            else launch_lds(kExpand, k_expand<false>, grid, dim3(kBlock), lds_bytes, st, ea, tables);
         } else {
-            launch(kExpand, k_expand_small, dim3((unsigned)blocks), dim3(kBlock), st, ea, ins[t], outs[t]);
+            launch(kExpand, k_expand_small, grid, dim3(kBlock), st, ea, tables);
         }
     }
     hipError_t e = hipGetLastError();
@@ -471,6 +479,9 @@ constexpr uint64_t kExpandWsMinR = 256;
 inline bool expand_ws_applies(int32_t rows, int q, uint64_t R) {
     return q >= (int)kExpMinQ && R >= kExpandWsMinR && rows > 0;
 }
+// ... and tables up to kTogetherBytes are better off without: with byte rows (four launches) against without (one), block
+// tables of 7.7 MB 17.9 and 9.3 us, 81 MB 31.9 and 30.2, 161 MB 52.9 and 53.0, 266 MB 83 and 88, 1078 MB 300 and 319 us
+inline bool expand_ws_pays(int32_t rows, uint64_t R) { return (uint64_t)rows * R * sizeof(int32_t) > kTogetherBytes; }
 // rows converted and expanded at a time: their byte table fits kByteRowsMax; a multiple of 4, so that every
 // chunk's piece of the output starts on a 16-byte boundary
 inline uint32_t expand_ws_chunk_rows(uint32_t rows, int q) {
@@ -509,7 +520,7 @@ int bcs_expand_ws(int32_t p, int32_t n, int32_t r0, int32_t r1, const int32_t *r
     const bool aligned = ((recv_blocks ? (uintptr_t)recv_blocks : 0) | (send_blocks ? (uintptr_t)send_blocks : 0)) % 16 == 0;
     const bool tables_ok = (recv == nullptr) == (recv_blocks == nullptr) && (send == nullptr) == (send_blocks == nullptr) &&
                            (recv || send);
-    if (need <= 0 || !aligned || !tables_ok || !workspace || workspace_bytes < (size_t)need ||
+    if (need <= 0 || !aligned || !tables_ok || !expand_ws_pays(r1 - r0, R) || !workspace || workspace_bytes < (size_t)need ||
         (((uintptr_t)workspace) & 15u))
         return bcs_expand(p, n, r0, r1, recv, send, recv_blocks, send_blocks, stream);
     hipStream_t st = (hipStream_t)stream;
@@ -555,7 +566,6 @@ namespace {
 // workspace or kByteRowsMax are made and expanded a chunk of ranks at a time; any workspace that holds the schedules'
 // scratch will do.  (Rows of up to 128 entries used to be expanded by the workgroup that built them, 256 ranks each: 43 us
 // at 65 MB, 143 at 218 MB.)
-constexpr uint64_t kTogetherBytes = 128ull << 20;   // of one block table
 
 int sched_expand_rows(int32_t p, uint32_t root, int32_t n, int q, uint64_t R, int32_t *recv_out, int32_t *send_out,
                       int32_t *recv_blocks, int32_t *send_blocks, int8_t *ws, size_t ws_bytes, hipStream_t st) {
