@@ -803,11 +803,16 @@ int64_t bcs_pack_workspace_bytes(int32_t p) {
 }
 
 namespace {
-int pack_plan(int32_t p, int32_t n, const int32_t *idx, const int64_t *displs, int64_t *offsets, void *workspace,
-              size_t workspace_bytes, hipStream_t st, PackPlan &plan) {
+int pack_args(int32_t p, int32_t n, const int32_t *idx, const int64_t *displs, const int64_t *offsets, const void *workspace,
+              size_t workspace_bytes) {
     if (p < 1 || n < 1 || !idx || !displs || !offsets) return BCS_EINVAL;
     const int64_t need = bcs_pack_workspace_bytes(p);
     if (!workspace || workspace_bytes < (size_t)need || (((uintptr_t)workspace) & 7u)) return BCS_ENOMEM;
+    return BCS_OK;
+}
+
+int pack_plan(int32_t p, int32_t n, const int32_t *idx, const int64_t *displs, int64_t *offsets, void *workspace,
+              hipStream_t st, PackPlan &plan) {
     const uint32_t groups = (uint32_t)(((uint64_t)p + kPlanRoots - 1) / kPlanRoots);
     plan.offsets = offsets;
     plan.src = (int64_t *)workspace;
@@ -847,6 +852,22 @@ int launch_copy(int32_t p, int64_t limit, const int64_t *offsets, const int64_t 
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? BCS_OK : hip_fail(e);
 }
+// plan and payload of one round: one launch where the round is short, else the plan's launches and the payload's
+template <bool PACK>
+int launch_round(int32_t p, int32_t n, const int32_t *idx, const int64_t *displs, int64_t limit, int64_t *offsets,
+                 void *workspace, int32_t *data, int32_t *message, hipStream_t st) {
+    if ((uint32_t)p <= kRoundMaxP && limit > 0 && limit <= kRoundMaxElements) {
+        const int aligned = (int)((((uintptr_t)message) & 15u) == 0);
+        launch(kPackCopy, k_pack_round<PACK>, dim3((unsigned)((limit + kBlock * 4 - 1) / (kBlock * 4))), dim3(kBlock), st,
+               (uint32_t)p, (uint32_t)n, limit, idx, displs, offsets, data, message, aligned);
+        hipError_t e = hipGetLastError();
+        return e == hipSuccess ? BCS_OK : hip_fail(e);
+    }
+    PackPlan plan;
+    const int rc = pack_plan(p, n, idx, displs, offsets, workspace, st, plan);
+    if (rc != BCS_OK || limit == 0) return rc;
+    return launch_copy<PACK>(p, limit, offsets, plan.src, data, message, st);
+}
 inline bool copy_size_ok(int64_t limit) { return ((uint64_t)limit + kBlock * 4 - 1) / (kBlock * 4) <= 0x7fffffffull; }
 }  // namespace
 
@@ -857,10 +878,10 @@ int bcs_pack_round(int32_t p, int32_t n, const int32_t *idx, const int64_t *disp
                    void *stream) {
     if (!data || capacity < 0 || (!packed && capacity > 0)) return BCS_EINVAL;
     if (!copy_size_ok(capacity)) return BCS_EINVAL;
-    PackPlan plan;
-    const int rc = pack_plan(p, n, idx, displs, offsets, workspace, workspace_bytes, (hipStream_t)stream, plan);
-    if (rc != BCS_OK || capacity == 0) return rc;
-    return launch_copy<true>(p, capacity, offsets, plan.src, const_cast<int32_t *>(data), packed, (hipStream_t)stream);
+    const int rc = pack_args(p, n, idx, displs, offsets, workspace, workspace_bytes);
+    if (rc != BCS_OK) return rc;
+    return launch_round<true>(p, n, idx, displs, capacity, offsets, workspace, const_cast<int32_t *>(data), packed,
+                              (hipStream_t)stream);
 }
 
 int bcs_unpack_round(int32_t p, int32_t n, const int32_t *idx, const int64_t *displs, int32_t *data,
@@ -868,10 +889,10 @@ int bcs_unpack_round(int32_t p, int32_t n, const int32_t *idx, const int64_t *di
                      void *stream) {
     if (!data || length < 0 || (!packed && length > 0)) return BCS_EINVAL;
     if (!copy_size_ok(length)) return BCS_EINVAL;
-    PackPlan plan;
-    const int rc = pack_plan(p, n, idx, displs, offsets, workspace, workspace_bytes, (hipStream_t)stream, plan);
-    if (rc != BCS_OK || length == 0) return rc;
-    return launch_copy<false>(p, length, offsets, plan.src, data, const_cast<int32_t *>(packed), (hipStream_t)stream);
+    const int rc = pack_args(p, n, idx, displs, offsets, workspace, workspace_bytes);
+    if (rc != BCS_OK) return rc;
+    return launch_round<false>(p, n, idx, displs, length, offsets, workspace, data, const_cast<int32_t *>(packed),
+                               (hipStream_t)stream);
 }
 
 int bcs_pack_plan_rounds(int32_t p, int32_t n, int64_t rounds, const int32_t *idx_table, const int64_t *displs,
