@@ -131,10 +131,11 @@ def _ptr(t, numel=0, what="tensor"):
     if t is None:
         return None
     import torch
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.int32 and t.is_contiguous()):
+    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is torch.int32 and t.is_contiguous()):
         raise TypeError("expected a contiguous int32 tensor in device memory")
-    _need(t, numel, what)
-    return ctypes.c_void_p(t.data_ptr())
+    if numel and t.numel() < numel:
+        _need(t, numel, what)
+    return t.data_ptr()
 
 
 def _rows(r0, r1):
@@ -147,14 +148,16 @@ def _ws(workspace):
         return None, 0
     if not workspace.is_cuda or not workspace.is_contiguous():
         raise TypeError("expected a contiguous workspace tensor in device memory")
-    return ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size()
+    return workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
 def _stream(stream):
-    import torch
+    """The stream's handle.  Addresses and handles go to ctypes as plain numbers, and the current stream is asked for by
+    its handle: calls of a few microseconds are bound by what happens here."""
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        import torch
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def bcs_q(p):
@@ -313,10 +316,11 @@ def bcs_allgather_tables_ws(p, n, r, pack_idx, unpack_idx, workspace, stream=Non
 def _dev(t, dtype, numel=0, what="tensor"):
     """Device pointer of a contiguous device tensor of the given torch dtype and at least `numel` elements."""
     import torch
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()):
+    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is dtype and t.is_contiguous()):
         raise TypeError("expected a contiguous %s tensor in device memory" % dtype)
-    _need(t, numel, what)
-    return ctypes.c_void_p(t.data_ptr())
+    if numel and t.numel() < numel:
+        _need(t, numel, what)
+    return t.data_ptr()
 
 
 def bcs_pack_workspace_bytes(p):
