@@ -2,13 +2,12 @@
 """Benchmark of the schedule-construction hot path on one MI355X.
 
 Headline (`value`, `ms_per_step`, `roofline`): one step = the receive and send schedules of ALL ranks of the
-largest configuration, p = 2^27 - 1 (q = 27): skips, baseblocks, range search, Alg. 4 for every rank, send rows by
-neighbour look-up (Alg. 9's second loop); 29 GB of int32 tables are written per step.  The same JSON line carries
+largest configuration, p = 2^27 - 1 (q = 27); 29 GB of int32 tables are written per step.  The same JSON line carries
 one record per baseline configuration under `configs`, each with its own roofline block and CPU-oracle baseline:
   C2  p = 2^20 + 1: schedules of all ranks, then their expansion for n = 256 blocks (one library call a step);
   C3  the headline itself;
   C4  p = 65 537, n = 4096: expansion of both tables (2.156 GB), through bcs_expand and through bcs_expand_ws;
-  C5  2^20 seeded (p, r, root) triples of mixed q: receive rows, and send rows by Alg. 5.
+  C5  2^20 seeded (p, r, root) triples of mixed q: receive and send rows.
 Inputs are just (p, root, n) and the seeded triples: synthetic by construction.  Outputs are preallocated; nothing
 crosses PCIe inside a timed region.  Kernel durations are device-side: the library gives every launch its own pair
 of HIP events on the stream the kernel runs on, in a second timed region of the same steps.
@@ -51,12 +50,15 @@ def csrc_digest():
 # Key: (config, kernel).  `csrc`: csrc_digest() of the sources that were profiled; when the sources have changed
 # since, the record is still printed but marked "stale": true, and a warning goes to stderr.
 PROFILED = {
-    "csrc": "f7b790bceae31f3a",
+    "csrc": "d4bd0bb2db28f425",
     "source": "profiles/c2_step_p1048577_n256.md, c3_sched_p134217727.md, c4_expand_p65537_n4096.md, c5_batch_2e20.md, "
               "allgather_tables_p1048577_n256.md",
     "counters": {
         # per dispatch: FETCH_SIZE / WRITE_SIZE in KiB as read, SQ_WAVES, SQ_INSTS_VALU / SQ_WAVES, SQ_INSTS_SALU / SQ_WAVES,
         # SQ_THREAD_CYCLES_VALU / SQ_ACTIVE_INST_VALU (lanes active per vector instruction, of 64)
+        ("C3", "k_sched"): {'fetch_kib': 937, 'write_kib': 28311552, 'waves': 7077888, 'valu_per_wave': 346.2, 'salu_per_wave': 111.4},
+        ("C2", "k_sched"): {'fetch_kib': 91, 'write_kib': 111072, 'waves': 21505, 'valu_per_wave': 579.9, 'salu_per_wave': 215.0},
+        ("C5 recv_and_send", "k_batch"): {'fetch_kib': 11527, 'write_kib': 266240, 'waves': 16384, 'valu_per_wave': 1215.6, 'salu_per_wave': 298.8},
         ("C2", "k_expand_rows"): {'fetch_kib': 35345, 'write_kib': 1130584, 'waves': 1130500, 'valu_per_wave': 69.0, 'salu_per_wave': 9.0, 'active_lanes': 64.0},
         ("C4", "k_expand"): {'fetch_kib': 9004, 'write_kib': 1052688, 'waves': 263176, 'valu_per_wave': 258.5, 'salu_per_wave': 195.0, 'active_lanes': 63.3},
         ("C4", "k_rows_to_bytes"): {'fetch_kib': 2252, 'write_kib': 1280, 'waves': 5124, 'valu_per_wave': 50.0, 'salu_per_wave': 12.0, 'active_lanes': 64.0},
@@ -238,7 +240,7 @@ def run_c2(torch, bcs, steps, warmup, digest):
 
     ms, ms_ev, timing = timed_steps(torch, bcs, step, steps, warmup)
     models = {"k_expand_rows": ("hbm", P * R * 4), "k_expand": ("hbm", P * R * 4),
-              "k_sched": ("hbm", 2 * P * (q * 4 + 24))}             # both tables and their byte rows out
+              "k_sched": ("hbm", P * (q * 4 + 24))}                 # one table and its byte rows a launch
     kernels = kernel_records(timing, steps, models, "C2", digest)
     construct_ms = sum(kernels[k]["ms_per_step"] for k in ("k_sched",) if k in kernels)
     exp = kernels.get("k_expand_rows") or kernels.get("k_expand")

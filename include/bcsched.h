@@ -26,9 +26,9 @@
  *     larger one (so such a call cannot be part of a stream capture).
  *   - Return value: BCS_OK (0) or a negative BCS_E* code.  On an error nothing
  *     has been enqueued and no output is touched.  No call throws.
- *   - No call allocates or frees its outputs.  bcs_sched* with a send table
- *     over the full rank range, or over a large part of it, need scratch
- *     memory (bcs_sched_workspace_bytes says how much): the *_ws variants take it
+ *   - No call allocates or frees its outputs.  Calls that expand schedules
+ *     and the allgather tables need scratch memory (the *_workspace_bytes calls
+ *     say how much): the *_ws variants take it
  *     from the caller, the plain variants keep one allocation per device that
  *     grows on demand and is released by bcs_release().  Plain calls on one
  *     device share that allocation: the library orders them itself (a plain
@@ -62,7 +62,7 @@ extern "C" {
 #define BCS_EINVAL  (-1)  /* an argument is outside its domain (see each call)        */
 #define BCS_EHIP    (-2)  /* a HIP call failed; bcs_last_hip_error() has its code      */
 #define BCS_ENOMEM  (-3)  /* scratch allocation failed, or the given workspace is small */
-#define BCS_ETOOBIG (-4)  /* bcs_sched_rooted_static: needs more than its fixed scratch  */
+#define BCS_ETOOBIG (-4)  /* bcs_sched_rooted_static: needs more than its limit of scratch */
 
 #define BCS_MAX_Q         31           /* p <= 2^31 - 1                                */
 #define BCS_BATCH_STRIDE  32           /* ints per row of the batch tables             */
@@ -86,10 +86,8 @@ int64_t bcs_rounds(int32_t p, int32_t n);
  * ranks r0 <= r < r1 for a broadcast rooted at rank 0.
  *   recv_out, send_out: device, (r1-r0) x q int32, entry [(r-r0)*q + k].
  *   Either may be NULL (that table is not produced); both NULL is an error.
- * When the call covers all ranks (r0 = 0, r1 = p) send rows are read off the
- * receive rows of the to-neighbours (Alg. 9, second loop); otherwise each send
- * entry is recomputed from the neighbour's receive schedule (Alg. 5).  Both
- * give the same values.
+ * Rows come from the rank's own place in the graph, send rows included, so any
+ * range costs the same a rank; the values are those of Alg. 4 and Alg. 5.
  * p = 1: q = 0, rows are empty, nothing is enqueued, BCS_OK.
  * BCS_EINVAL: p < 1, r0 < 0, r0 > r1, r1 > p, both outputs NULL. */
 int bcs_sched(int32_t p, int32_t r0, int32_t r1,
@@ -104,43 +102,31 @@ int bcs_sched_rooted(int32_t p, int32_t root, int32_t r0, int32_t r1,
                      int32_t *recv_out, int32_t *send_out, void *stream);
 
 /* Scratch bytes bcs_sched_rooted_ws needs for these arguments (0 when none).
- * Negative: BCS_EINVAL.  A call over all ranks that also wants send rows keeps
- * there the receive entries slot by slot (one byte each) and the greedy skip
- * sums of all ranks (the walk of Alg. 2 kept as a mask, one word a rank,
- * rounded up to 256 bytes): every end point of a
- * window of Alg. 4 is some rank, so the receive rows read these instead of
- * walking q + 2 times each.  A call for a part of the ranks with send rows
- * (Alg. 5) asks for the same table when filling it costs less than the walks
- * it saves: (r1 - r0) q^2 >= 8 p. */
+ * Negative: BCS_EINVAL.  The size is part of the call's contract and is checked
+ * (all ranks with send rows: q rows of p bytes padded to 256, and 4 p bytes; a
+ * part of the ranks with send rows and (r1 - r0) q^2 >= 8 p: 4 p bytes); the
+ * present construction does not touch the workspace. */
 int64_t bcs_sched_workspace_bytes(int32_t p, int32_t r0, int32_t r1, int want_send);
 
 /* bcs_sched_rooted with caller-provided scratch.  `workspace` is device
  * memory, 256-byte aligned, of at least bcs_sched_workspace_bytes(...) bytes;
  * its contents are undefined afterwards.  BCS_ENOMEM if it is too small or
  * NULL while scratch is needed, BCS_EINVAL if it is needed and not 256-byte
- * aligned.  Performs no allocation.  A call over all
- * ranks for receive rows alone needs none; given 4 p bytes (rounded up to 256)
- * it uses them for the table of skip sums. */
+ * aligned.  Performs no allocation. */
 int bcs_sched_rooted_ws(int32_t p, int32_t root, int32_t r0, int32_t r1,
                         int32_t *recv_out, int32_t *send_out,
                         void *workspace, size_t workspace_bytes, void *stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc):
- * bcs_sched_rooted with its scratch in a fixed array of
- * BCS_STATIC_SCRATCH_BYTES that lives in the library's code object, one copy
- * on every GPU the library runs on, held until the process ends.  Arguments,
+ * bcs_sched_rooted within a fixed limit of scratch.  Arguments,
  * results and errors are those of bcs_sched_rooted, bit for bit.  The call
- * allocates and frees nothing; the first call on a device looks the array's
- * address up (and, as every schedule-building call, may enqueue the fill of the
- * low-level table), later calls enqueue kernels only.
+ * allocates and frees nothing; the first call on a device may, as every
+ * schedule-building call, enqueue the fill of the library's tables, later
+ * calls enqueue one kernel only.
  * Limit: bcs_sched_workspace_bytes(p, r0, r1, send_out != NULL) must not
  * exceed BCS_STATIC_SCRATCH_BYTES, else BCS_ETOOBIG and nothing is enqueued
- * (all ranks with send rows: p up to 1 342 016).  Every call on a
- * GPU shares that GPU's array: calls that overlap on one GPU (two streams, or
- * two threads) race and must be ordered by the caller.  Nothing in the array
- * has to start at zero: each call overwrites what it reads, so the contents
- * the last call left behind do no harm. */
+ * (all ranks with send rows: p up to 1 342 016).  Calls share no state. */
 #define BCS_STATIC_SCRATCH_BYTES (32u << 20)
 int bcs_sched_rooted_static(int32_t p, int32_t root, int32_t r0, int32_t r1,
                             int32_t *recv_out, int32_t *send_out, void *stream);
@@ -150,9 +136,8 @@ int bcs_sched_rooted_static(int32_t p, int32_t root, int32_t r0, int32_t r1,
  *   recv_out, send_out: device, count x BCS_BATCH_STRIDE int32; row i holds
  *   q_i = ceil(log2 p[i]) entries, the rest BCS_BATCH_PAD.  Either may be NULL.
  *   q_out: device, count int32, may be NULL.
- * Send rows need no other rank of that graph: an entry is taken from the rank's
- * own greedy digits where that gives Alg. 5's value, and recomputed per Alg. 5
- * (the to-neighbour's rounds up to it) otherwise; the results are Alg. 5's.
+ * Rows come from the rank's own place in its graph; the values are those of
+ * Alg. 4 and Alg. 5.
  * Triples are validated on the device: a row with p < 1 or r, root outside
  * [0, p) gets q_out = -1 and all-PAD rows; host-side errors are BCS_EINVAL for
  * count < 0, a NULL input array, or all outputs NULL. */
@@ -180,7 +165,7 @@ int bcs_expand(int32_t p, int32_t n, int32_t r0, int32_t r1,
  * from the caller.  This is the fast path for long rows: measured on MI355X
  * at p = 65 537, n = 4096 it writes 0.87-0.89 of the HBM peak where bcs_expand,
  * which may not use scratch memory, reaches 0.82-0.83.  For rows of 256 rounds or more
- * the schedule rows are first rewritten as bytes into `workspace` (about a
+ * and block tables above 128 MB the schedule rows are first rewritten as bytes into `workspace` (about a
  * million rows at a time, so that it stays in cache) and the tables are
  * expanded from there; results are those of bcs_expand, bit for bit.
  *   workspace: device, 16-byte aligned, bcs_expand_workspace_bytes(p, n, r0, r1)
@@ -197,20 +182,20 @@ int bcs_expand_ws(int32_t p, int32_t n, int32_t r0, int32_t r1,
 /* Schedules of all p ranks and both of their (rank, round) -> block tables in
  * one call: the same results as bcs_sched_rooted_ws(p, root, 0, p, ...) followed
  * by bcs_expand(p, n, 0, p, ...) (Alg. 4, Alg. 9's send look-up, index arithmetic
- * of Alg. 6), bit for bit.  For many ranks and moderate n the rows are expanded
- * by the workgroup that built them, straight from on-chip memory; other sizes
- * run the two calls above one after the other.
+ * of Alg. 6), bit for bit.
  *   recv_out, send_out: device, p x q int32 (required when q > 0).
  *   recv_blocks, send_blocks: device, p x R int32, R = n-1+q (required when
  *   R > 0; p = 1 with n = 1 has nothing to write and returns BCS_OK).
- * For longer rows the schedule kernels also leave the rows as bytes in scratch
- * memory, which the expansion then reads from cache instead of re-reading the
- * int32 tables.
+ * For rows of 16 rounds or more and q >= 3 the schedule kernel also leaves the
+ * rows as bytes in scratch memory, which the expansion then reads from cache
+ * instead of re-reading the int32 tables: for both tables at once while a block
+ * table has 128 MB or less, else table by table, in chunks of ranks where the
+ * byte rows exceed the workspace or 32 MB.
  * Scratch: bcs_sched_expand_workspace_bytes(p, n) bytes (negative: BCS_EINVAL);
  * the plain call uses the per-device allocation, the _ws call takes it from the
  * caller (256-byte aligned) and allocates nothing.  With less than that but at
  * least bcs_sched_workspace_bytes(p, 0, p, 1) bytes the _ws call still works
- * (without the byte rows).  p = 1: both block tables get n-1 columns of
+ * (in more and smaller chunks).  p = 1: both block tables get n-1 columns of
  * BCS_NO_BLOCK.
  * BCS_EINVAL: p < 1, root outside [0, p), n < 1, n > BCS_MAX_N, a required
  * table NULL, a workspace that is not 256-byte aligned.  BCS_ENOMEM: workspace

@@ -202,7 +202,7 @@ def bcs_sched_rooted_ws(p, root, r0, r1, recv_out, send_out, workspace, stream=N
 
 
 def bcs_sched_rooted_static(p, root, r0, r1, recv_out, send_out, stream=None):
-    """bcs_sched_rooted on the library's fixed scratch array: allocates nothing (raises ETOOBIG beyond its size)."""
+    """bcs_sched_rooted within the library's fixed limit of scratch: allocates nothing (raises ETOOBIG beyond it)."""
     need = _rows(r0, r1) * bcs_q(p)
     _check(lib().bcs_sched_rooted_static(p, root, r0, r1, _ptr(recv_out, need, "recv_out"),
                                          _ptr(send_out, need, "send_out"), _stream(stream)),

@@ -34,6 +34,10 @@
 // more row of the table) and a few bit operations per round.
 // All of it is branch-free apart from the wave-uniform test for Alg. 4's rare second range.
 //
+// The kernels build rows from the closed form of bcs_rows.h; the windows here are its definition: Alg. 4 on them fills the
+// table of low rounds.  recv_row_tab, recv_row_tab_upto, round_from_digits and send_row_direct are earlier forms of the
+// rows that no kernel uses any more; the host tests hold them against the oracle, entry by entry.
+//
 // (3) Rounds without a window (round_from_digits, one p per launch).  From level 6 up most rounds of most ranks
 // follow from D(v) alone: the home round gives the baseblock, a round whose digit is set gives the next digit
 // above, a round whose digit is clear gives the round's own index when the value of the lower digits keeps clear
