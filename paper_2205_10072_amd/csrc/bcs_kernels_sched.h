@@ -12,7 +12,7 @@ namespace {
 // The low-level table of bcs_core.h lives in the code object; k_build_lowtab fills it once per device
 // and process (one thread per entry, by the level walk).
 // ----------------------------------------------------------------------------------------------
-__device__ __align__(16) uint8_t g_lowtab[kLowTableBytes];   // read a dword at a time by stage_lowtab
+__device__ __align__(16) uint8_t g_lowtab[kLowTableBytes];   // read by k_build_lowrows
 
 __global__ __launch_bounds__(kBlock) void k_build_lowtab() {
     const int e = blockIdx.x * kBlock + threadIdx.x;
@@ -20,12 +20,6 @@ __global__ __launch_bounds__(kBlock) void k_build_lowtab() {
     const int shape = e / kLowShapeBytes;
     const int rest = e - shape * kLowShapeBytes;
     g_lowtab[e] = (uint8_t)low_table_entry(shape, rest >> 7, rest & 127);
-}
-
-// copies one shape of the table (kLowShapeBytes, a multiple of 4) into LDS; callers synchronise
-__device__ __forceinline__ void stage_lowtab(uint32_t *dst, int shape) {
-    const uint32_t *src = reinterpret_cast<const uint32_t *>(g_lowtab + (size_t)shape * kLowShapeBytes);
-    for (int i = threadIdx.x; i < kLowShapeBytes / 4; i += kBlock) dst[i] = src[i];
 }
 
 // ----------------------------------------------------------------------------------------------

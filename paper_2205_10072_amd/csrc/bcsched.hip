@@ -4,7 +4,7 @@
 // One lane owns one rank.  Everything is 32-bit integer work on the vector ALU; block sets are
 // 32-bit masks (q <= 31); the skips of a uniform-p launch live in scalar registers.
 //
-// The per-rank construction is in bcs_core.h, the kernels in bcs_kernels_*.h; this file holds the launch and
+// The per-rank construction is in bcs_rows.h (its definition by windows in bcs_core.h), the kernels in bcs_kernels_*.h; this file holds the launch and
 // timing helpers, the host logic and the C ABI.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
@@ -328,16 +328,12 @@ int64_t bcs_rounds(int32_t p, int32_t n) {
     return (int64_t)n - 1 + host_q(p);
 }
 
-// Scratch of a launch over all ranks with a send table: the slot-major receive table, then the digit masks of
-// all ranks (one word each).
+// The sizes that bcs_sched_workspace_bytes states: for all ranks with send rows a slot-major receive table (which the allgather
+// tables keep in their workspace) and a word a rank, for a large part of the ranks the words alone.  The schedules
+// themselves use none of it; callers' buffers and refusals go by these sizes.
 inline uint64_t slot_table_bytes(int32_t p, int q) { return slot_ld(p) * (uint64_t)q * sizeof(slot_t); }
-// The digit table pays at every size (measured on MI355X: receive rows of all ranks in 0.57-0.73 of the walking
-// kernel's time from 2^18 to 2^27 ranks, table pass included), with all of a row's reads issued up front.
 inline uint64_t digit_table_bytes(int32_t p) { return round_up((uint64_t)p * sizeof(uint32_t), 256); }
 
-// A part of the ranks with send rows (Alg. 5) takes the digit table when filling it (p walks) costs less than the
-// walks it saves (about q^2 / 2 a rank).  Measured: 2^20 ranks of 2^20+1 gain 0.27 ms, 2^20 ranks of 2^27-1
-// (q^2 (r1 - r0) = 5.7 p) lose 0.02 ms to the 0.32 ms the table of 2^27 ranks takes.
 inline bool partial_range_tabled(int32_t p, int q, int32_t r0, int32_t r1) {
     return (uint64_t)(r1 - r0) * (uint64_t)(q * q) >= 8ull * (uint64_t)p;
 }
