@@ -50,7 +50,7 @@ def csrc_digest():
 # Key: (config, kernel).  `csrc`: csrc_digest() of the sources that were profiled; when the sources have changed
 # since, the record is still printed but marked "stale": true, and a warning goes to stderr.
 PROFILED = {
-    "csrc": "102d2afd42269d55",
+    "csrc": "0458ee3fc4ba6703",
     "source": "profiles/c2_step_p1048577_n256.md, c3_sched_p134217727.md, c4_expand_p65537_n4096.md, c5_batch_2e20.md, "
               "allgather_tables_p1048577_n256.md",
     "counters": {

