@@ -301,6 +301,13 @@ ExpandArgs expand_args(uint64_t rows, uint64_t R, int q, int32_t n) {
     return ea;
 }
 
+// A launch takes fewer than 2^32 lanes along a grid dimension, so kernels whose lanes write four entries each take at most
+// this many entries (69 GB), whole workgroups: longer tables go by ranges of rows, multiples of four so that every range's
+// piece of the table starts on 16 bytes.
+constexpr uint64_t kMaxLanes = 0xffffffffull;
+constexpr uint64_t kLaunchEntries = kMaxLanes / kBlock * kBlock * 4;
+inline uint64_t rows_per_launch(uint64_t R) { return kLaunchEntries / R & ~(uint64_t)3; }      // R < 2^31: at least 4
+
 // Bytes of one block table up to which both tables of a call are expanded by one launch (the calls say what it gives).
 constexpr uint64_t kTogetherBytes = 128ull << 20;
 
@@ -521,7 +528,8 @@ int bcs_expand_ws(int32_t p, int32_t n, int32_t r0, int32_t r1, const int32_t *r
         return bcs_expand(p, n, r0, r1, recv, send, recv_blocks, send_blocks, stream);
     hipStream_t st = (hipStream_t)stream;
     const uint32_t rows = (uint32_t)(r1 - r0);
-    const uint32_t chunk = expand_ws_chunk_rows(rows, q);
+    const uint64_t by_bytes = expand_ws_chunk_rows(rows, q), by_lanes = rows_per_launch(R);
+    const uint32_t chunk = (uint32_t)(by_bytes < by_lanes ? by_bytes : by_lanes);
     const uint32_t RS = (uint32_t)byte_row_stride(q), w4 = RS / 4;
     const int32_t *ins[2] = {recv, send};
     int32_t *outs[2] = {recv_blocks, send_blocks};
@@ -533,7 +541,6 @@ int bcs_expand_ws(int32_t p, int32_t n, int32_t r0, int32_t r1, const int32_t *r
             const uint32_t rc = rows - c0 < chunk ? rows - c0 : chunk;
             const ExpandRowsArgs ra = expand_rows_args(rc, R, q, n);
             const uint64_t pieces = (ra.total + kBlock * 4 - 1) / (kBlock * 4);
-            if (pieces > 0x7fffffffull) return BCS_EINVAL;
             launch(kRowsToBytes, k_rows_to_bytes, dim3((rc * w4 + kBlock - 1) / kBlock), dim3(kBlock), st, rc, (uint32_t)q,
                    RS, (uint32_t)((1ull << 32) / w4 + 1ull), ins[t] + (uint64_t)c0 * q, (int8_t *)workspace);
             launch(kExpandRows, k_expand_rows, dim3((unsigned)pieces), dim3(kBlock), st, ra, (const int8_t *)workspace,
@@ -568,10 +575,10 @@ int sched_expand_rows(int32_t p, uint32_t root, int32_t n, int q, uint64_t R, in
     const uint64_t RS = (uint64_t)byte_row_stride(q), rows_bytes = byte_rows_bytes(p, q);
     const bool together = 2 * rows_bytes <= ws_bytes && (uint64_t)p * R * 4u <= kTogetherBytes;
     const uint64_t cap = ws_bytes < kByteRowsMax ? ws_bytes : kByteRowsMax;
-    const uint64_t fit = (cap / RS - 1u) & ~(uint64_t)3;               // a multiple of 4 rows: pieces start on 16 bytes
+    const uint64_t by_bytes = (cap / RS - 1u) & ~(uint64_t)3, by_lanes = rows_per_launch(R);      // multiples of 4
+    const uint64_t fit = by_bytes < by_lanes ? by_bytes : by_lanes;
     const uint32_t chunk = together || (uint64_t)p <= fit ? (uint32_t)p : (uint32_t)fit;
     if (chunk == 0) return BCS_ENOMEM;
-    if (((uint64_t)chunk * R + kBlock * 4 - 1) / (kBlock * 4) > 0x7fffffffull) return BCS_EINVAL;
     SkipTab tab;
     host_skips(p, tab);
     int rc = ensure_lowtab(st);

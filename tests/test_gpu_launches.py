@@ -1,0 +1,57 @@
+"""GPU tests of tables that one launch of a kernel cannot cover (2^32 lanes), against the index arithmetic of Alg. 6 and the
+oracle.  What is launched for such sizes is checked in full on the CPU (test_launches.py)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bcs():
+    import paper_2205_10072_amd as m
+    m.lib()
+    return m
+
+
+def _check(p, n, sched, blocks, oracle, seed):
+    """`blocks` against the index arithmetic of Alg. 6 on `sched` with tensor operations, a range of rows at a time, and
+    sampled rows against the oracle."""
+    q, R = sched.shape[1], blocks.shape[1]
+    x = (q - R % q) % q
+    j = torch.arange(R, device="cuda")
+    k = (x + j) % q
+    shift = (j - k).to(torch.int32)
+    step = max(1, (1 << 28) // R)
+    for r0 in range(0, p, step):
+        want = (sched[r0:r0 + step][:, k] + shift).clamp_(min=-1, max=n - 1)
+        assert torch.equal(blocks[r0:r0 + step], want), r0
+        del want
+    rng = np.random.default_rng(seed)
+    for r in [0, 1, p - 1] + [int(v) for v in rng.integers(0, p, 20)]:
+        assert np.array_equal(blocks[r].cpu().numpy()[None], oracle.expand(p, n, sched[r:r + 1].cpu().numpy())), r
+
+
+def test_block_tables_of_more_than_2_to_34_entries(bcs, oracle):
+    """2 x 69 GB in one call with the schedules' workspace, then one of them again through bcs_expand_ws."""
+    p, n, root = (1 << 20) + 1, 16500, 12345
+    q, R = bcs.bcs_q(p), bcs.bcs_rounds(p, n)
+    assert p * R > 1 << 34
+    print("one call, 2 x %.1f GB" % (4e-9 * p * R), flush=True)
+    recv, send = (torch.empty((p, q), dtype=torch.int32, device="cuda") for _ in range(2))
+    rb, sb = (torch.full((p, R), 4242, dtype=torch.int32, device="cuda") for _ in range(2))
+    ws = torch.empty(bcs.bcs_sched_workspace_bytes(p, 0, p), dtype=torch.uint8, device="cuda")
+    bcs.bcs_sched_expand_ws(p, root, n, recv, send, rb, sb, ws)
+    torch.cuda.synchronize()
+    orecv, osend = oracle.sched_range(p, root=root, threads=16)
+    assert np.array_equal(recv.cpu().numpy(), orecv) and np.array_equal(send.cpu().numpy(), osend)
+    _check(p, n, recv, rb, oracle, 1)
+    _check(p, n, send, sb, oracle, 2)
+    print("bcs_expand_ws, one table", flush=True)
+    sb.fill_(4242)
+    ws = torch.empty(bcs.bcs_expand_workspace_bytes(p, n, 0, p), dtype=torch.uint8, device="cuda")
+    bcs.bcs_expand_ws(p, n, 0, p, recv, None, sb, None, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(rb, sb)
+    del recv, send, rb, sb, ws
+    torch.cuda.empty_cache()

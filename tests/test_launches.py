@@ -1,0 +1,53 @@
+"""CPU tests of what the calls enqueue: the real library on a stand-in runtime (launchlog.py), which refuses a launch of
+2^32 lanes or more as the HIP runtime does."""
+import pytest
+
+from launchlog import launches, run, shown
+
+
+def _covers(pieces, start, entries, size=4):
+    """(address, entries) pieces follow one another from `start` and make up `entries`, each at a 16-byte address."""
+    at = start
+    for address, count in pieces:
+        assert address == at and address % 16 == 0 and count > 0
+        at += count * size
+    assert at == start + entries * size
+
+
+BIG = [((1 << 20) + 1, 17000), ((1 << 20) + 1, 16405), (9, 2**31 - 100), (33, 600000000), (70000, 300000)]
+
+
+@pytest.mark.parametrize("need", ["L.bcs_sched_workspace_bytes(p, 0, p, 1)", "L.bcs_sched_expand_workspace_bytes(p, n)"])
+@pytest.mark.parametrize("p,n", BIG)
+def test_block_tables_of_more_than_2_to_34_entries_in_one_call(tmp_path, p, n, need):
+    """bcs_sched_expand_ws, with the schedules' workspace alone and with its own: every launch stays below 2^32 lanes and
+    the pieces of both block tables are complete."""
+    log = run(tmp_path, """
+p, n = %d, %d
+show(L.bcs_sched_expand_ws(p, 1, n, T(1), T(2), T(3), T(4), T(5), %s, None))
+""" % (p, n, need))
+    assert shown(log) == [0]
+    R = n - 1 + (p - 1).bit_length()
+    for table in (3, 4):
+        _covers([(e["arg"][3], e["arg"][0]) for e in launches(log, "k_expand_rows") if e["arg"][3] >> 44 == table],
+                table << 44, p * R)
+
+
+@pytest.mark.parametrize("p,n", BIG)
+def test_block_tables_of_more_than_2_to_34_entries_from_schedule_rows(tmp_path, p, n):
+    log = run(tmp_path, """
+need = L.bcs_expand_workspace_bytes(%d, %d, 1, %d)
+show(L.bcs_expand_ws(%d, %d, 1, %d, T(1), T(2), T(3), T(4), T(5), need, None))
+""" % (p, n, p, p, n, p))
+    R, q = n - 1 + (p - 1).bit_length(), (p - 1).bit_length()
+    assert shown(log) == [0]
+    for table in (3, 4):
+        _covers([(e["arg"][3], e["arg"][0]) for e in launches(log, "k_expand_rows") if e["arg"][3] >> 44 == table],
+                table << 44, (p - 1) * R)
+    # each expansion reads what the conversion before it left: the same rows
+    todo = launches(log)
+    for made, used in zip(todo[0::2], todo[1::2]):
+        assert (made["name"], used["name"]) == ("k_rows_to_bytes", "k_expand_rows")
+        assert made["arg"][0] * R == used["arg"][0] and made["arg"][5] == used["arg"][1] == 5 << 44
+        first = (used["arg"][3] - ((used["arg"][3] >> 44) << 44)) // (4 * R)
+        assert made["arg"][4] == ((used["arg"][3] >> 44) - 2 << 44) + 4 * first * q
