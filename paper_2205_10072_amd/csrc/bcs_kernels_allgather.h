@@ -16,7 +16,8 @@ namespace {
 // of q only, so a workgroup takes one slot and kAgChunk consecutive roots, reads its 2 x kAgChunk
 // schedule entries once and walks down the rounds k-x, k-x+q, ..., writing one contiguous piece of
 // kAgChunk entries per table and round; lanes are consecutive roots, so every store of a wave is one
-// contiguous 256-byte piece.  k_allgather_tables_flat (16-byte aligned outputs) is described with it.
+// contiguous 256-byte piece.  Also the kernel for tables that one launch of k_allgather_tables_flat (16-byte aligned
+// outputs, up to 2^34 entries; described below) cannot cover.
 // ----------------------------------------------------------------------------------------------
 constexpr int kAgRootsPerLane = 16;
 constexpr int kAgChunk = kAgRootsPerLane * kBlock;

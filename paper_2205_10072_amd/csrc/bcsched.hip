@@ -703,7 +703,7 @@ int bcs_allgather_tables_ws(int32_t p, int32_t n, int32_t r, int32_t *pack_idx, 
     const unsigned bx = (unsigned)(((uint64_t)p + kAgChunk - 1) / kAgChunk);
     const uint32_t x = (uint32_t)((q - (int)(R % (uint64_t)q)) % q);
     const bool vec = ((((uintptr_t)pack_idx) | ((uintptr_t)unpack_idx)) & 15u) == 0;
-    if (vec) {
+    if (vec && R * (uint64_t)p <= kLaunchEntries) {
         AgFlatArgs fa;
         fa.total = R * (uint64_t)p;
         fa.magic_p = ~0ull / (uint64_t)p + 1ull;
@@ -714,7 +714,6 @@ int bcs_allgather_tables_ws(int32_t p, int32_t n, int32_t r, int32_t *pack_idx, 
         fa.nm1 = n - 1;
         fa.magic_q = (uint32_t)((1ull << 32) / (uint64_t)q + 1ull);
         const uint64_t pieces = (fa.total + kBlock * 4 - 1) / (kBlock * 4);
-        if (pieces > 0x7fffffffull) return BCS_EINVAL;
         launch(kAllgather, k_allgather_tables_flat, dim3((unsigned)pieces, (pack_idx && unpack_idx) ? 2u : 1u),
                dim3(kBlock), st, tab, fa, (const slot_t *)recvT, ld, pack_idx, unpack_idx);
     } else {

@@ -55,3 +55,25 @@ def test_block_tables_of_more_than_2_to_34_entries(bcs, oracle):
     assert torch.equal(rb, sb)
     del recv, send, rb, sb, ws
     torch.cuda.empty_cache()
+
+
+def test_allgather_table_of_more_than_2_to_34_entries(bcs, oracle):
+    """One 69 GB table, every round against the defining index arithmetic on the oracle's receive rows."""
+    p, n, r = (1 << 20) + 1, 16500, 777777
+    q, R = bcs.bcs_q(p), bcs.bcs_rounds(p, n)
+    assert p * R > 1 << 34
+    pack = torch.full((R, p), 4242, dtype=torch.int32, device="cuda")
+    ws = torch.empty(bcs.bcs_allgather_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    bcs.bcs_allgather_tables_ws(p, n, r, pack, None, ws)
+    torch.cuda.synchronize()
+    recv = torch.from_numpy(oracle.sched_range(p, want_send=False, threads=16)[0]).cuda()
+    skips, x = bcs.bcs_skips(p), (q - R % q) % q
+    vr = (r - torch.arange(p, device="cuda")) % p
+    cols = [recv[:, k].contiguous()[(vr + int(skips[k])) % p] for k in range(q)]
+    same = torch.ones((), dtype=torch.bool, device="cuda")
+    for j in range(R):
+        k = (x + j) % q
+        same &= (pack[j] == (cols[k] + (j - k)).clamp_(min=-1, max=n - 1)).all()
+    assert bool(same)
+    del pack, recv, cols, ws
+    torch.cuda.empty_cache()

@@ -51,3 +51,17 @@ show(L.bcs_expand_ws(%d, %d, 1, %d, T(1), T(2), T(3), T(4), T(5), need, None))
         assert made["arg"][0] * R == used["arg"][0] and made["arg"][5] == used["arg"][1] == 5 << 44
         first = (used["arg"][3] - ((used["arg"][3] >> 44) << 44)) // (4 * R)
         assert made["arg"][4] == ((used["arg"][3] >> 44) - 2 << 44) + 4 * first * q
+
+
+@pytest.mark.parametrize("p,n,one", [((1 << 20) + 1, 17000, False), ((1 << 20) + 1, 17000, True), (9, 2**31 - 100, False),
+                                     ((1 << 20) + 1, 16300, False)])
+def test_allgather_tables_of_more_than_2_to_34_entries(tmp_path, p, n, one):
+    log = run(tmp_path, """
+need = L.bcs_allgather_workspace_bytes(%d)
+show(L.bcs_allgather_tables_ws(%d, %d, 3, T(1), %s, T(3), need, None))
+""" % (p, p, n, "None" if one else "T(2)"))
+    assert shown(log) == [0]
+    last = launches(log)[-1]
+    flat = p * (n - 1 + (p - 1).bit_length()) < 1 << 34            # else by slots and pieces of 4096 roots
+    assert last["name"] == ("k_allgather_tables_flat" if flat else "k_allgather_tables")
+    assert last["grid"][:2] == ([last["grid"][0], 2] if flat else [(p + 4095) // 4096, (p - 1).bit_length()])
