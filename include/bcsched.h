@@ -299,7 +299,7 @@ int bcs_allgather_plan(int32_t p, int32_t r, int32_t *to, int32_t *from,
 int bcs_census_plan(int32_t p, int32_t r, int32_t *to, int32_t *from, int32_t *own);
 
 /* The partner tables of the same two collectives for the processes [r0, r1) at
- * once, written by one kernel (HBM-bound, pure stores): what a launcher or a
+ * once, written by one kernel (HBM-bound, pure stores; a launch for every 17 G entries): what a launcher or a
  * simulator of the whole machine needs, and the device-side form of the two
  * plans above.  to and from are device arrays of (r1 - r0) * q int32, entry
  * [(r - r0) * q + k]; either may be NULL.

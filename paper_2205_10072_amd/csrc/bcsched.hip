@@ -775,14 +775,19 @@ int partner_tables(int32_t p, int32_t r0, int32_t r1, uint32_t census, int32_t *
     const uint64_t total = (uint64_t)(r1 - r0) * (uint64_t)q;
     if (total == 0) return BCS_OK;                                          // p = 1 or an empty range
     if (!to && !from) return BCS_EINVAL;
-    const uint64_t blocks = (total + kBlock * 4 - 1) / (kBlock * 4);       // at most 2^31 * 31 / 1024
     const bool vec = ((((uintptr_t)to) | ((uintptr_t)from)) & 15u) == 0;
-    if (vec)
-        launch(kPartnerTables, k_partner_tables<true>, dim3((unsigned)blocks), dim3(kBlock), (hipStream_t)stream,
-               (uint32_t)p, (uint32_t)q, census, (uint32_t)r0, total, to, from);
-    else
-        launch(kPartnerTables, k_partner_tables<false>, dim3((unsigned)blocks), dim3(kBlock), (hipStream_t)stream,
-               (uint32_t)p, (uint32_t)q, census, (uint32_t)r0, total, to, from);
+    const uint64_t step = kLaunchEntries / (uint64_t)q & ~(uint64_t)3;      // rows a launch; 31 * 2^31 entries take four
+    for (uint64_t row = 0; row < (uint64_t)(r1 - r0); row += step) {
+        const uint64_t rest = total - row * q, count = rest < step * q ? rest : step * q;
+        const dim3 grid((unsigned)((count + kBlock * 4 - 1) / (kBlock * 4)));
+        int32_t *const t = to ? to + row * q : nullptr, *const f = from ? from + row * q : nullptr;
+        if (vec)
+            launch(kPartnerTables, k_partner_tables<true>, grid, dim3(kBlock), (hipStream_t)stream, (uint32_t)p,
+                   (uint32_t)q, census, (uint32_t)r0 + (uint32_t)row, count, t, f);
+        else
+            launch(kPartnerTables, k_partner_tables<false>, grid, dim3(kBlock), (hipStream_t)stream, (uint32_t)p,
+                   (uint32_t)q, census, (uint32_t)r0 + (uint32_t)row, count, t, f);
+    }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? BCS_OK : hip_fail(e);
 }

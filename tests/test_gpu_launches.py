@@ -77,3 +77,21 @@ def test_allgather_table_of_more_than_2_to_34_entries(bcs, oracle):
     assert bool(same)
     del pack, recv, cols, ws
     torch.cuda.empty_cache()
+
+
+def test_partner_table_of_more_than_2_to_34_entries(bcs):
+    """The to-processes of so many processes that a second launch writes the end of the table (69 GB): every entry against
+    the distances of Alg. 7."""
+    p, r0 = 2**30 + 1, 77
+    q, rows = bcs.bcs_q(p), 2**34 // bcs.bcs_q(p) + 1001
+    assert rows * q > 1 << 34 and r0 + rows < p
+    to = torch.full((rows, q), -7, dtype=torch.int32, device="cuda")
+    bcs.bcs_allgather_partners(p, r0, r0 + rows, to, None)
+    torch.cuda.synchronize()
+    dist = torch.tensor(bcs.bcs_skips(p)[:q], device="cuda", dtype=torch.int64)
+    step = 1 << 22
+    for a in range(0, rows, step):
+        r = torch.arange(r0 + a, r0 + min(rows, a + step), device="cuda", dtype=torch.int64)
+        assert torch.equal(to[a:a + step].long(), (r[:, None] - dist) % p), a
+    del to
+    torch.cuda.empty_cache()

@@ -65,3 +65,19 @@ show(L.bcs_allgather_tables_ws(%d, %d, 3, T(1), %s, T(3), need, None))
     flat = p * (n - 1 + (p - 1).bit_length()) < 1 << 34            # else by slots and pieces of 4096 roots
     assert last["name"] == ("k_allgather_tables_flat" if flat else "k_allgather_tables")
     assert last["grid"][:2] == ([last["grid"][0], 2] if flat else [(p + 4095) // 4096, (p - 1).bit_length()])
+
+
+@pytest.mark.parametrize("call", ["bcs_allgather_partners", "bcs_census_partners"])
+@pytest.mark.parametrize("p,r0,r1", [(2**31 - 1, 0, 2**31 - 1), (2**30 + 1, 5, 2**30), (2**29 + 1, 0, 2**29 + 1)])
+def test_partner_tables_of_any_length(tmp_path, call, p, r0, r1):
+    log = run(tmp_path, "show(L.%s(%d, %d, %d, T(1), T(2), None))" % (call, p, r0, r1))
+    assert shown(log) == [0]
+    q, done = (p - 1).bit_length(), launches(log, "k_partner_tables")
+    for table in (1, 2):
+        _covers([(e["arg"][4 + table], e["arg"][4]) for e in done], table << 44, (r1 - r0) * q)
+    row = r0
+    for e in done:                                                   # the first process of each piece
+        assert e["arg"][:4] == [p, q, int("census" in call), row] and e["arg"][4] % q == 0
+        assert e["lanes"] * 4 >= e["arg"][4]
+        row += e["arg"][4] // q
+    assert row == r1
