@@ -908,12 +908,15 @@ int bcs_pack_plan_rounds(int32_t p, int32_t n, int64_t rounds, const int32_t *id
         return BCS_EINVAL;
     if ((((uintptr_t)offsets_all) | ((uintptr_t)src_all)) & 7u) return BCS_EINVAL;
     if (rounds == 0) return BCS_OK;
-    PackPlan all;
-    all.offsets = offsets_all;
-    all.src = src_all;
-    all.totals = nullptr;
-    launch(kPackPlan, k_pack_plan_one, dim3((unsigned)rounds), dim3(kBlock), (hipStream_t)stream, (uint32_t)p, (uint32_t)n,
-           idx_table, displs, all);
+    const int64_t step = (int64_t)(kMaxLanes / kBlock);             // rounds a launch: a workgroup each
+    for (int64_t j = 0; j < rounds; j += step) {
+        PackPlan part;
+        part.offsets = offsets_all + j * ((int64_t)p + 1);
+        part.src = src_all + j * (int64_t)p;
+        part.totals = nullptr;
+        launch(kPackPlan, k_pack_plan_one, dim3((unsigned)(rounds - j < step ? rounds - j : step)), dim3(kBlock),
+               (hipStream_t)stream, (uint32_t)p, (uint32_t)n, idx_table + j * (int64_t)p, displs, part);
+    }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? BCS_OK : hip_fail(e);
 }

@@ -81,3 +81,15 @@ def test_partner_tables_of_any_length(tmp_path, call, p, r0, r1):
         assert e["lanes"] * 4 >= e["arg"][4]
         row += e["arg"][4] // q
     assert row == r1
+
+
+def test_plans_of_more_rounds_than_a_launch_has_workgroups(tmp_path):
+    p, rounds = 3, (1 << 25) + 5
+    log = run(tmp_path, "show(L.bcs_pack_plan_rounds(%d, %d, %d, T(1), T(2), T(3), T(4), None))" % (p, rounds, rounds))
+    assert shown(log) == [0]
+    at = 0
+    for e in launches(log, "k_pack_plan_one"):
+        assert e["arg"][2] == (1 << 44) + 4 * p * at and e["arg"][3] == 2 << 44
+        assert e["arg"][4] == (3 << 44) + 8 * (p + 1) * at          # the plan's first member: where the offsets go
+        at += e["grid"][0]
+    assert at == rounds
