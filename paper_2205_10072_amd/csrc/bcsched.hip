@@ -412,8 +412,13 @@ int bcs_sched_batch(int64_t count, const int32_t *p, const int32_t *r, const int
     if (blocks > 0x7fffffffull) return BCS_EINVAL;
     const int rc = ensure_lowtab((hipStream_t)stream);
     if (rc != BCS_OK) return rc;
-    launch(kBatch, k_batch, dim3((unsigned)blocks), dim3(kBatchBlock), (hipStream_t)stream, count, p, r, root,
-                       recv_out, send_out, q_out);
+    const int64_t step = (int64_t)(kMaxLanes / kBatchBlock * kBatchBlock);      // triples a launch: a lane each
+    for (int64_t i = 0; i < count; i += step) {
+        const int64_t part = count - i < step ? count - i : step, row = i * BCS_BATCH_STRIDE;
+        launch(kBatch, k_batch, dim3((unsigned)((part + kBatchBlock - 1) / kBatchBlock)), dim3(kBatchBlock),
+               (hipStream_t)stream, part, p + i, r + i, root + i, recv_out ? recv_out + row : nullptr,
+               send_out ? send_out + row : nullptr, q_out ? q_out + i : nullptr);
+    }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? BCS_OK : hip_fail(e);
 }

@@ -95,3 +95,26 @@ def test_partner_table_of_more_than_2_to_34_entries(bcs):
         assert torch.equal(to[a:a + step].long(), (r[:, None] - dist) % p), a
     del to
     torch.cuda.empty_cache()
+
+
+def test_batch_of_more_than_2_to_32_triples(bcs):
+    """The round counts of 2^32 + 77 triples (the last of them invalid) against the counts of their p."""
+    count = (1 << 32) + 77
+    p = torch.empty(count, dtype=torch.int32, device="cuda")
+    zero = torch.zeros(count, dtype=torch.int32, device="cuda")
+    step = 1 << 26
+    for a in range(0, count, step):
+        i = torch.arange(a, min(count, a + step), device="cuda", dtype=torch.int64)
+        p[a:a + step] = (i * 2654435761 % ((2 << (i % 30)) - 1) + 1).to(torch.int32)
+    p[-1] = 0
+    q = torch.full((count,), -7, dtype=torch.int32, device="cuda")
+    bcs.bcs_sched_batch(p, zero, zero, None, None, q)
+    torch.cuda.synchronize()
+    powers = torch.tensor([1 << k for k in range(32)], device="cuda", dtype=torch.int64)
+    for a in range(0, count, step):
+        want = torch.searchsorted(powers, p[a:a + step].long()).to(torch.int32)       # least k with 2^k >= p
+        if a + step >= count:
+            want[-1] = -1
+        assert torch.equal(q[a:a + step], want), a
+    del p, zero, q
+    torch.cuda.empty_cache()

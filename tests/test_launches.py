@@ -93,3 +93,22 @@ def test_plans_of_more_rounds_than_a_launch_has_workgroups(tmp_path):
         assert e["arg"][4] == (3 << 44) + 8 * (p + 1) * at          # the plan's first member: where the offsets go
         at += e["grid"][0]
     assert at == rounds
+
+
+def test_batches_of_more_than_2_to_32_triples(tmp_path):
+    """Only the round counts asked for: 69 GB of triples and counts, which the card holds."""
+    count = (1 << 32) + 77
+    log = run(tmp_path, "show(L.bcs_sched_batch(%d, T(1), T(2), T(3), None, None, T(4), None))" % count)
+    assert shown(log) == [0]
+    at = 0
+    for e in launches(log, "k_batch"):
+        assert e["arg"][1:4] == [(t << 44) + 4 * at for t in (1, 2, 3)] and e["arg"][4:6] == [0, 0]
+        assert e["arg"][6] == (4 << 44) + 4 * at and 0 < e["arg"][0] <= e["lanes"]
+        at += e["arg"][0]
+    assert at == count
+    log = run(tmp_path, "show(L.bcs_sched_batch(%d, T(1), T(2), T(3), T(5), T(6), None, None))" % count)
+    at = 0
+    for e in launches(log, "k_batch"):
+        assert e["arg"][4:7] == [(5 << 44) + 128 * at, (6 << 44) + 128 * at, 0]
+        at += e["arg"][0]
+    assert at == count
