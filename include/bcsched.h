@@ -253,7 +253,8 @@ int bcs_allgather_tables_ws(int32_t p, int32_t n, int32_t r,
  *   workspace: device, 8-byte aligned, bcs_pack_workspace_bytes(p) bytes.
  * Both calls enqueue four kernels and allocate nothing.
  * BCS_EINVAL: p < 1, n < 1, a NULL array (`packed` may be NULL when capacity /
- * length is 0: then only `offsets` is produced), negative capacity / length.
+ * length is 0: then only `offsets` is produced), capacity / length negative or
+ * above 2^36 - 4096 elements (no card holds them).
  * BCS_ENOMEM: workspace NULL, misaligned or too small. */
 int64_t bcs_pack_workspace_bytes(int32_t p);
 int bcs_pack_round(int32_t p, int32_t n, const int32_t *idx, const int64_t *displs,
@@ -273,7 +274,8 @@ int bcs_unpack_round(int32_t p, int32_t n, const int32_t *idx, const int64_t *di
  * bcs_pack_round_planned / bcs_unpack_round_planned: the payload of one round from its two plan rows
  * (offsets: p+1 entries, src: p entries); arguments otherwise as bcs_pack_round / bcs_unpack_round.
  * All three enqueue one kernel and allocate nothing.
- * BCS_EINVAL: p < 1, n < 1, rounds < 0, a NULL array, plan arrays not 8-byte aligned, negative capacity / length. */
+ * BCS_EINVAL: p < 1, n < 1, rounds < 0, a NULL array, plan arrays not 8-byte aligned,
+ * capacity / length negative or above 2^36 - 4096. */
 int bcs_pack_plan_rounds(int32_t p, int32_t n, int64_t rounds, const int32_t *idx_table, const int64_t *displs,
                          int64_t *offsets_all, int64_t *src_all, void *stream);
 int bcs_pack_round_planned(int32_t p, const int64_t *offsets, const int64_t *src, const int32_t *data,
@@ -342,7 +344,8 @@ const char *bcs_kernel_name(int id);
  * full-rate 32-bit integer vector operations (add, xor, min, subtract) and then
  * stores one word to sink[blocks * 256] (device).  Timed with
  * bcs_timing_begin/end (kernel "k_valu_peak") it gives the integer-ALU rate
- * this GPU reaches in practice.  BCS_EINVAL for a zero count or NULL sink. */
+ * this GPU reaches in practice.  BCS_EINVAL for a zero count, 2^24 blocks
+ * or more, or NULL sink. */
 #define BCS_VALU_PEAK_OPS_PER_ITER 32
 int bcs_valu_peak_launch(uint32_t blocks, uint32_t iters, uint32_t *sink, void *stream);
 

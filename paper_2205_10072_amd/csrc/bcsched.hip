@@ -444,6 +444,15 @@ int bcs_expand(int32_t p, int32_t n, int32_t r0, int32_t r1, const int32_t *recv
         hipError_t e0 = hipGetLastError();
         return e0 == hipSuccess ? BCS_OK : hip_fail(e0);
     }
+    // sixteen entries a lane: from 275 GB a table on, by ranges of rows
+    const uint64_t most = kMaxLanes / kBlock * kExpChunk / R & ~(uint64_t)3;
+    for (uint64_t a = 0; rows > most && a < rows; a += most) {
+        const uint64_t b = rows - a < most ? rows : a + most;
+        const int rc = bcs_expand(p, n, r0 + (int32_t)a, r0 + (int32_t)b, recv ? recv + a * q : nullptr,
+                                  send ? send + a * q : nullptr, recv_blocks ? recv_blocks + a * R : nullptr,
+                                  send_blocks ? send_blocks + a * R : nullptr, stream);
+        if (rc != BCS_OK || b == rows) return rc;
+    }
     // Both tables in one launch: a call of a few thousand ranks is bound by its launches (2 x 7.7 MB: 13.1 us with one for
     // each table, 9.3 us now; 2 x 81 MB 34.7 and 30.2 us).  From some hundred MB on it gives nothing (2 x 509 MB: 165 and
     // 170 us).
@@ -451,7 +460,6 @@ int bcs_expand(int32_t p, int32_t n, int32_t r0, int32_t r1, const int32_t *recv
     const ExpandTables both = {{recv, send}, {recv_blocks, send_blocks}};
     auto aligned = [&](int t) { return (((uintptr_t)both.out[t]) & 15u) == 0 ? 1 : 0; };
     const uint64_t blocks = (ea.total + kExpChunk - 1) / kExpChunk;
-    if (blocks > 0x7fffffffull) return BCS_EINVAL;
     const bool together = recv && send && aligned(0) == aligned(1) && ea.total * sizeof(int32_t) <= kTogetherBytes;
     for (int t = 0; t < (together ? 1 : 2); ++t) {
         if (!both.in[t]) continue;
@@ -880,7 +888,8 @@ int launch_round(int32_t p, int32_t n, const int32_t *idx, const int64_t *displs
     if (rc != BCS_OK || limit == 0) return rc;
     return launch_copy<PACK>(p, limit, offsets, plan.src, data, message, st);
 }
-inline bool copy_size_ok(int64_t limit) { return ((uint64_t)limit + kBlock * 4 - 1) / (kBlock * 4) <= 0x7fffffffull; }
+// a launch of the payload kernel covers 2^36 elements (275 GB), which with their buffers no card holds
+inline bool copy_size_ok(int64_t limit) { return (uint64_t)limit <= kMaxLanes / kBlock * ((uint64_t)kCopyIter * kBlock * 4); }
 }  // namespace
 
 extern "C" {
@@ -943,7 +952,7 @@ int bcs_unpack_round_planned(int32_t p, const int64_t *offsets, const int64_t *s
 }
 
 int bcs_valu_peak_launch(uint32_t blocks, uint32_t iters, uint32_t *sink, void *stream) {
-    if (blocks == 0 || iters == 0 || !sink) return BCS_EINVAL;
+    if (blocks == 0 || blocks > kMaxLanes / kBlock || iters == 0 || !sink) return BCS_EINVAL;
     launch(kValuPeak, k_valu_peak, dim3(blocks), dim3(kBlock), (hipStream_t)stream, iters, 0x2205u, sink);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? BCS_OK : hip_fail(e);

@@ -29,7 +29,7 @@ struct Entry {
 std::mutex g_mutex;
 std::vector<Entry> g_log;
 std::map<const void *, std::string> g_names;
-std::map<std::string, std::string> g_signature;    // a kernel's arguments: '4' or '8' bytes each
+std::map<std::string, std::string> g_signature;    // a kernel's arguments: '4' or '8' bytes, 'E': 32
 uint64_t g_slow_stream = 0;
 int g_slow_us = 0, g_last = 0;
 uintptr_t g_next_pointer = 0x10000000;
@@ -119,7 +119,13 @@ int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t, s
     const std::string &name = g_names[f];
     strncpy(e.name, name.c_str(), sizeof e.name - 1);
     const std::string &sizes = g_signature[name];
-    for (size_t i = 0; i < sizes.size() && i < 12; ++i) memcpy(&e.arg[i], args[i], (size_t)(sizes[i] - '0'));
+    size_t at = 0;
+    for (size_t i = 0; i < sizes.size(); ++i) {
+        const size_t bytes = sizes[i] == 'E' ? 32 : (size_t)(sizes[i] - '0'), words = (bytes + 7) / 8;
+        if (at + words > 12) break;
+        memcpy(&e.arg[at], args[i], bytes);
+        at += words;
+    }
     g_log.push_back(e);
     return 0;
 }

@@ -31,8 +31,9 @@ S.stub_get.argtypes = [i64, ctypes.POINTER(Entry)]
 S.stub_slow.argtypes = [ctypes.c_uint64, ctypes.c_int]
 for name, sizes in (("k_expand_rows", "88888"), ("k_rows_to_bytes", "444488"), ("k_partner_tables", "4444888"),
                     ("k_batch", "8888888"), ("k_pack_plan_one", "44888"), ("k_allgather_tables_flat", "888888"),
-                    ("k_sched", "84444488"), ("k_expand", "88")):
+                    ("k_sched", "84444488")):
     S.stub_signature(name.encode(), sizes.encode())
+S.stub_signature(b"k_expand", b"8E")                     # E: a struct of four addresses
 L.bcs_sched_rooted_ws.argtypes = [i32] * 4 + [P] * 3 + [sz, P]
 L.bcs_sched_expand_ws.argtypes = [i32] * 3 + [P] * 5 + [sz, P]
 L.bcs_sched_expand.argtypes = [i32] * 3 + [P] * 5

@@ -112,3 +112,26 @@ def test_batches_of_more_than_2_to_32_triples(tmp_path):
         assert e["arg"][4:7] == [(5 << 44) + 128 * at, (6 << 44) + 128 * at, 0]
         at += e["arg"][0]
     assert at == count
+
+
+@pytest.mark.parametrize("p,n", [(33, 2**31 - 100), (5000000, 13800), (40, 2**31 - 100)])
+def test_expansion_without_workspace_of_more_lanes_than_a_launch_has(tmp_path, p, n):
+    """Sixteen entries a lane: a table of 275 GB and more."""
+    log = run(tmp_path, "show(L.bcs_expand(%d, %d, 1, %d, T(1), T(2), T(3), T(4), None))" % (p, n, p))
+    assert shown(log) == [0]
+    R, q = n - 1 + (p - 1).bit_length(), (p - 1).bit_length()
+    done = launches(log, "k_expand")                                 # arg: entries, rows of both tables, both block tables
+    for table in (3, 4):
+        mine = [e["arg"] for e in done if e["arg"][3] >> 44 == table]
+        _covers([(a[3], a[0]) for a in mine], table << 44, (p - 1) * R)
+        for a in mine:
+            first = (a[3] - (table << 44)) // (4 * R)
+            assert a[1] == ((table - 2) << 44) + 4 * q * first and a[2] == a[4] == 0
+
+
+@pytest.mark.parametrize("call", ["bcs_pack_round_planned(3, T(1), T(2), T(3), T(4), 1 << 38, None)",
+                                  "bcs_pack_round(3, 4, T(1), T(2), T(3), T(4), 1 << 38, T(5), T(6), 1 << 20, None)",
+                                  "bcs_valu_peak_launch(1 << 24, 1, T(1), None)"])
+def test_sizes_beyond_a_launch_and_the_card_are_refused_before_anything_is_enqueued(tmp_path, call):
+    log = run(tmp_path, "show(L.%s)" % call)
+    assert shown(log) == [-1] and not launches(log)
