@@ -182,7 +182,9 @@ int ensure_lowtab(hipStream_t st) {
 // The per-device scratch of the plain calls.  One allocation serves every plain call on the device, so two of
 // them on different streams must not overlap: when a call comes on another stream than the one before it, that
 // earlier stream's work is made a dependency of the new one (an event recorded there now covers everything
-// the earlier call enqueued).
+// the earlier call enqueued).  A call holds the lock from scratch_get until its last launch is enqueued: an event recorded
+// in between, by another thread's call, would not cover its kernels, and a larger block or bcs_release would free memory
+// that they have yet to use.
 struct Scratch {
     void *ptr = nullptr;
     size_t bytes = 0;
@@ -193,12 +195,12 @@ struct Scratch {
 Scratch g_scratch[kMaxDevices];
 std::mutex g_scratch_mutex;
 
-int scratch_get(size_t bytes, hipStream_t st, void **out) {
+int scratch_get(size_t bytes, hipStream_t st, void **out, std::unique_lock<std::mutex> &held) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(e);
     if (dev < 0 || dev >= kMaxDevices) return BCS_EINVAL;
-    std::lock_guard<std::mutex> lock(g_scratch_mutex);
+    held = std::unique_lock<std::mutex>(g_scratch_mutex);
     Scratch &s = g_scratch[dev];
     if (s.bytes < bytes) {
         if (s.ptr) {
@@ -657,8 +659,9 @@ int bcs_sched_expand(int32_t p, int32_t root, int32_t n, int32_t *recv_out, int3
     }
     const int64_t need = bcs_sched_expand_workspace_bytes(p, n);
     void *ws = nullptr;
+    std::unique_lock<std::mutex> held;             // until the call below has enqueued everything
     if (need > 0) {
-        const int rc = scratch_get((size_t)need, (hipStream_t)stream, &ws);
+        const int rc = scratch_get((size_t)need, (hipStream_t)stream, &ws, held);
         if (rc != BCS_OK) return rc;
     }
     return bcs_sched_expand_ws(p, root, n, recv_out, send_out, recv_blocks, send_blocks, ws, (size_t)need, stream);
@@ -742,8 +745,9 @@ int bcs_allgather_tables(int32_t p, int32_t n, int32_t r, int32_t *pack_idx, int
     if (!pack_idx && !unpack_idx) return BCS_EINVAL;
     const int64_t need = bcs_allgather_workspace_bytes(p);
     void *ws = nullptr;
+    std::unique_lock<std::mutex> held;             // until the call below has enqueued everything
     if (need > 0) {
-        const int rc = scratch_get((size_t)need, (hipStream_t)stream, &ws);
+        const int rc = scratch_get((size_t)need, (hipStream_t)stream, &ws, held);
         if (rc != BCS_OK) return rc;
     }
     return bcs_allgather_tables_ws(p, n, r, pack_idx, unpack_idx, ws, (size_t)need, stream);

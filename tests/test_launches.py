@@ -135,3 +135,57 @@ def test_expansion_without_workspace_of_more_lanes_than_a_launch_has(tmp_path, p
 def test_sizes_beyond_a_launch_and_the_card_are_refused_before_anything_is_enqueued(tmp_path, call):
     log = run(tmp_path, "show(L.%s)" % call)
     assert shown(log) == [-1] and not launches(log)
+
+
+PLAIN = {"bcs_sched_expand": "L.bcs_sched_expand(%s, 0, 300, T(1), T(2), T(3), T(4), %s)",
+         "bcs_allgather_tables": "L.bcs_allgather_tables(%s, 300, 0, T(1), T(2), %s)"}
+
+
+@pytest.mark.parametrize("first", PLAIN)
+@pytest.mark.parametrize("second", list(PLAIN) + ["bcs_release"])
+def test_plain_calls_of_two_threads_do_not_come_between_one_another(tmp_path, first, second):
+    """Plain calls share one allocation.  While one is enqueueing its kernels (each launch takes 50 ms here), another
+    thread calls with more ranks, or releases: the allocation may be freed, and the other stream ordered behind the
+    first, only when the first call's kernels are all enqueued."""
+    other = PLAIN[second] % (8000000, "3 << 20") if second in PLAIN else "L.bcs_release()"
+    log = run(tmp_path, """
+L.bcs_sched_rooted_ws(5, 0, 0, 5, T(1), None, None, 0, None)           # fills the tables
+S.stub_reset()
+S.stub_slow(2 << 20, 50000)
+rcs = [None, None]
+def one(): rcs[0] = %s
+def two(): rcs[1] = %s
+a, b = threading.Thread(target=one), threading.Thread(target=two)
+a.start()
+while not S.stub_count(): time.sleep(0.001)                            # it has its memory
+time.sleep(0.01)
+b.start()
+a.join()
+b.join()
+show(rcs)
+""" % (PLAIN[first] % (1000003, "2 << 20"), other))
+    assert shown(log) == [[0, 0]]
+    last = max(i for i, (kind, e) in enumerate(log) if kind == "launch" and e["stream"] == 2 << 20)
+    assert all(kind in ("launch", "malloc") and e["stream"] in (0, 2 << 20) for kind, e in log[:last])
+    freed = [i for i, (kind, e) in enumerate(log) if kind == "free"]
+    assert len(freed) == 1 and freed[0] > last
+
+
+def test_a_plain_call_on_another_stream_is_ordered_behind_all_of_the_call_before(tmp_path):
+    """The same with the same sizes: no allocation changes hands, the order between the streams is what counts."""
+    log = run(tmp_path, """
+L.bcs_sched_rooted_ws(5, 0, 0, 5, T(1), None, None, 0, None)
+S.stub_reset()
+S.stub_slow(2 << 20, 50000)
+a = threading.Thread(target=lambda: L.bcs_sched_expand(1000003, 0, 300, T(1), T(2), T(3), T(4), 2 << 20))
+b = threading.Thread(target=lambda: L.bcs_sched_expand(1000003, 0, 300, T(5), T(6), T(7), T(8), 3 << 20))
+a.start()
+while not S.stub_count(): time.sleep(0.001)
+time.sleep(0.01)
+b.start()
+a.join()
+b.join()
+""")
+    order = [(kind, e["stream"] >> 20) for kind, e in log if kind in ("launch", "record", "wait")]
+    mine = order.count(("launch", 2))
+    assert mine > 1 and order == [("launch", 2)] * mine + [("record", 2), ("wait", 3)] + [("launch", 3)] * mine
