@@ -195,7 +195,8 @@ int bcs_expand_ws(int32_t p, int32_t n, int32_t r0, int32_t r1,
  * the plain call uses the per-device allocation, the _ws call takes it from the
  * caller (256-byte aligned) and allocates nothing.  With less than that but at
  * least bcs_sched_workspace_bytes(p, 0, p, 1) bytes the _ws call still works
- * (in more and smaller chunks).  p = 1: both block tables get n-1 columns of
+ * (block tables of up to 128 MB without byte rows, longer ones in more and smaller
+ * chunks).  p = 1: both block tables get n-1 columns of
  * BCS_NO_BLOCK.
  * BCS_EINVAL: p < 1, root outside [0, p), n < 1, n > BCS_MAX_N, a required
  * table NULL, a workspace that is not 256-byte aligned.  BCS_ENOMEM: workspace

@@ -640,7 +640,12 @@ int bcs_sched_expand_ws(int32_t p, int32_t root, int32_t n, int32_t *recv_out, i
     const int64_t base = q > 0 ? bcs_sched_workspace_bytes(p, 0, p, 1) : 0;
     if (base > 0 && (!workspace || workspace_bytes < (size_t)base)) return BCS_ENOMEM;
     const bool aligned = ((((uintptr_t)recv_blocks) | ((uintptr_t)send_blocks)) & 15u) == 0;
-    if (q >= (int)kExpMinQ && R >= kExpMinR && aligned)
+    // Tables of up to kTogetherBytes whose byte rows exceed the workspace (the schedules' size alone) would take eight launches
+    // or more in chunks; the schedules and bcs_expand take two.  p = 1000, n = 16 21.6 and 7.8 us; p = 20000, n = 200 31.7 and
+    // 11.1; p = 200003, n = 64 57.5 and 40.5 (34.2 with byte rows of both tables at once)
+    const bool chunks_pay = q > 0 && ((uint64_t)p * R * sizeof(int32_t) > kTogetherBytes ||
+                                      2 * byte_rows_bytes(p, q) <= workspace_bytes);
+    if (q >= (int)kExpMinQ && R >= kExpMinR && aligned && chunks_pay)
         return sched_expand_rows(p, (uint32_t)root, n, q, R, recv_out, send_out, recv_blocks, send_blocks,
                                  (int8_t *)workspace, workspace_bytes, (hipStream_t)stream);
     if (q > 0) {

@@ -189,3 +189,15 @@ b.join()
     order = [(kind, e["stream"] >> 20) for kind, e in log if kind in ("launch", "record", "wait")]
     mine = order.count(("launch", 2))
     assert mine > 1 and order == [("launch", 2)] * mine + [("record", 2), ("wait", 3)] + [("launch", 3)] * mine
+
+
+@pytest.mark.parametrize("p,n", [(1000, 16), (1000, 64), (10001, 40), (20000, 200), (200003, 14), (65537, 400)])
+def test_one_call_with_the_schedules_workspace_alone_takes_two_launches_while_it_is_short(tmp_path, p, n):
+    """Byte rows of both tables do not fit such a workspace; short calls are bound by their launches."""
+    log = run(tmp_path, """
+p, n = %d, %d
+L.bcs_sched_rooted_ws(5, 0, 0, 5, T(1), None, None, 0, None)
+S.stub_reset()
+L.bcs_sched_expand_ws(p, 0, n, T(1), T(2), T(3), T(4), T(5), L.bcs_sched_workspace_bytes(p, 0, p, 1), None)
+""" % (p, n))
+    assert [e["name"] for e in launches(log)] == ["k_sched", "k_expand"]
