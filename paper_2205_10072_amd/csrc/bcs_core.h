@@ -35,15 +35,7 @@
 // All of it is branch-free apart from the wave-uniform test for Alg. 4's rare second range.
 //
 // The kernels build rows from the closed form of bcs_rows.h; the windows here are its definition: Alg. 4 on them fills the
-// table of low rounds.  recv_row_tab, recv_row_tab_upto, round_from_digits and send_row_direct are earlier forms of the
-// rows that no kernel uses any more; the host tests hold them against the oracle, entry by entry.
-//
-// (3) Rounds without a window (round_from_digits, one p per launch).  From level 6 up most rounds of most ranks
-// follow from D(v) alone: the home round gives the baseblock, a round whose digit is set gives the next digit
-// above, a round whose digit is clear gives the round's own index when the value of the lower digits keeps clear
-// of the ends of its range.  The 64 consecutive ranks of a wave share their high digits, so whole waves skip the
-// window in about three of four rounds; a wave with a lane the rule leaves out computes the window as in (2) and
-// every lane keeps whichever result applies to it.
+// table of low rounds, and the tests hold the kernels' rows against it.
 #ifndef BCS_CORE_H
 #define BCS_CORE_H
 
@@ -218,60 +210,38 @@ BCS_HD uint32_t low_table_entry(int shape, int row, int low) {
 template <class Pol>
 BCS_HD uint32_t digits(const Pol &pol, uint32_t y) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    // three vector ops a level: subtract with borrow-out, keep the old value on borrow, shift the borrow
-    // into the (inverted) digit mask.  gfx950 wants two wait states between a vector op that writes
-    // vcc and one that reads it, hence the s_nop.
+    // a level: subtract with borrow-out, keep the old value on borrow, shift the borrow into the (inverted) digit
+    // mask.  gfx950 wants two wait states between a vector op that writes vcc and one that reads it, hence the s_nop.
     uint32_t inv = 0;
-    if constexpr (Pol::kScalarSkips) {
-        // levels 7 and up by the walk; what is left is a rank below skips[7] <= 128, whose digits are read
-        // from the table's last row
-        constexpr int kHigh = Pol::kTopLevel + 1 > kLowLevels ? Pol::kTopLevel + 1 - kLowLevels : 0;
-#pragma unroll
-        for (int k = pol.top(); k >= kLowLevels; --k) {
-            uint32_t t;
-            asm("v_subrev_co_u32 %0, vcc, %3, %1\n\t"
-                "s_nop 1\n\t"
-                "v_cndmask_b32 %1, %0, %1, vcc\n\t"
-                "v_addc_co_u32 %2, vcc, %2, %2, vcc"
-                : "=&v"(t), "+v"(y), "+v"(inv)
-                : "s"(pol.s(k))
-                : "vcc");
-        }
-        const uint32_t lowd = pol.lowtab()[kLowDigitRow * 128 + (int)y];
-        const uint32_t highd = kHigh > 0 ? (~inv & (0xffffffffu >> (32 - (kHigh > 0 ? kHigh : 1)))) : 0u;
-        return (highd << kLowLevels) | lowd;
-    } else {
-        // Per-lane p: the lane's own levels come first, whatever the wave's bound.  Step m handles level
-        // q-1-m, whose skip is ((p-1) >> (m+1)) + 1 (Alg. 1's halving), so g = skip - 1 is one shift a
-        // step and "y - g - 1 with borrow-out" (borrow-in forced to one) subtracts the skip: four vector
-        // ops a level.  Steps past level 0 find y = 0 below a skip of 1 and change nothing; the digits
-        // are moved down to their places at the end.
-        // The walk stops seven levels short of the wave's bound: what is left of y is then below the lane's
-        // skips[7] (or is 0, for a lane with fewer levels than steps), and its digits come from the table.
-        const int steps = pol.top() + 1 > kLowLevels ? pol.top() + 1 - kLowLevels : 0;
-        const uint64_t ones = ~0ull;
-        uint32_t g = pol.pm1;
+    static_assert(!Pol::kScalarSkips, "a p per lane; kernels of one p take their digits from rank_place");
+    // Per-lane p: the lane's own levels come first, whatever the wave's bound.  Step m handles level
+    // q-1-m, whose skip is ((p-1) >> (m+1)) + 1 (Alg. 1's halving), so g = skip - 1 is one shift a
+    // step and "y - g - 1 with borrow-out" (borrow-in forced to one) subtracts the skip: four vector
+    // ops a level.  Steps past level 0 find y = 0 below a skip of 1 and change nothing; the digits
+    // are moved down to their places at the end.
+    // The walk stops seven levels short of the wave's bound: what is left of y is then below the lane's
+    // skips[7] (or is 0, for a lane with fewer levels than steps), and its digits come from the table.
+    const int steps = pol.top() + 1 > kLowLevels ? pol.top() + 1 - kLowLevels : 0;
+    const uint64_t ones = ~0ull;
+    uint32_t g = pol.pm1;
 #pragma unroll 1
-        for (int m = 0; m < steps; ++m) {
-            uint32_t t;
-            asm("v_lshrrev_b32 %3, 1, %3\n\t"
-                "v_subb_co_u32_e64 %0, vcc, %1, %3, %4\n\t"
-                "s_nop 1\n\t"
-                "v_cndmask_b32 %1, %0, %1, vcc\n\t"
-                "v_addc_co_u32 %2, vcc, %2, %2, vcc"
-                : "=&v"(t), "+v"(y), "+v"(inv), "+v"(g)
-                : "s"(ones)
-                : "vcc");
-        }
-        const uint32_t walked = steps > 0 ? (~inv & (0xffffffffu >> (32 - steps))) : 0u;
-        const int left = pol.ql - steps;                   // levels the walk did not reach (at most seven)
-        // A lane whose own q is below the round the wave is in gets an inert skip and with it a y that is no
-        // rank at all: its result is never used, but its table index must stay inside the row.
-        const uint32_t lowd = pol.lowtab()[kLowDigitRow * 128 + (int)(y & 127u)];
-        return (left >= 0 ? walked << left : walked >> -left) | lowd;
+    for (int m = 0; m < steps; ++m) {
+        uint32_t t;
+        asm("v_lshrrev_b32 %3, 1, %3\n\t"
+            "v_subb_co_u32_e64 %0, vcc, %1, %3, %4\n\t"
+            "s_nop 1\n\t"
+            "v_cndmask_b32 %1, %0, %1, vcc\n\t"
+            "v_addc_co_u32 %2, vcc, %2, %2, vcc"
+            : "=&v"(t), "+v"(y), "+v"(inv), "+v"(g)
+            : "s"(ones)
+            : "vcc");
     }
-    const int levels = pol.top() + 1;
-    return levels > 0 ? (~inv & (0xffffffffu >> (32 - levels))) : 0u;
+    const uint32_t walked = steps > 0 ? (~inv & (0xffffffffu >> (32 - steps))) : 0u;
+    const int left = pol.ql - steps;                   // levels the walk did not reach (at most seven)
+    // A lane whose own q is below the round the wave is in gets an inert skip and with it a y that is no
+    // rank at all: its result is never used, but its table index must stay inside the row.
+    const uint32_t lowd = pol.lowtab()[kLowDigitRow * 128 + (int)(y & 127u)];
+    return (left >= 0 ? walked << left : walked >> -left) | lowd;
 #else
     // host build: the same split as on the GPU, levels 7 and up by the walk and the rest from the table's digit
     // row, so that the host tests check that row too
@@ -352,268 +322,31 @@ BCS_HD int recv_round_value(const Pol &pol, uint32_t v, int i, uint32_t s_n, uin
     return is_home ? own : blk - q;
 }
 
-// The same round for callers that keep B themselves: the new block joins B, the entry goes to emit.
-template <class Pol, class DigitsOf, class Emit>
-BCS_HD void recv_round(const Pol &pol, uint32_t v, int i, uint32_t s_n, uint32_t d_lo, uint32_t d_hi, int home,
-                       int own, uint32_t &B, DigitsOf digits_of, Emit emit) {
-    const int q = pol.q();
-    int blk;
-    const int val = recv_round_value(pol, v, i, s_n, d_lo, d_hi, home, own, B, digits_of, blk);
-    const bool active = i < q;
-    // one emit for both kinds of round, so that a wave with lanes of both kinds does not run it twice
-    B |= active ? (1u << (blk & 31)) : 0u;
-    if (active) emit(i, val);
-}
-
-// Rounds that need no window (one p per launch).  With D(v) the digit mask of the rank, low the value of its
-// digits below i and c the number of odd levels below i, round i's entry is
-//   - the rank's baseblock when i is its highest digit (Alg. 4's first branch);
-//   - (next digit j of v above i) - q when digit i is set and low >= c.  The rank w = v - skips[i] - low has the
-//     digits of v above i and nothing below (taking digits out of a greedy sum leaves a greedy sum), so its
-//     baseblock is j; low < skips[i+1] - skips[i] puts it into the round's first window, whose other end has digit
-//     j clear, so j is the window's largest block; and v cannot have come by block j before: its own baseblock
-//     is at or below i, the earlier rounds' windows lie above v - skips[i] except for round i-1's second range,
-//     which reaches fewer than c ranks below it (and w lies low ranks below), and the next rank with baseblock j
-//     is more than 2 skips[i] above w;
-//   - i - q when digit i is clear and low keeps clear of the ends of its range: taking skips[i] from v borrows
-//     from the next digit j above (the lap digit when there is none), which sets digits i..j-1 and lowers the low
-//     part by the number o of odd levels in [i, j) (skips[j] - skips[i] = sum of skips[i..j-1] minus o).  With
-//     low' = low - o >= 0: the rank w = v - skips[i] - low' has lowest digit i and lies in the first window when
-//     low' < skips[i+1] - skips[i]; every other rank of the window shares the digits above i and has a lower
-//     lowest digit; and block i is new: v's baseblock is not i, the earlier rounds reach down to
-//     v - skips[i] - c + 1 only, which misses w when low' >= c, and the next rank with lowest digit i lies
-//     skips[i+1] - (odd levels in [i+1, j)) above w, past v.  The test allows for every o from 0 to the number of
-//     odd levels from i up and keeps twice the margin this needs (it is case (b) of send_row_direct below).
-// Both are also checked against the oracle (every rank of every p the CPU tests run this code on, the full-size
-// configurations on the GPU) and, on the GPU, against rows taken from windows throughout (the batch kernel) for
-// every rank of every p up to 2^22 and for slices of tens of thousands of larger p.  Low rounds rarely agree
-// across the 64 ranks of a wave, so the test starts at round kDigitRoundsFrom.
-constexpr int kDigitRoundsFrom = 6;
-constexpr int kTabAhead = 10;                           // recv_row_tab reads the end points of rounds below this ahead
-
-// dl = D(v) with the lap digit (so that there always is a digit above round i); returns whether the entry could
-// be taken from the digits and leaves it in val, its block (the lap digit's index q for the home round, which
-// Alg. 4's set B never holds) in blk.  Written with masks instead of conditions: one straight run of vector ops.
-template <class Pol>
-BCS_HD bool round_from_digits(const Pol &pol, uint32_t dl, int i, uint32_t s_i, uint32_t low, int home, int own,
-                              int &val, int &blk) {
-    const int q = pol.q();
-    const uint32_t odd = pol.odd_mask();
-    const int mrg = 2 * __builtin_popcount(odd & ((2u << (i & 31)) - 1u)) + 2;
-    const int c1 = mrg + __builtin_popcount(odd >> (i & 31));          // low must exceed this ...
-    const int c2 = (int)s_i - mrg - 1;                                  // ... and stay below this
-    const uint32_t width = c2 > c1 + 1 ? (uint32_t)(c2 - c1 - 1) : 0u;
-    const uint32_t m = 0u - ((dl >> (i & 31)) & 1u);                    // all ones when digit i is set
-    const uint32_t above = (dl >> (i & 31)) >> 1;                       // never 0: the lap digit
-    const uint32_t next = (uint32_t)(__builtin_ctz(above) + i + 1);
-    blk = (int)((m & next) | (~m & (uint32_t)i));
-    val = i == home ? own : blk - q;
-    const uint32_t x = (low - (uint32_t)c1 - 1u) & ~m;
-    const uint32_t cbelow = (uint32_t)__builtin_popcount(odd & ((1u << (i & 31)) - 1u));   // odd levels below i
-    return (m != 0u && low >= cbelow) || x < width;
-}
-
-template <class Pol, class Emit>
-BCS_HD void recv_row_from(const Pol &pol, uint32_t v, uint32_t dv, int last, Emit emit);
-
 template <class Pol, class Emit>
 BCS_HD void recv_row(const Pol &pol, uint32_t v, int last, Emit emit) {
-    recv_row_from(pol, v, digits(pol, v), last, emit);
-}
-
-// recv_row for a caller that already has dv = digits(pol, v)
-template <class Pol, class Emit>
-BCS_HD void recv_row_from(const Pol &pol, uint32_t v, uint32_t dv, int last, Emit emit) {
     const uint32_t p = pol.p();
     const int q = pol.q();
     const uint32_t lap = 1u << (q & 31);
+    const uint32_t dv = digits(pol, v);
     const int home = 31 - BCS_CLZ(dv);                    // -1 for the root
     const int own = dv ? __builtin_ctz(dv) : 0;
     uint32_t B = v ? (1u << own) : 0u;
-    // Digits of v - skips[n] with the lap digit.  When skips[n] is part of v's greedy sum, taking it out leaves the
-    // greedy sum of v - skips[n] (the ranks below it were below skips[n] before and still are), and for n = q the
-    // end point is v itself: no walk.  The high digits of consecutive ranks agree, so whole waves take this path.
-    // (Lanes with unrelated p never agree on it, so the per-lane policy does not ask.)
-    auto end_digits = [&](int n, uint32_t s) -> uint32_t {
+    auto end_digits = [&](uint32_t s) -> uint32_t {       // digits of v - s with the lap digit
         const bool ahead = v >= s;
-        const uint32_t y = ahead ? v - s : v + p - s;
-        if constexpr (Pol::kScalarSkips) {
-            const uint32_t nbit = 1u << (n & 31);
-            const bool direct = (n == q) || (dv & nbit) != 0u;
-            uint32_t d = (n == q) ? dv : ((dv & ~nbit) | lap);
-            if (BCS_WAVE_ANY(!direct)) d = digits(pol, y) | (ahead ? lap : 0u);
-            return d;
-        } else {
-            return digits(pol, y) | (ahead ? lap : 0u);
-        }
+        return digits(pol, ahead ? v - s : v + p - s) | (ahead ? lap : 0u);
     };
-    uint32_t s_i = pol.sdyn(0);
-    uint32_t d_hi = end_digits(0, s_i);
-    bool have_hi = true;                                  // wave-uniform: d_hi holds the digits of v - skips[i]
-    uint32_t low = 0;                                     // value of v's digits below round i
+    uint32_t d_hi = end_digits(pol.sdyn(0));
 #pragma unroll 1
     for (int i = 0; i <= last; ++i) {
-        const uint32_t s_n = pol.sdyn(i + 1);
-        int val = 0, blk = 0;
-        bool easy = false, window = true;
-        if constexpr (Pol::kScalarSkips) {
-            easy = i >= kDigitRoundsFrom && round_from_digits(pol, dv | lap, i, s_i, low, home, own, val, blk);
-            window = BCS_WAVE_ANY(!easy);
-        }
-        if (window) {
-            if (!have_hi) d_hi = end_digits(i, s_i);
-            const uint32_t d_lo = end_digits(i + 1, s_n);
-            int wb;
-            const int w = recv_round_value(pol, v, i, s_n, d_lo, d_hi, home, own, B,
-                                           [&](uint32_t r) { return digits(pol, r); }, wb);
-            val = easy ? val : w;
-            blk = easy ? blk : wb;
-            d_hi = d_lo;
-        }
-        have_hi = window;
+        const uint32_t s_n = pol.sdyn(i + 1), d_lo = end_digits(s_n);
+        int blk;
+        const int val = recv_round_value(pol, v, i, s_n, d_lo, d_hi, home, own, B,
+                                         [&](uint32_t r) { return digits(pol, r); }, blk);
         const bool active = i < q;                        // per-lane q may be below the wave's bound
         B |= active ? (1u << (blk & 31)) : 0u;
         if (active) emit(i, val);
-        low += (0u - ((dv >> (i & 31)) & 1u)) & s_i;
-        s_i = s_n;
-    }
-}
-
-// The same row with every digit mask read from a table of all ranks' masks (dtab[y] = digits of rank y, filled
-// by one walk per rank beforehand): every end point of every window is some rank.  All q rounds, unrolled, so that
-// the skips are the policy's registers and the reads of later rounds can be issued ahead of the rounds that use
-// them.
-template <class Pol, class Emit>
-BCS_HD void recv_row_tab(const Pol &pol, const uint32_t *__restrict__ dtab, uint32_t v, Emit emit) {
-    static_assert(Pol::kScalarSkips, "one p per launch: the inert skips of the per-lane policy are no table indices");
-    constexpr int kQ = Pol::kTopLevel + 1;
-    const uint32_t p = pol.p();
-    const uint32_t lap = 1u << (kQ & 31);
-    // d(n): digits of v - skips[n] with the lap digit.  Those of the low rounds, which always need their windows,
-    // are read ahead; the others only by the few waves that need a window in a high round.
-    constexpr int kAhead = kQ < kTabAhead ? kQ : kTabAhead;
-    auto end_point = [&](int n) -> uint32_t {
-        const uint32_t s = pol.s(n);
-        const bool ahead = v >= s;
-        return dtab[ahead ? v - s : v + p - s] | (ahead ? lap : 0u);
-    };
-    uint32_t d[kAhead + 1];
-#pragma unroll
-    for (int n = 0; n <= kAhead; ++n) d[n] = end_point(n);
-    const uint32_t dv = dtab[v];                         // skips[q] = p: the rank itself, no lap
-    const int home = 31 - BCS_CLZ(dv);
-    const int own = dv ? __builtin_ctz(dv) : 0;
-    uint32_t B = v ? (1u << own) : 0u;
-    uint32_t low = 0;                                    // value of v's digits below round i
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-        int val = 0, blk = 0;
-        const bool easy = i >= kDigitRoundsFrom && round_from_digits(pol, dv | lap, i, pol.s(i), low, home, own, val, blk);
-        if (BCS_WAVE_ANY(!easy)) {
-            const uint32_t d_hi = i <= kAhead ? d[i <= kAhead ? i : 0] : end_point(i);
-            const uint32_t d_lo = i + 1 == kQ ? dv : (i + 1 <= kAhead ? d[i + 1 <= kAhead ? i + 1 : 0] : end_point(i + 1));
-            int wb;
-            const int w = recv_round_value(pol, v, i, pol.s(i + 1), d_lo, d_hi, home, own, B,
-                                           [&](uint32_t r) { return dtab[r]; }, wb);
-            val = easy ? val : w;
-            blk = easy ? blk : wb;
-        }
-        B |= 1u << (blk & 31);
-        emit(i, val);
-        low += (0u - ((dv >> i) & 1u)) & pol.s(i);
-    }
-}
-
-// Rounds 0..last of the same row, for Alg. 5's neighbours (last varies, so the rounds stay a loop): the read for
-// the next round is issued before this round's work.  dv = dtab[v] comes from the caller.
-template <class Pol, class Emit>
-BCS_HD void recv_row_tab_upto(const Pol &pol, const uint32_t *__restrict__ dtab, uint32_t v, uint32_t dv, int last,
-                              Emit emit) {
-    static_assert(Pol::kScalarSkips, "one p per launch: the inert skips of the per-lane policy are no table indices");
-    const uint32_t p = pol.p();
-    const int q = pol.q();
-    const uint32_t lap = 1u << (q & 31);
-    auto end_point = [&](uint32_t s) -> uint32_t {       // digits of v - s with the lap digit, s in [1, p]
-        const bool ahead = v >= s;
-        return dtab[ahead ? v - s : v + p - s] | (ahead ? lap : 0u);
-    };
-    uint32_t d_hi = end_point(pol.sdyn(0));
-    uint32_t s_n = pol.sdyn(1);
-    uint32_t d_lo = end_point(s_n);
-    const int home = 31 - BCS_CLZ(dv);
-    const int own = dv ? __builtin_ctz(dv) : 0;
-    uint32_t B = v ? (1u << own) : 0u;
-#pragma unroll 1
-    for (int i = 0; i <= last; ++i) {
-        const uint32_t s_next = pol.sdyn(i + 2 <= q ? i + 2 : q);
-        const uint32_t d_next = end_point(s_next);
-        recv_round(pol, v, i, s_n, d_lo, d_hi, home, own, B, [&](uint32_t r) { return dtab[r]; }, emit);
         d_hi = d_lo;
-        d_lo = d_next;
-        s_n = s_next;
     }
-}
-
-// Send entries without the to-neighbour's rounds (Alg. 5 costs entry k that neighbour's rounds 0..k).
-// With t = (v + skips[k]) mod p the entry is entry k of t's receive row, and in three cases none of t's rounds
-// are needed:
-//   (a) k is t's home round, which is the case exactly for v < skips[k+1] - skips[k]: the entry is t's
-//       baseblock (Alg. 4's first branch), and D(t) = D(v) with digit k added, so that baseblock is v's, or k
-//       for v = 0;
-//   otherwise, when v has a digit at or above k, let m be the lowest such digit and L the value of v's digits
-//   below k.  The rank with the digits of v from m up and nothing below lies in round k's first window
-//   (v - (skips[k+1] - skips[k]), v], holds baseblock m, and nothing larger lies there; so the entry is m - q
-//   unless t has come by block m in its earlier rounds.  Those rounds' windows reach back to v + 1 only, and past
-//   it, by Alg. 4's second range, by at most the number of odd levels; between v + 1 and t the ranks whose lower
-//   part is empty hold blocks other than m.  So the entry is m - q
-//   (b) when L keeps clear of both ends of its range: 2c + 2 < L < skips[k] - 1 - (2c + 2), c = the number of
-//       odd levels up to k.  The second range of round i of t reaches skips[k] - skips[i+1] + 1 - c_i ranks past
-//       v + 1 at most, so it can touch the holder of m, the rank v - L, only for L < c; at the other end a lower
-//       part within c of skips[k] - 1 runs over the end of its (shortened) copy when the skip is added.  Every
-//       exception found (all entries of every rank of every p <= 40 000; 39 million entries of structured larger
-//       p up to 2^31 with L within 80 of either end, 0.6 million of them exceptions) has L within c - 1 of an end;
-//       the margin is more than twice that;
-//   (c) when the digits of t below k are those of v (adding the skip did not disturb them): no exception in the
-//       same searches.
-// (b) is what round_from_digits argues for receive rounds, read from the sender (digit k of v clear: t has digit k
-// set and the same low part; set: the addition carries, t has digit k clear and the low part L plus the odd levels
-// the carry passes); (c) goes beyond it and is an observation, not a proved statement.  The CPU tests compare this
-// code with Alg. 5 of the oracle entry by entry (every rank of every p <= 1500, of every p <= 40 000 behind the slow
-// marker, and structured large p).  Everything else -- L near an end of its range and low digits disturbed by a
-// carry that met an odd level -- is left to Alg. 5: the return value has bit k set for every entry k < q that was
-// NOT emitted.
-template <class Pol, class DigitsOf, class Emit>
-BCS_HD uint32_t send_row_direct(const Pol &pol, uint32_t v, uint32_t dv, DigitsOf digits_of, Emit emit) {
-    const uint32_t p = pol.p();
-    const int q = pol.q();
-    uint32_t pending = 0;
-    uint32_t low = 0;                                         // value of v's digits below k
-#pragma unroll 1
-    for (int k = 0; k <= pol.top(); ++k) {
-        const bool active = k < q;                            // per-lane q may be below the wave's bound
-        const uint32_t s = active ? pol.sdyn(k) : 0u;
-        const uint32_t kbit = 1u << (k & 31);
-        const uint32_t oddk = (pol.odd_mask() >> (k & 31)) & 1u;
-        const uint32_t above = dv & ~(kbit - 1u);
-        const bool home = active && v + oddk < s;             // v < skips[k+1] - skips[k]
-        const uint32_t mrg = 2u * (uint32_t)__builtin_popcount(pol.odd_mask() & ((kbit << 1) - 1u)) + 2u;
-        const bool mid = low > mrg && low + mrg + 1u < s;
-        bool direct = home || (above != 0u && mid);
-        const bool ask = active && !direct && above != 0u;    // (c) needs the digits of t
-        bool same_low = false;
-        if (BCS_WAVE_ANY(ask)) {
-            uint32_t t = v + s;
-            t = t >= p ? t - p : t;
-            const uint32_t dt = digits_of(t);
-            same_low = ((dv ^ dt) & (kbit - 1u)) == 0u;
-        }
-        direct = direct || (ask && same_low);
-        const int val = home ? (v ? __builtin_ctz(dv | 0x80000000u) : k) : __builtin_ctz(above | 0x80000000u) - q;
-        if (active && direct) emit(k, val);
-        pending |= (active && !direct) ? kbit : 0u;
-        low += (dv & kbit) ? s : 0u;
-    }
-    return pending;
 }
 
 }  // namespace bcs

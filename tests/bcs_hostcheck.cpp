@@ -1,9 +1,10 @@
-// Host build of the per-rank construction in bcs_core.h, one "lane" at a time, so that CPU tests can
+// Host build of the per-rank construction in bcs_core.h and of the earlier forms in bcs_earlier_rows.h, one "lane" at a time, so that CPU tests can
 // compare the code the GPU lanes run with the oracle.  Test support; not part of libbcsched.
 #include <stddef.h>
 #include <stdint.h>
 
 #include "bcs_core.h"
+#include "bcs_earlier_rows.h"
 
 using namespace bcs;
 
@@ -42,7 +43,7 @@ void row_uniform(const SkipTab &t, uint32_t v, int last, int32_t *out) {
     for (int k = 0; k <= Q; ++k) pol.S[k] = t.s[k];
     pol.tab = &t;
     pol.low = low_for((int32_t)t.s[Q]);
-    recv_row(pol, v, last, [&](int i, int val) { out[i] = val; });
+    recv_row_mixed(pol, v, last, [&](int i, int val) { out[i] = val; });
 }
 
 // the same row from a table of all ranks' digit masks, as the kernels for whole rank ranges build it

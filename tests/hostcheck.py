@@ -10,6 +10,7 @@ ROOT = os.path.dirname(HERE)
 SRC = os.path.join(HERE, "bcs_hostcheck.cpp")
 CSRC = os.path.join(ROOT, "paper_2205_10072_amd", "csrc")
 CORE = os.path.join(CSRC, "bcs_core.h")
+EARLIER = os.path.join(HERE, "bcs_earlier_rows.h")
 LIB = os.path.join(HERE, "libbcs_hostcheck.so")
 
 _lib = None
@@ -18,7 +19,7 @@ _lib = None
 def build(lib=LIB, extra=(), force=True):
     """Compiles the host build of the lane code (g++); `extra` adds flags, e.g. sanitizers."""
     stale = (force or not os.path.exists(lib)
-             or os.path.getmtime(lib) < max(os.path.getmtime(SRC), os.path.getmtime(CORE)))
+             or os.path.getmtime(lib) < max(os.path.getmtime(f) for f in (SRC, CORE, EARLIER)))
     if stale:
         subprocess.run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wno-unknown-pragmas", "-I", CSRC]
                        + list(extra) + ["-o", lib, SRC], check=True)
