@@ -1,4 +1,4 @@
-// Host build of the closed-form rows in bcs_rows.h, for the CPU tests.  Test support; not part of libbcsched.
+// Host build of the closed-form rows in bcs_rows.h and of their definition by windows, for the CPU tests.  Test support; not part of libbcsched.
 #include <stddef.h>
 #include <stdint.h>
 #include <vector>
@@ -33,32 +33,33 @@ PerLane per_lane(uint32_t p, int wave_q) {
     return pol;
 }
 
+LowRow read(uint32_t e) { return g_rows.at(e); }          // throws where a kernel would read past the table
+
+// Receive and send rows the way the kernels make them.  Returns false where the low send entries, which come from v's own
+// block and the next one, differ from those of the to-neighbours' own rows.
 template <class Pol>
-void rows(const Pol &pol, uint32_t v, int32_t *recv, int32_t *send) {
+bool rows(const Pol &pol, uint32_t v, int32_t *recv, int32_t *send) {
     const uint32_t q = (uint32_t)pol.q(), base = row_base(pol);
     const RankPlace pl = rank_place(pol, v);
-    const LowRow w = g_rows[base + (q >= 7 ? pl.ctx * 128u : 0u) + pl.low];
+    const LowRow w = read(base + pl.ctx * 128u + pl.low);
     const LowRow b = row_bytes(w, pl.ctx, pl.J, q);
     auto byte = [](const LowRow &x, uint32_t k) { return (int32_t)(int8_t)((k < 4 ? x.lo >> (8 * k) : x.hi >> (8 * k - 32)) & 0xffu); };
-    int32_t across[7];                                       // the batch kernel's way to the low send entries
-    send_low_entries(pol, pl, base, [&](uint32_t e) { return g_rows[e]; }, [&](int k, int32_t e) { across[k] = e; });
-    for (uint32_t k = 0; k < q && k < 7; ++k) {
-        recv[k] = byte(b, k);
-        if (!Pol::kScalarSkips) {
-            send[k] = across[k];
-            continue;
-        }
+    bool same = true;
+    for (uint32_t k = 0; k < q && k < (uint32_t)kLowLevels; ++k) recv[k] = byte(b, k);
+    send_low_entries(pol, pl, base, read, [&](int k, int32_t e) { if (k < (int)q) send[k] = e; });
+    for (uint32_t k = 0; k < q && k < (uint32_t)kLowLevels; ++k) {
         const uint32_t t = (uint32_t)(((uint64_t)v + pol.s((int)k)) % pol.p());
         const RankPlace pt = rank_place(pol, t);
-        send[k] = byte(row_bytes(g_rows[base + (q >= 7 ? pt.ctx * 128u : 0u) + pt.low], pt.ctx, pt.J, q), k);
+        same &= send[k] == byte(row_bytes(read(base + pt.ctx * 128u + pt.low), pt.ctx, pt.J, q), k);
     }
     high_entries(pol, pl, place_own(pl, w), [&](int k, int32_t e) { recv[k] = e; }, [&](int k, int32_t e) { send[k] = e; });
     recv_fix(pol, pl, w, [&](int k, int32_t e) { recv[k] = e; });
-    send_fix(pol, v, pl, base, [&](uint32_t e) { return g_rows[e]; }, [&](int k, int32_t e) { send[k] = e; });
+    send_fix(pol, v, pl, base, read, [&](int k, int32_t e) { send[k] = e; });
+    return same;
 }
 
 template <int Q>
-void uniform_rows(uint32_t p, uint32_t v, int32_t *recv, int32_t *send) {
+bool uniform_rows(uint32_t p, uint32_t v, int32_t *recv, int32_t *send) {
     SkipTab t;
     for (int k = 0; k <= Q; ++k) t.s[k] = ((p - 1u) >> (Q - k)) + 1u;
     t.odd = odd_levels(p, Q);
@@ -66,15 +67,15 @@ void uniform_rows(uint32_t p, uint32_t v, int32_t *recv, int32_t *send) {
     for (int k = 0; k <= Q; ++k) pol.S[k] = t.s[k];
     pol.tab = &t;
     pol.low = g_low.data() + (size_t)low_shape(p, Q) * kLowShapeBytes;
-    rows(pol, v, recv, send);
+    return rows(pol, v, recv, send);
 }
 
 template <int Q>
-void uniform_for(int q, uint32_t p, uint32_t v, int32_t *recv, int32_t *send) {
+bool uniform_for(int q, uint32_t p, uint32_t v, int32_t *recv, int32_t *send) {
     if constexpr (Q > 0) {
-        if (q == Q) uniform_rows<Q>(p, v, recv, send);
-        else uniform_for<Q - 1>(q, p, v, recv, send);
+        return q == Q ? uniform_rows<Q>(p, v, recv, send) : uniform_for<Q - 1>(q, p, v, recv, send);
     }
+    return false;
 }
 }  // namespace
 
@@ -84,8 +85,26 @@ extern "C" int rc_rows(int32_t p, const int32_t *v, int64_t count, int wave_q, i
     if (p < 2) return -1;
     ready();
     for (int64_t i = 0; i < count; ++i) {
-        if (wave_q) rows(per_lane((uint32_t)p, wave_q), (uint32_t)v[i], recv + i * 32, send + i * 32);
-        else uniform_for<kMaxQ>(ceil_log2((uint32_t)p), (uint32_t)p, (uint32_t)v[i], recv + i * 32, send + i * 32);
+        const bool same = wave_q ? rows(per_lane((uint32_t)p, wave_q), (uint32_t)v[i], recv + i * 32, send + i * 32)
+                                 : uniform_for<kMaxQ>(ceil_log2((uint32_t)p), (uint32_t)p, (uint32_t)v[i], recv + i * 32,
+                                                      send + i * 32);
+        if (!same) return 1;
+    }
+    return 0;
+}
+
+// the same rows by their definition: every receive round from its windows (Alg. 4), every send entry from the receive row
+// of the to-neighbour (Alg. 5)
+extern "C" int rc_windows(int32_t p, const int32_t *v, int64_t count, int32_t *recv, int32_t *send) {
+    if (p < 2) return -1;
+    ready();
+    const PerLane pol = per_lane((uint32_t)p, 0);
+    for (int64_t i = 0; i < count; ++i) {
+        recv_row(pol, (uint32_t)v[i], pol.ql - 1, [&](int k, int e) { recv[i * 32 + k] = e; });
+        for (int k = 0; k < pol.ql; ++k) {
+            const uint32_t t = (uint32_t)(((uint64_t)(uint32_t)v[i] + pol.s(k)) % (uint32_t)p);
+            recv_row(pol, t, k, [&](int j, int e) { if (j == k) send[i * 32 + k] = e; });
+        }
     }
     return 0;
 }

@@ -35,11 +35,29 @@ int hc_recv_rows_all(int32_t p, int32_t *out);
 int hc_recv_rows_all_tab(int32_t p, uint32_t *dtab, int32_t *out);
 int hc_recv_row_tab(int32_t p, const uint32_t *dtab, int32_t v, int last, int32_t *out);
 uint32_t hc_range_blocks(int32_t p, uint32_t a, uint32_t b);
+int rc_rows(int32_t p, const int32_t *v, int64_t count, int wave_q, int32_t *recv, int32_t *send);
 }
 
 static int fail(const char *what, long a, long b) {
     fprintf(stderr, "sanitize_driver: mismatch in %s at (%ld, %ld)\n", what, a, b);
     return 1;
+}
+
+// closed-form rows of the ranks first, first + step, ... against the oracle's (rows of q entries)
+static int closed_form(int32_t p, const int32_t *recv, const int32_t *send, int32_t step) {
+    const int q = orc_q(p);
+    std::vector<int32_t> v, r, s;
+    for (int64_t i = 0; i < p; i += step) v.push_back((int32_t)i);
+    r.resize(v.size() * 32);
+    s.resize(v.size() * 32);
+    for (int wave_q : {0, q, 31}) {
+        if (rc_rows(p, v.data(), (int64_t)v.size(), wave_q, r.data(), s.data())) return fail("rc_rows", p, wave_q);
+        for (size_t i = 0; i < v.size(); ++i)
+            if (memcmp(&r[i * 32], recv + (size_t)v[i] * q, sizeof(int32_t) * q) ||
+                memcmp(&s[i * 32], send + (size_t)v[i] * q, sizeof(int32_t) * q))
+                return fail("closed-form row", p, v[i]);
+    }
+    return 0;
 }
 
 static int one_p(int32_t p) {
@@ -48,6 +66,7 @@ static int one_p(int32_t p) {
     std::vector<uint32_t> dtab(p);
     if (orc_sched_range(p, 0, 0, p, recv.data(), send.data(), 1)) return fail("orc_sched_range", p, 0);
     if (p < 2) return 0;
+    if (closed_form(p, recv.data(), send.data(), p > 5000 ? 37 : 1)) return 1;
     orc_baseblocks_linear(p, bb.data());
     if (hc_recv_rows_all(p, got.data()) || memcmp(got.data(), recv.data(), sizeof(int32_t) * p * q)) return fail("hc_recv_rows_all", p, 0);
     if (hc_recv_rows_all_tab(p, dtab.data(), got.data()) || memcmp(got.data(), recv.data(), sizeof(int32_t) * p * q))
@@ -109,6 +128,12 @@ int main(int argc, char **argv) {
             if (orc_recvsched(p, v, q - 1, 0, want)) return fail("orc_recvsched", p, v);
             if (hc_recv_row(p, v, q - 1, row) || memcmp(row, want, sizeof(int32_t) * q)) return fail("uniform row, large p", p, v);
             if (hc_recv_row_perlane(p, v, 30, 31, row) || memcmp(row, want, sizeof(int32_t) * q)) return fail("perlane row, large p", p, v);
+            int32_t swant[33], row32[32], srow32[32];
+            if (orc_sendsched(p, v, swant)) return fail("orc_sendsched", p, v);
+            for (int wave_q : {0, 31})
+                if (rc_rows(p, &v, 1, wave_q, row32, srow32) || memcmp(row32, want, sizeof(int32_t) * q) ||
+                    memcmp(srow32, swant, sizeof(int32_t) * q))
+                    return fail("closed-form row, large p", p, v);
         }
     }
     {

@@ -1,5 +1,6 @@
-"""CPU tests of the closed-form rows (csrc/bcs_rows.h) against the oracle: every rank of small p, and the ends of
-blocks of large p (where the exceptions of the closed form lie)."""
+"""CPU tests of the closed-form rows (csrc/bcs_rows.h), made as the kernels make them, against the oracle and against their
+definition by windows (csrc/bcs_core.h): every rank of small p, and the ends of blocks of large p (where the exceptions of
+the closed form lie)."""
 import ctypes
 import os
 import subprocess
@@ -21,12 +22,16 @@ def rows(tmp_path_factory):
     L = ctypes.CDLL(lib)
     i32p = ctypes.POINTER(ctypes.c_int32)
     L.rc_rows.argtypes = [ctypes.c_int32, i32p, ctypes.c_int64, ctypes.c_int, i32p, i32p]
+    L.rc_windows.argtypes = [ctypes.c_int32, i32p, ctypes.c_int64, i32p, i32p]
 
     def call(p, ranks, wave_q):
         v = np.ascontiguousarray(ranks, dtype=np.int32)
         out = np.full((2, len(v), 32), 12345, dtype=np.int32)
         ptr = [a.ctypes.data_as(i32p) for a in (v, out[0], out[1])]
-        assert L.rc_rows(p, ptr[0], len(v), wave_q, ptr[1], ptr[2]) == 0
+        if wave_q == "windows":
+            assert L.rc_windows(p, ptr[0], len(v), ptr[1], ptr[2]) == 0
+        else:
+            assert L.rc_rows(p, ptr[0], len(v), wave_q, ptr[1], ptr[2]) == 0
         q = (p - 1).bit_length()
         assert (out[:, :, q:] == 12345).all()
         return out[0, :, :q], out[1, :, :q]
@@ -69,3 +74,31 @@ def test_rows_at_the_ends_of_blocks(rows, q):
                 got_r, got_s = rows(p, np.arange(r0, r0 + 72), wave_q)
                 assert np.array_equal(got_r, recv), (p, r0, wave_q)
                 assert np.array_equal(got_s, send), (p, r0, wave_q)
+
+
+def _p_of(rng, q):
+    """p of q bits: random, or with few, many or all levels odd above the lowest six bits."""
+    kind = int(rng.integers(0, 4))
+    if kind == 0:
+        return int(rng.integers((1 << (q - 1)) + 1, min(1 << q, 2**31 - 1) + 1))
+    odd = [0.05, 0.95, 1.0][kind - 1]
+    bits = "".join("0" if rng.random() < odd else "1" for _ in range(q - 7))
+    return min(2**31 - 1, (1 << (q - 1) | int(bits + format(int(rng.integers(0, 64)), "06b"), 2)) + 1)
+
+
+@pytest.mark.parametrize("q", range(2, 32))
+def test_rows_against_windows(rows, q):
+    """The two constructions share the table of the low levels and nothing else.  Ranks at random, at the ends of the ring and
+    within 150 of sums of skips, on both sides."""
+    rng = np.random.default_rng(100 + q)
+    for _ in range(25):
+        p = _p_of(rng, q) if q > 7 else int(rng.integers((1 << (q - 1)) + 1, (1 << q) + 1))
+        skips = [((p - 1) >> (q - k)) + 1 for k in range(q + 1)]
+        centres = [0, p] + [sum(s for s in skips[:q] if rng.random() < 0.4) for _ in range(10)]
+        ranks = [int(x) for x in rng.integers(0, p, 40)]
+        for c in centres:
+            ranks += [int((c + d) % p) for d in rng.integers(-150, 151, 30)]
+        want = rows(p, ranks, "windows")
+        for wave_q in (0, q, 31):
+            got = rows(p, ranks, wave_q)
+            assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), (p, wave_q)
