@@ -606,10 +606,11 @@ def test_send_rule_against_the_look_up_for_every_rank_of_large_p(bcs):
 
 
 def test_rows_from_digits_against_rows_from_windows(bcs):
-    """The one-p kernels take most rounds above level 5 from the rank's own digits; the batch kernel takes every
-    round from its windows.  Every rank of 40 values of p of 8 to 27 bits (random, and with chosen odd levels),
-    each under a random root: the table by bcs_sched_rooted (all ranks: digit masks from the table) and a ragged
-    part of it (digit walks) against bcs_sched_batch on the same ranks."""
+    """Every rank of 40 values of p of 8 to 27 bits (random, and with chosen odd levels), each under a random root: the
+    rows that bcs_sched_rooted makes from the ranks' own digits, all ranks at once and a ragged part of them, and the
+    rows of bcs_sched_batch, against receive rows from windows throughout (Alg. 4) and send rows by look-up in them
+    (of the part: by Alg. 5), which bcs_windows.hip makes for itself."""
+    import windows
     from test_host_logic import _p_from_bits
     rng = np.random.default_rng(20220511)
     ps = [(1 << 20) + 1, (1 << 23) + 1, (1 << 24) + 12345, (1 << 26) - 3, (1 << 27) - 1]
@@ -621,29 +622,37 @@ def test_rows_from_digits_against_rows_from_windows(bcs):
             pr = rng.choice([0.1, 0.5, 0.9, 1.0])
             ps.append(_p_from_bits(q, int(rng.integers(0, 64)), [k for k in range(7, q) if rng.random() < pr]))
     CH = 1 << 24
-    brecv = torch.empty((CH, bcs.BATCH_STRIDE), dtype=torch.int32, device="cuda")
+    brecv, bsend = dev_tables(CH, bcs.BATCH_STRIDE)
     qout = torch.empty(CH, dtype=torch.int32, device="cuda")
     for p in ps:
         q = bcs.bcs_q(p)
         root = int(rng.integers(0, p))
-        full = torch.empty((p, q), dtype=torch.int32, device="cuda")
-        bcs.bcs_sched_rooted(p, root, 0, p, full, None)
+        full, sfull = (torch.empty((p, q), dtype=torch.int32, device="cuda") for _ in range(2))
+        bcs.bcs_sched_rooted(p, root, 0, p, full, sfull)
+        windows.check(p, root, 0, p, full, sfull)
         a = int(rng.integers(0, p))
         b = min(p, a + int(rng.integers(1, 1 << 20)))
-        part = torch.empty((b - a, q), dtype=torch.int32, device="cuda")
-        bcs.bcs_sched_rooted(p, root, a, b, part, None)
-        torch.cuda.synchronize()
-        assert torch.equal(full[a:b], part), (p, root, a, b)
+        part, spart = (torch.empty((b - a, q), dtype=torch.int32, device="cuda") for _ in range(2))
+        bcs.bcs_sched_rooted(p, root, a, b, part, spart)
+        windows.check(p, root, a, b, part, spart)
+        assert windows.differences() == 0, (p, root, a, b)
         for c0 in range(0, p, CH):
             n = min(p, c0 + CH) - c0
             pp = torch.full((n,), p, dtype=torch.int32, device="cuda")
             rr = torch.arange(c0, c0 + n, dtype=torch.int32, device="cuda")
             ro = torch.full((n,), root, dtype=torch.int32, device="cuda")
-            bcs.bcs_sched_batch(pp, rr, ro, brecv[:n], None, qout[:n])
+            bcs.bcs_sched_batch(pp, rr, ro, brecv[:n], bsend[:n], qout[:n])
             torch.cuda.synchronize()
             assert torch.equal(full[c0:c0 + n], brecv[:n, :q]), (p, root, c0)
-        del full, part
-    bcs.bcs_release()
+            assert torch.equal(sfull[c0:c0 + n], bsend[:n, :q]), (p, root, c0)
+        del full, sfull, part, spart
+    # the check itself: one entry changed is one difference
+    recv, send = dev_tables(1000, 10)
+    bcs.bcs_sched(1000, 0, 1000, recv, send)
+    send[77, 3] += 1
+    windows.check(1000, 0, 0, 1000, recv, send)
+    windows.check(1000, 0, 50, 100, None, send[50:100].contiguous())
+    assert windows.differences() == 2
     torch.cuda.empty_cache()
 
 
