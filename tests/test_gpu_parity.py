@@ -120,7 +120,7 @@ def test_sub_ranges_roots_and_single_tables(bcs, oracle):
         bcs.bcs_sched_rooted_ws(p, root, 0, p, recv_d, send_d, ws)
         torch.cuda.synchronize()
         assert np.array_equal(recv_d.cpu().numpy(), orecv) and np.array_equal(send_d.cpu().numpy(), osend)
-        # partial ranges: send rows are recomputed (Alg. 5) and must equal the looked-up ones
+        # partial ranges
         for r0, r1 in [(0, min(p, 1)), (p - 1, p), (p // 3, min(p, p // 3 + 300)), (max(0, p - 259), p), (1, p)]:
             if p > 70000 and r1 - r0 > 1000:
                 continue
@@ -135,32 +135,32 @@ def test_sub_ranges_roots_and_single_tables(bcs, oracle):
     assert bool((recv == 777).all()) and bool((send == 777).all())
 
 
-def test_receive_rows_with_and_without_the_digit_table(bcs, oracle):
-    """Receive rows of all ranks: by digit walks (no workspace) and from the table of all ranks' digit masks (a
-    workspace of a word a rank), at a small p and at two large ones.  The two agree everywhere; sampled rows are
-    the oracle's."""
+def test_receive_rows_with_and_without_a_workspace(bcs, oracle):
+    """Receive rows alone need no workspace and leave alone one that is given: the same rows, those of the definition by
+    windows, with sampled ones the oracle's, and the workspace as it was."""
+    import windows
     rng = np.random.default_rng(24)
     for p, root in [(70001, 69), (1 << 24, 5), ((1 << 25) + 12345, 1 << 25)]:
         q = bcs.bcs_q(p)
-        walked = torch.full((p, q), 777, dtype=torch.int32, device="cuda")
-        tabled = torch.full((p, q), 778, dtype=torch.int32, device="cuda")
-        ws = torch.empty(4 * p + 256, dtype=torch.uint8, device="cuda")
-        bcs.bcs_sched_rooted_ws(p, root, 0, p, walked, None, None)
-        bcs.bcs_sched_rooted_ws(p, root, 0, p, tabled, None, ws)
-        torch.cuda.synchronize()
-        assert torch.equal(walked, tabled), p
+        bare = torch.full((p, q), 777, dtype=torch.int32, device="cuda")
+        given = torch.full((p, q), 778, dtype=torch.int32, device="cuda")
+        ws = torch.full((4 * p + 256,), 99, dtype=torch.uint8, device="cuda")
+        bcs.bcs_sched_rooted_ws(p, root, 0, p, bare, None, None)
+        bcs.bcs_sched_rooted_ws(p, root, 0, p, given, None, ws)
+        windows.check(p, root, 0, p, given)
+        assert windows.differences() == 0, p
+        assert torch.equal(bare, given) and bool((ws == 99).all()), p
         for r in [0, 1, root, p - 1, p // 2] + [int(x) for x in rng.integers(0, p, 150)]:
             want = oracle.recvsched(p, (r - root) % p)
-            assert np.array_equal(tabled[r].cpu().numpy(), want), (p, r)
-        del walked, tabled, ws
+            assert np.array_equal(given[r].cpu().numpy(), want), (p, r)
+        del bare, given, ws
 
 
 def test_sched_random_ranges(bcs, oracle):
     """Seeded random p, roots, rank ranges (whole, ragged, short) and choices of tables, through the plain call and the
-    one with a caller workspace: every kernel variant behind bcs_sched_rooted (digit walks, digit table, look-up,
-    recomputation) gets its share."""
+    one with a caller workspace of the stated size or more."""
     rng = np.random.default_rng(2205_10072)
-    tabled_parts = 0
+    parts_with_workspace = 0
     for case in range(400):
         bits = int(rng.integers(1, 18))
         p = int(rng.integers(max(2, 1 << (bits - 1)), (1 << bits) + 2))
@@ -184,7 +184,7 @@ def test_sched_random_ranges(bcs, oracle):
         recv = torch.full((r1 - r0, q), 777, dtype=torch.int32, device="cuda") if want & 1 else None
         send = torch.full((r1 - r0, q), 778, dtype=torch.int32, device="cuda") if want & 2 else None
         need = bcs.bcs_sched_workspace_bytes(p, r0, r1, 1 if send is not None else 0)
-        tabled_parts += need > 0 and not (r0 == 0 and r1 == p)
+        parts_with_workspace += need > 0 and not (r0 == 0 and r1 == p)
         if rng.integers(0, 2):
             ws = torch.empty(need + (4 * p + 512) * int(rng.integers(0, 2)), dtype=torch.uint8, device="cuda")
             bcs.bcs_sched_rooted_ws(p, root, r0, r1, recv, send, ws if ws.numel() else None)
@@ -196,12 +196,12 @@ def test_sched_random_ranges(bcs, oracle):
             assert np.array_equal(recv.cpu().numpy(), orecv), ("recv", p, root, r0, r1, want)
         if send is not None:
             assert np.array_equal(send.cpu().numpy(), osend), ("send", p, root, r0, r1, want)
-    assert tabled_parts > 20
+    assert parts_with_workspace > 20
 
 
 def test_every_q_from_1_to_31(bcs, oracle):
     """One kernel instance exists per q: each is run on two p of that bit length (one random, one 2^q or 2^(q-1)+1),
-    over all ranks when that is cheap and over ragged chunks otherwise, with both ways of making send rows."""
+    over all ranks when that is cheap and over ragged chunks as well."""
     rng = np.random.default_rng(31)
     for q in range(1, 32):
         lo, hi = (1 << (q - 1)) + 1, min(1 << q, 2**31 - 1)
@@ -235,7 +235,7 @@ def test_largest_p_sampled_chunks(bcs, oracle):
 
 
 def test_largest_p_all_ranks_in_full(bcs, oracle):
-    """Config 3 in the all-ranks launch configuration (send by look-up), compared in full: every receive row
+    """Config 3 in the all-ranks launch configuration, compared in full: every receive row
     against the oracle, chunk by chunk, and every send entry against its definition
     send[r][k] = recv[(r + skips[k]) mod p][k] (Alg. 9's look-up; Alg. 5) on the verified receive table."""
     p = 134217727
@@ -314,11 +314,14 @@ def test_expand_p65537_n4096(bcs, oracle):
 
 
 def test_expand_with_workspace(bcs, oracle):
-    """bcs_expand_ws: the caller's tables rewritten as byte rows in the workspace, then expanded from there; the
-    same results as bcs_expand whatever path the sizes take."""
+    """bcs_expand_ws: from 256 rounds and 128 MB a table on the caller's tables are rewritten as byte rows in the workspace
+    and expanded from there, else the call is bcs_expand; the same results whatever path the sizes take, and the path
+    they are meant to take."""
     for p, n, r0, r1 in [(65537, 4096, 0, 65537), (65537, 300, 1000, 50001), (5, 700, 0, 5), (1000, 247, 0, 1000),
                          (1000, 246, 3, 999), (33, 251, 0, 33), (4097, 521, 4000, 4097), (1048577, 256, 0, 1048577),
-                         (9, 3, 0, 9), (2, 400, 0, 2), ((1 << 22) + 1, 300, 5, (1 << 22) - 2)]:   # the last: three chunks
+                         (9, 3, 0, 9), (2, 400, 0, 2), ((1 << 22) + 1, 300, 5, (1 << 22) - 2),    # the last: three chunks
+                         (5, 7000000, 0, 5), (33, 1200000, 3, 33), (1000, 40000, 3, 999), (4097, 9000, 1, 4097),
+                         (1000, 33545, 0, 1000), (1000, 33546, 0, 1000)]:     # at 128 MB a table and 4 kB above it
         q, R = bcs.bcs_q(p), bcs.bcs_rounds(p, n)
         orecv, osend = oracle.sched_range(p, r0=r0, r1=r1, threads=16)
         recv, send = torch.from_numpy(orecv).cuda(), torch.from_numpy(osend).cuda()
@@ -328,14 +331,45 @@ def test_expand_with_workspace(bcs, oracle):
         for ws_bytes, both in [(need, True), (need, False), (max(0, need - 16), True)]:
             ws = torch.empty(max(16, ws_bytes), dtype=torch.uint8, device="cuda")[:ws_bytes]
             rb, sb = dev_tables(r1 - r0, R, fill=4242)
+            bcs.bcs_timing_begin()
             bcs.bcs_expand_ws(p, n, r0, r1, recv, send if both else None, rb, sb if both else None, ws)
             torch.cuda.synchronize()
+            by_rows = 0 < need <= ws_bytes and (r1 - r0) * R * 4 > 128 << 20
+            assert ("k_rows_to_bytes" in bcs.bcs_timing_end()) == by_rows, (p, n, r0, r1, ws_bytes, both)
             assert np.array_equal(rb.cpu().numpy(), want_r), (p, n, r0, r1, ws_bytes, both)
             if both:
                 assert np.array_equal(sb.cpu().numpy(), want_s), (p, n, r0, r1, ws_bytes)
             else:
                 assert bool((sb == 4242).all())
             del rb, sb
+
+
+def test_expansion_from_byte_rows_for_every_short_row(bcs, oracle):
+    """The conversion's stride and reciprocal for q = 3..16, and the expansion's shift and slots: ragged ranges of rows above
+    128 MB a table, against bcs_expand in full and sampled rows of the oracle."""
+    rng = np.random.default_rng(316)
+    for q in range(3, 17):
+        p = int(rng.integers((1 << (q - 1)) + 1, (1 << q) + 1))
+        r0 = int(rng.integers(0, max(1, p // 4)))
+        rows = p - r0 - int(rng.integers(0, max(1, p // 4)))
+        n = (128 << 20) // (4 * rows) + int(rng.integers(1, 5000))
+        R, root = bcs.bcs_rounds(p, n), int(rng.integers(0, p))
+        recv, send = dev_tables(rows, q)
+        bcs.bcs_sched_rooted(p, root, r0, r0 + rows, recv, send)
+        ws = torch.empty(bcs.bcs_expand_workspace_bytes(p, n, r0, r0 + rows), dtype=torch.uint8, device="cuda")
+        got, want = dev_tables(rows, R, fill=4242), dev_tables(rows, R, fill=-4242)
+        bcs.bcs_expand(p, n, r0, r0 + rows, recv, send, *want)
+        bcs.bcs_timing_begin()
+        bcs.bcs_expand_ws(p, n, r0, r0 + rows, recv, send, *got, ws)
+        torch.cuda.synchronize()
+        assert bcs.bcs_timing_end()["k_rows_to_bytes"][1] == 2, (p, n)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), (p, n, r0, rows)
+        at = [0, rows - 1, int(rng.integers(0, rows))]
+        osched = oracle.sched_range(p, root=root, r0=r0, r1=r0 + rows)
+        for t in range(2):
+            assert np.array_equal(got[t][at].cpu().numpy(), oracle.expand(p, n, osched[t][at])), (p, n, t)
+        del got, want
+    torch.cuda.empty_cache()
 
 
 def test_expand_small_and_ragged(bcs, oracle):
@@ -390,7 +424,7 @@ def test_tables_of_more_than_2_to_32_entries(bcs, oracle):
         _check_blocks_on_device(p, n, recv, rb, oracle, orecv, seed=p)
         del recv, rb, orecv
         torch.cuda.empty_cache()
-    p, n, root = (1 << 25) + 1, 103, 31415926                          # fused kernels, R = 128
+    p, n, root = (1 << 25) + 1, 103, 31415926                          # byte rows in chunks of ranks, R = 128
     q, R = bcs.bcs_q(p), bcs.bcs_rounds(p, n)
     assert R == 128 and p * R > 1 << 32
     recv, send = dev_tables(p, q)
@@ -466,11 +500,11 @@ def test_irregular_batch(bcs, oracle):
 
 
 def test_batch_send_rows_where_the_direct_rule_is_at_its_limits(bcs, oracle):
-    """Send rows of the batch kernel (entries taken from the rank's own digits where that is exact, Alg. 5 otherwise)
-    on triples built to sit at the rule's limits: p with chosen odd levels for q up to 31, ranks whose additions
-    r + skips[k] carry through odd levels, with lower parts empty, largest possible and on both sides of the rule's
-    margin; every entry against Alg. 5 of the oracle.  A second call takes the same ranks as a range of one p
-    (the kernel for parts of the ranks uses the same rule)."""
+    """Send rows of the batch kernel on triples built to sit where entries do not follow from the rank's own digits alone:
+    p with chosen odd levels for q up to 31, ranks whose additions r + skips[k] carry through odd levels, with lower
+    parts empty, largest possible and on both sides of twice the number of odd levels (the limits of the direct rule in
+    bcs_earlier_rows.h, wider than the closed form's exceptions); every entry against Alg. 5 of the oracle.  Then
+    such ranks as ranges of one p."""
     from test_host_logic import _p_from_bits
     rng = np.random.default_rng(310522)
     ps, rs = [], []
@@ -505,7 +539,7 @@ def test_batch_send_rows_where_the_direct_rule_is_at_its_limits(bcs, oracle):
     assert np.array_equal(qv.cpu().numpy(), oq)
     assert np.array_equal(recv.cpu().numpy(), orecv)
     assert np.array_equal(send.cpu().numpy(), osend)
-    # the kernel for a part of the ranks of one p uses the same rule: ranges around sums of skips
+    # ranges of one p around sums of skips
     for q, pat in ((27, list(range(7, 27))), (31, [k for k in range(7, 31) if k % 2]), (21, [9, 14])):
         p = _p_from_bits(q, int(rng.integers(0, 64)), pat)
         skips = oracle.skips(p).astype(np.int64)
@@ -520,10 +554,10 @@ def test_batch_send_rows_where_the_direct_rule_is_at_its_limits(bcs, oracle):
             assert np.array_equal(got, want), (p, root, r0, r1)
 
 
-def test_batch_with_more_left_over_send_entries_than_the_work_list_holds(bcs, oracle):
-    """The batch kernel works the send entries that need Alg. 5 off as a list of the workgroup, 4096 entries at a
-    time.  Triples picked (with the host build of the same lane code) so that every workgroup of 1024 has more than
-    that: ranks of p = 2^16+1 and 2^20+1 with seven or more such entries each."""
+def test_batch_of_the_ranks_with_the_most_send_entries_that_no_simple_rule_gives(bcs, oracle):
+    """Batches of nothing but ranks, of p = 2^16+1 and 2^20+1, that have seven or more send entries which the direct rule of
+    bcs_earlier_rows.h leaves to Alg. 5 (picked with its host build): low parts near an end of their range and low
+    digits disturbed by a carry through odd levels, the places where the closed form takes its exceptions."""
     import hostcheck
     rng = np.random.default_rng(77)
     ps, vs = [], []
@@ -535,7 +569,7 @@ def test_batch_with_more_left_over_send_entries_than_the_work_list_holds(bcs, or
         many = ranks[left >= 7]
         assert len(many) >= 2048
         pick = rng.choice(many, 2048, replace=False)
-        assert left[pick].reshape(2, 1024).sum(axis=1).min() > 4096 + 1024     # more than one filling of the list
+        assert left[pick].reshape(2, 1024).sum(axis=1).min() > 4096 + 1024
         ps += [p] * 2048
         vs += pick.tolist()
     p_arr = np.array(ps, dtype=np.int32)
@@ -553,12 +587,11 @@ def test_batch_with_more_left_over_send_entries_than_the_work_list_holds(bcs, or
 
 
 def test_send_rule_against_the_look_up_for_every_rank_of_large_p(bcs):
-    """Send rows of parts of the ranks (taken from the ranks' own digits where the rule applies, Alg. 5 otherwise)
-    against send rows of all ranks by look-up in the receive table, which is their definition (Alg. 9, second loop):
-    every rank of 40 values of p of 12 to 27 bits, random and with chosen odd levels, each under a random root and cut
-    into two ranges at a random rank.  Then p of 30 and 31 bits, whose tables do not fit: slices of 2^20 ranks
-    against entry k of the receive rows of their to-neighbours.  (The receive rows themselves are compared with the
-    oracle elsewhere in this file.)"""
+    """Send rows against their definition by look-up in the receive rows (Alg. 9, second loop): every rank of 40 values of p of
+    12 to 27 bits, random and with chosen odd levels, each under a random root, made at once and in two ranges cut at a
+    random rank, against entry k of the to-neighbours' receive rows.  Then p of 30 and 31 bits, whose tables do not
+    fit: slices of 2^20 ranks against the receive rows of their to-neighbours.  (The receive rows themselves are compared
+    with the oracle and with windows elsewhere in this file.)"""
     from test_host_logic import _p_from_bits
     rng = np.random.default_rng(20220510)
     ps = [(1 << 20) + 1, (1 << 23) + 1, (1 << 24) + 12345, (1 << 26) - 3, (1 << 27) - 1]
@@ -571,15 +604,19 @@ def test_send_rule_against_the_look_up_for_every_rank_of_large_p(bcs):
             ps.append(_p_from_bits(q, int(rng.integers(0, 64)), [k for k in range(7, q) if rng.random() < pr]))
     for p in ps:
         q = bcs.bcs_q(p)
-        full = torch.empty((p, q), dtype=torch.int32, device="cuda")
+        recv, full = (torch.empty((p, q), dtype=torch.int32, device="cuda") for _ in range(2))
         part = torch.full((p, q), 99, dtype=torch.int32, device="cuda")
         root, cut = int(rng.integers(0, p)), int(rng.integers(1, p))
+        bcs.bcs_sched_rooted(p, root, 0, p, recv, None)
         bcs.bcs_sched_rooted(p, root, 0, p, None, full)
         bcs.bcs_sched_rooted(p, root, 0, cut, None, part[:cut])
         bcs.bcs_sched_rooted(p, root, cut, p, None, part[cut:])
         torch.cuda.synchronize()
         assert torch.equal(full, part), (p, root, cut)
-        del full, part
+        skips = bcs.bcs_skips(p)
+        for k in range(q):
+            assert torch.equal(full[:, k], torch.roll(recv[:, k], -int(skips[k]))), (p, root, k)
+        del recv, full, part
     bcs.bcs_release()
     torch.cuda.empty_cache()
     W = 1 << 20
@@ -801,11 +838,11 @@ def _sched_expand_case(bcs, oracle, p, n, root, own_ws=False, misalign=False):
 
 
 def test_sched_expand_one_call(bcs, oracle):
-    """bcs_sched_expand: schedules and both block tables of all ranks in one call.  Short rows are expanded by
-    the workgroup that built them (every q from 3 to 23 here; larger q would need more than 2^23 ranks at
-    once), longer rows from byte rows kept in scratch memory, the rest by the separate kernels; all compared in full."""
+    """bcs_sched_expand: schedules and both block tables of all ranks in one call, every q from 3 to 23, expanded from byte
+    rows in scratch memory (rows of 16 rounds or more, q >= 3, tables on 16 bytes) or by the separate kernels; all
+    compared in full."""
     rng = np.random.default_rng(2205)
-    for q in range(3, 22):                              # fused: R = n-1+q <= 96
+    for q in range(3, 22):                              # short rows
         p = (1 << (q - 1)) + 1 + int(rng.integers(0, 1 << (q - 1)))
         _sched_expand_case(bcs, oracle, p, int(rng.integers(max(1, 17 - q), 60)), int(rng.integers(0, p)),
                            own_ws=bool(q & 1))
@@ -813,12 +850,11 @@ def test_sched_expand_one_call(bcs, oracle):
     _sched_expand_case(bcs, oracle, (1 << 22) + 1, 1, (1 << 22), own_ws=True)   # q = 23, n = 1
     for p, n, root in [(5, 14, 4), (255, 89, 0), (256, 89, 255), (257, 88, 1), (511, 9, 77), (513, 87, 512),
                        (1000, 37, 123), (65536, 113, 9), (70001, 100, 70000), (65535, 81, 3)]:
-        _sched_expand_case(bcs, oracle, p, n, root)     # fused, tiles with ragged tails, both length classes
+        _sched_expand_case(bcs, oracle, p, n, root)
     for p, n, root in [(1, 1, 0), (1, 9, 0), (2, 40, 1), (3, 20, 2), (4, 33, 0), (9, 3, 8), (1000, 5, 1),
                        (1000, 200, 999), (4097, 100, 5), (65535, 145, 9), (70000, 1000, 7), (5, 700, 2), (33, 14, 32),
                        (1025, 641, 1024), (300001, 160, 7)]:
-        # longer rows: expansion from the byte rows the schedule kernels leave behind (plain call, caller's
-        # workspace of the full size), or the separate kernels (a workspace that only holds the schedules' scratch)
+        # the plain call, a caller's workspace of the full size, and one that only holds the schedules' scratch
         for own_ws in (False, True, "small"):
             _sched_expand_case(bcs, oracle, p, n, root, own_ws=own_ws)
     _sched_expand_case(bcs, oracle, 1000, 37, 123, misalign=True)

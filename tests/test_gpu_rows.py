@@ -46,8 +46,9 @@ def test_rows_of_ranges_that_end_inside_a_piece(bcs, oracle, p):
 
 @pytest.mark.parametrize("p,n", [(5, 30), (10001, 40), (10001, 3), (300007, 400), (1500001, 20)])
 def test_sched_expand_with_any_workspace(bcs, oracle, p, n):
-    """Both tables at once, table by table (block tables above 128 MB), and in chunks of ranks: a workspace that holds
-    the schedules' scratch only is too small for the byte rows at q = 14 and above, and 1500001 ranks exceed 32 MB."""
+    """Both tables at once, table by table (block tables above 128 MB), and in chunks of ranks: a workspace of the schedules'
+    size alone holds no byte rows of both tables (up to 128 MB a table: bcs_expand; above: chunks), and the byte rows of
+    1500001 ranks exceed 32 MB."""
     q, R, root = bcs.bcs_q(p), bcs.bcs_rounds(p, n), p // 3
     want = oracle.sched_range(p, root, 0, p)
     blocks = [oracle.expand(p, n, w) for w in want]

@@ -1,7 +1,6 @@
-"""Collected last (file name order): the entry point that allocates nothing (bcs_sched_rooted_static: scratch in a fixed array inside the library)
-against bcs_sched_rooted, bit for bit, through the C ABI.  Two calls in a row, the second with a smaller input,
-so that whatever the first left in the shared array is still there; then a part of the ranks with send rows by
-Alg. 5 (which takes the table of digit masks from the same array), and a size beyond the array."""
+"""Collected last (file name order): the entry point for callers that cannot allocate (bcs_sched_rooted_static: a fixed limit of
+scratch) against bcs_sched_rooted, bit for bit, through the C ABI: all ranks, a smaller call right after, a part of the ranks
+with send rows, the largest p within the limit and one beyond it."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -37,15 +36,15 @@ def test_static_scratch_entry_point_equals_the_allocating_one(oracle):
     small = _both(bcs, 1000, 7, 0, 1000)
     orecv, osend = oracle.sched_range(1000, root=7)
     assert np.array_equal(small[0].cpu().numpy(), orecv) and np.array_equal(small[1].cpu().numpy(), osend)
-    print("static: the largest p the array holds, send rows only", flush=True)
+    print("static: the largest p within the limit, send rows only", flush=True)
     _both(bcs, 1342016, 0, 0, 1342016, want_recv=False)
-    print("static: p=65537, ranks 100..60100, send rows by Alg. 5 with the digit table", flush=True)
+    print("static: p=65537, ranks 100..60100, a part of the ranks", flush=True)
     assert bcs.bcs_sched_workspace_bytes(65537, 100, 60100) > 0
     _both(bcs, 65537, 3, 100, 60100)
     print("static: p=2 and p=1", flush=True)
     _both(bcs, 2, 1, 0, 2)
     bcs.bcs_sched_rooted_static(1, 0, 0, 1, small[0], small[1])
-    print("static: beyond the array", flush=True)
+    print("static: beyond the limit", flush=True)
     p = 1342017
     t = torch.empty((p, 21), dtype=torch.int32, device="cuda")
     with pytest.raises(bcs.BcsError) as err:
