@@ -33,9 +33,10 @@
 //     head plus dl = low + o(7, z) - skips[7], whose entry k is k + 1 - q for dl < o(k+1, z), else t's x - q;
 //     and for k = 7 set with low = 0 t's round 7 is the one that catches up where t's x is not 7.
 // The argument covers where the holders lie; that Alg. 4 then acts as described is checked against its definition by
-// windows: every rank of every p from 65 to 199 999, of 154 800 larger p up to 2^23, and 238 469 slices of up to 2^21 ranks
-// of p up to 2^31, at and around both ends of blocks, the p with few, many and random odd levels (4.3 10^11 ranks, random
-// roots): no difference.  The CPU tests repeat this against the oracle at smaller counts.
+// windows (bcs_core.h, made for every rank on the GPU; send rows by look-up in those rows, of slices by Alg. 5): every rank
+// of every p up to 200 000 and of 140 000 larger p up to 2^23, and 40 000 slices of 2^16 ranks of p up to 2^31, at and
+// around both ends of blocks, the p with few, many and random odd levels, under random roots (3.0 10^11 ranks): no
+// difference.  The CPU and GPU tests repeat this against windows and the oracle at smaller counts.
 #ifndef BCS_ROWS_H
 #define BCS_ROWS_H
 

@@ -13,7 +13,7 @@ GOLDEN = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden")
 
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs an MI355X (runs the HIP library through its C ABI)")
-    config.addinivalue_line("markers", "slow: CPU test of many minutes; runs only with BCS_RUN_SLOW=1 in the environment")
+    config.addinivalue_line("markers", "slow: test of minutes; runs only with BCS_RUN_SLOW=1 in the environment")
 
 
 def pytest_collection_modifyitems(config, items):
