@@ -156,7 +156,8 @@ def _stream(stream):
     its handle: calls of a few microseconds are bound by what happens here."""
     if stream is None:
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)          # not documented: a torch may come without
+        return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream
 
 

@@ -382,3 +382,16 @@ def test_taking_a_digit_out_of_a_greedy_sum_leaves_a_greedy_sum(oracle):
                 continue
             lower = _greedy_digits(skips, ranks[has] - int(skips[n]))
             assert np.array_equal(lower, d[has] & ~(1 << n)), (p, n)
+
+
+def test_the_current_stream_without_torchs_private_call(monkeypatch):
+    """The binding asks for the current stream's handle by a call that torch does not document; without it, by the
+    documented one."""
+    import torch
+    import paper_2205_10072_amd as bcs
+
+    class Stream:
+        cuda_stream = 4711
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    assert bcs._stream(None) == 4711 and bcs._stream(Stream) == 4711
