@@ -156,8 +156,10 @@ def _stream(stream):
     its handle: calls of a few microseconds are bound by what happens here."""
     if stream is None:
         import torch
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)          # not documented: a torch may come without
-        return raw(torch.cuda.current_device()) if raw else torch.cuda.current_stream().cuda_stream
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        except AttributeError:                     # not documented: a torch may come without it
+            return torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream
 
 
