@@ -16,6 +16,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -34,48 +35,70 @@ HBM_PEAK_GBS = 8000.0                       # MI355X HBM3E
 INT_VALU_PEAK_GOPS = 256 * 4 * 16 * 2.4     # CUs x SIMDs x lanes x GHz = 39 321.6 G lane-ops/s (32-bit, full rate)
 
 
+def code_only(text):
+    """C++ source without comments and with white space closed up: what a profile depends on."""
+    text = re.sub(r'//[^\n]*|/\*.*?\*/|("(?:\\.|[^"\\\n])*")', lambda m: m.group(1) or " ", text, flags=re.S)
+    return " ".join(text.split())
+
+
 def csrc_digest():
-    """Short hash of the kernel sources: counter figures below are tied to the sources they were profiled on."""
+    """Short hash of the kernel sources' code (comments do not count): counter figures below are tied to the code they
+    were profiled on."""
     h = hashlib.sha256()
     d = os.path.join(ROOT, "paper_2205_10072_amd", "csrc")
     for name in sorted(os.listdir(d)):
         if name.endswith((".h", ".hip")):
-            with open(os.path.join(d, name), "rb") as f:
-                h.update(name.encode() + b"\0" + f.read())
+            with open(os.path.join(d, name), encoding="utf-8") as f:
+                h.update(name.encode() + b"\0" + code_only(f.read()).encode())
     return h.hexdigest()[:16]
 
 
 # Counter figures that this run does not measure itself: rocprofv3 --pmc runs of this same file, summarised under
 # profiles/ (FETCH_SIZE scaled x2.0 and WRITE_SIZE x1.0 by the 1 GiB copy calibration; KiB per dispatch).
-# Key: (config, kernel).  `csrc`: csrc_digest() of the sources that were profiled; when the sources have changed
-# since, the record is still printed but marked "stale": true, and a warning goes to stderr.
+# Key: (config, kernel).  Each entry names its profile and the csrc_digest() of the run that produced it; only such a run
+# may change either.  When the sources' code has changed since, the record is still printed but marked "stale": true, and a
+# warning goes to stderr.
+# Per dispatch: FETCH_SIZE / WRITE_SIZE in KiB as read, SQ_WAVES, SQ_INSTS_VALU / SQ_WAVES, SQ_INSTS_SALU / SQ_WAVES,
+# SQ_THREAD_CYCLES_VALU / SQ_ACTIVE_INST_VALU (lanes active per vector instruction, of 64)
 PROFILED = {
-    "csrc": "0458ee3fc4ba6703",
-    "source": "profiles/c2_step_p1048577_n256.md, c3_sched_p134217727.md, c4_expand_p65537_n4096.md, c5_batch_2e20.md, "
-              "allgather_tables_p1048577_n256.md",
-    "counters": {
-        # per dispatch: FETCH_SIZE / WRITE_SIZE in KiB as read, SQ_WAVES, SQ_INSTS_VALU / SQ_WAVES, SQ_INSTS_SALU / SQ_WAVES,
-        # SQ_THREAD_CYCLES_VALU / SQ_ACTIVE_INST_VALU (lanes active per vector instruction, of 64)
-        ("C3", "k_sched"): {'fetch_kib': 937, 'write_kib': 28311552, 'waves': 7077888, 'valu_per_wave': 346.2, 'salu_per_wave': 111.4},
-        ("C2", "k_sched"): {'fetch_kib': 91, 'write_kib': 111072, 'waves': 21505, 'valu_per_wave': 579.9, 'salu_per_wave': 215.0},
-        ("C5 recv_and_send", "k_batch"): {'fetch_kib': 11527, 'write_kib': 266240, 'waves': 16384, 'valu_per_wave': 1215.6, 'salu_per_wave': 298.8},
-        ("C2", "k_expand_rows"): {'fetch_kib': 35345, 'write_kib': 1130584, 'waves': 1130500, 'valu_per_wave': 69.0, 'salu_per_wave': 9.0, 'active_lanes': 64.0},
-        ("C4", "k_expand"): {'fetch_kib': 9004, 'write_kib': 1052688, 'waves': 263176, 'valu_per_wave': 258.5, 'salu_per_wave': 195.0, 'active_lanes': 63.3},
-        ("C4", "k_rows_to_bytes"): {'fetch_kib': 2252, 'write_kib': 1280, 'waves': 5124, 'valu_per_wave': 50.0, 'salu_per_wave': 12.0, 'active_lanes': 64.0},
-        ("C4", "k_expand_rows"): {'fetch_kib': 5135, 'write_kib': 1052924, 'waves': 1052692, 'valu_per_wave': 69.0, 'salu_per_wave': 9.0, 'active_lanes': 64.0},
-        ("AG", "k_allgather_tables"): {"fetch_kib": 41280, "write_kib": 2261412},
-    },
+    ("C3", "k_sched"): {"csrc": "ee84ee609835d4a9", "source": "c3_sched_p134217727.md", "fetch_kib": 921,
+                        "write_kib": 28311552, "waves": 7077888, "valu_per_wave": 346.2, "salu_per_wave": 111.4,
+                        "active_lanes": 63.4},
+    ("C2", "k_sched"): {"csrc": "ee84ee609835d4a9", "source": "c2_step_p1048577_n256.md", "fetch_kib": 85,
+                        "write_kib": 111072, "waves": 21505, "valu_per_wave": 545.3, "salu_per_wave": 211.7,
+                        "active_lanes": 59.9},
+    ("C2", "k_expand_rows"): {"csrc": "ee84ee609835d4a9", "source": "c2_step_p1048577_n256.md", "fetch_kib": 35346,
+                              "write_kib": 1130607, "waves": 1130500, "valu_per_wave": 73.0, "salu_per_wave": 17.0,
+                              "active_lanes": 64.0},
+    ("C4", "k_expand"): {"csrc": "ee84ee609835d4a9", "source": "c4_expand_p65537_n4096.md", "fetch_kib": 9008,
+                         "write_kib": 1052688, "waves": 263176, "valu_per_wave": 258.5, "salu_per_wave": 200.0,
+                         "active_lanes": 63.3},
+    ("C4", "k_rows_to_bytes"): {"csrc": "ee84ee609835d4a9", "source": "c4_expand_p65537_n4096.md", "fetch_kib": 2252,
+                                "write_kib": 1280, "waves": 5124, "valu_per_wave": 50.0, "salu_per_wave": 12.0,
+                                "active_lanes": 64.0},
+    ("C4", "k_expand_rows"): {"csrc": "ee84ee609835d4a9", "source": "c4_expand_p65537_n4096.md", "fetch_kib": 5136,
+                              "write_kib": 1052952, "waves": 1052692, "valu_per_wave": 73.0, "salu_per_wave": 17.0,
+                              "active_lanes": 64.0},
+    ("C5 recv_and_send", "k_batch"): {"csrc": "ee84ee609835d4a9", "source": "c5_batch_2e20.md", "fetch_kib": 11528,
+                                      "write_kib": 266274, "waves": 16384, "valu_per_wave": 1215.6,
+                                      "salu_per_wave": 298.8, "active_lanes": 62.5},
+    ("C5 recv_only", "k_batch"): {"csrc": "ee84ee609835d4a9", "source": "c5_batch_2e20.md", "fetch_kib": 10317,
+                                  "write_kib": 135185, "waves": 16384, "valu_per_wave": 835.1, "salu_per_wave": 207.6,
+                                  "active_lanes": 63.0},
+    ("AG", "k_allgather_tables"): {"csrc": "ee84ee609835d4a9", "source": "allgather_tables_p1048577_n256.md",
+                                   "fetch_kib": 59974, "write_kib": 2261340, "waves": 2261000, "valu_per_wave": 67.6,
+                                   "salu_per_wave": 24.0, "active_lanes": 63.9},
 }
 
 
 def profiled(config, kernel, digest):
-    ent = PROFILED["counters"].get((config, kernel))
+    ent = PROFILED.get((config, kernel))
     if ent is None:
         return None
     out = dict(ent)
-    out["source"] = PROFILED["source"]
-    out["profiled_at_csrc"] = PROFILED["csrc"]
-    out["stale"] = PROFILED["csrc"] != digest
+    out["profiled_at_csrc"] = out.pop("csrc")
+    out["source"] = "profiles/" + out["source"]
+    out["stale"] = out["profiled_at_csrc"] != digest
     return out
 
 
@@ -466,8 +489,7 @@ def bench_partner_tables(torch, bcs, args):
 
 def bench_shard(torch, bcs, args):
     """One GPU's share of C3 when the ranks are spread over eight GPUs with no exchange: ranks [0, p/8) of p = 2^27-1,
-    receive rows and send rows without the other ranks' receive rows (entries from the ranks' own digits where the
-    rule allows, Alg. 5 for the rest)."""
+    receive rows and send rows, both from the ranks' own digits, without the other ranks' rows."""
     p = P_C3
     q = bcs.bcs_q(p)
     r0, r1 = 0, (p + 7) // 8
@@ -489,8 +511,8 @@ def bench_shard(torch, bcs, args):
         "n_gpus": 1, "steps": steps, "warmup": args.warmup, "ms_per_step": ms,
         "ms_per_step_with_kernel_events": ms_ev,
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "int32", "data": "synthetic",
-        "config": {"workload": "ranks [0, p/8) of p=2^27-1 (q=27): the digit masks of all ranks, receive rows of the share, "
-                               "send rows of the share without the other ranks", "p": p, "q": q, "ranks": rows},
+        "config": {"workload": "ranks [0, p/8) of p=2^27-1 (q=27): receive and send rows of the share without the other "
+                               "ranks", "p": p, "q": q, "ranks": rows},
         "roofline": {"kernel": name, "bound": "alu", "achieved": None, "peak": INT_VALU_PEAK_GOPS, "unit": "Gop/s",
                      "frac": None, "traffic": None, "avg_ms": kernels[name]["avg_ms"],
                      "note": "no counter profile of this workload: times only"},
@@ -711,9 +733,10 @@ def main():
         if c not in ("C2", "C3", "C4", "C5"):
             sys.exit("bench.py: unknown configuration %r in --only" % c)
     digest = csrc_digest()
-    if PROFILED["counters"] and PROFILED["csrc"] != digest:
-        print("bench.py: kernel sources changed since the counter profiles were taken (%s -> %s): counter fields "
-              "are marked stale" % (PROFILED["csrc"], digest), file=sys.stderr)
+    stale = sorted("%s %s" % key for key, ent in PROFILED.items() if ent["csrc"] != digest)
+    if stale:
+        print("bench.py: the kernel sources' code is not what these counter profiles were taken on, their fields are marked "
+              "stale: %s" % ", ".join(stale), file=sys.stderr)
     if args.copy_calibration:
         a = torch.zeros(1 << 28, dtype=torch.int32, device="cuda")      # 1 GiB read + 1 GiB written per copy
         b = torch.empty_like(a)
