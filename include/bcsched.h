@@ -33,16 +33,18 @@
  *     grows on demand and is released by bcs_release().  Plain calls on one
  *     device share that allocation: the library orders them itself (a plain
  *     call on another stream than the plain call before it is made to wait,
- *     on the device, for that stream's work), so they never overlap; callers
- *     that want overlap use the *_ws variants with a workspace per stream.
+ *     on the device, for that stream's work), so they never overlap, from
+ *     several host threads neither; callers that want overlap use the *_ws
+ *     variants with a workspace per stream.
  *     A stream handed to a plain call should stay alive until the next plain
  *     call on the device (else that call synchronises the device instead).
  *   - The first call on a device that builds schedules (bcs_sched*,
  *     bcs_sched_batch, bcs_allgather_tables*) also enqueues, ahead of its own
- *     work, a short kernel that fills a 544 KiB table kept in the library's
- *     code object (baseblock sets of the seven lowest levels of the circulant
- *     graph).  Until that kernel has finished, calls on other streams are made
- *     to wait for it on the device; no call waits on the host.
+ *     work, two kernels (about 50 us) that fill two tables kept in the library's
+ *     code object: 544 KiB of baseblock sets of the seven lowest levels of the
+ *     circulant graph, and from them 6.6 MB of the rounds of those levels.
+ *     Until they have finished, calls on other streams are made to wait for them
+ *     on the device; no call waits on the host.
  *   - Calls that allocate nothing (the *_ws entry points, bcs_expand,
  *     bcs_sched_batch) may be recorded into a HIP graph, once one schedule-
  *     building call has been made on the device outside the capture (that first
@@ -252,7 +254,11 @@ int bcs_allgather_tables_ws(int32_t p, int32_t n, int32_t r,
  *   the message; offsets[p] = length of the whole message (compare it with
  *   `capacity` / `length` after synchronising).
  *   workspace: device, 8-byte aligned, bcs_pack_workspace_bytes(p) bytes.
- * Both calls enqueue four kernels and allocate nothing.
+ *   Its contents are undefined afterwards.
+ * Both calls allocate nothing.  They enqueue one kernel for up to 2048 processes
+ * and a capacity / length of 1 .. 512 K elements; else the plan's (one for up to
+ * 8192 processes, three above) and, unless the capacity / length is 0, the
+ * payload's.
  * BCS_EINVAL: p < 1, n < 1, a NULL array (`packed` may be NULL when capacity /
  * length is 0: then only `offsets` is produced), capacity / length negative or
  * above 2^36 - 4096 elements (no card holds them).
@@ -274,7 +280,7 @@ int bcs_unpack_round(int32_t p, int32_t n, const int32_t *idx, const int64_t *di
  *   src_all: device, rounds x p int64: where each root's block starts in `data` (elements).
  * bcs_pack_round_planned / bcs_unpack_round_planned: the payload of one round from its two plan rows
  * (offsets: p+1 entries, src: p entries); arguments otherwise as bcs_pack_round / bcs_unpack_round.
- * All three enqueue one kernel and allocate nothing.
+ * All three enqueue one kernel (the plans of 2^24 rounds or more: several) and allocate nothing.
  * BCS_EINVAL: p < 1, n < 1, rounds < 0, a NULL array, plan arrays not 8-byte aligned,
  * capacity / length negative or above 2^36 - 4096. */
 int bcs_pack_plan_rounds(int32_t p, int32_t n, int64_t rounds, const int32_t *idx_table, const int64_t *displs,

@@ -62,10 +62,6 @@ __global__ __launch_bounds__(kBlock) void k_allgather_tables(const SkipTab tab, 
     }
 }
 
-// K5 with 16-byte stores for any p.  Rows of p entries start on every possible 4-byte phase of a
-// 16-byte line, so the schedule entries of the workgroup's roots are staged in LDS and each round
-// reads them back at that round's phase: single entries up to the next 128-byte line, aligned groups
-// of four (a wave stores whole lines), up to three single entries.  Needs 16-byte aligned tables (else the kernel above runs).
 // The same tables as ONE flat stream of R * p entries each, for 16-byte aligned outputs: a workgroup writes one
 // piece of 1024 consecutive entries (4 KiB, whole lines whatever p is) and ends; a lane resolves round and root
 // of its four entries by itself (exact division by p with a multiply-high and one correction), reads the four
@@ -140,11 +136,12 @@ __global__ __launch_bounds__(kBlock) void k_allgather_tables_flat(const SkipTab 
 // K6: pack / unpack of one round of the irregular allgather (Alg. 9, its "Pack" and "Unpack" loops).
 // The message is the concatenation, root by root, of one block of each buffer; buffers have any
 // sizes (Section 3.2 uses (r mod 3) * floor(m/p)), a buffer of m elements is cut into n blocks at
-// floor(b*m/n).  Three small kernels make the plan -- each root's block length and source offset, an
-// exclusive scan of the lengths (1024 roots per workgroup, then the workgroup totals, then the sum) --
-// and one kernel moves the payload: it walks the MESSAGE in 16-byte pieces (aligned on that side), a
-// lane finds the root of its piece by a search that starts where its previous piece ended, and the
-// buffer side is read or written with whatever alignment the block happens to have.
+// floor(b*m/n).  Rounds of few processes and short messages take k_pack_round alone.  Else three small
+// kernels make the plan -- each root's block length and source offset, an exclusive scan of the lengths
+// (1024 roots per workgroup, then the workgroup totals, then the sum; one kernel for a few thousand
+// processes, k_pack_plan_one) -- and one kernel moves the payload: it walks the MESSAGE in 16-byte pieces
+// (aligned on that side), a lane finds the root of its piece by a search that starts where its previous
+// piece ended, and the buffer side is read or written with whatever alignment the block happens to have.
 // ----------------------------------------------------------------------------------------------
 constexpr int kPlanRoots = 1024;                     // roots per workgroup in the scan (4 per lane)
 
@@ -401,7 +398,8 @@ __global__ __launch_bounds__(kBlock) void k_pack_copy(uint32_t p, int64_t limit,
 // eight consecutive roots, one scan), then moves its 1024 elements, a lane one 16-byte piece whose root it finds by bisection.
 // Workgroup 0 writes the offsets out.  Packing and unpacking a round with two launches each against one (1152 processes):
 // 241 KB 26.7 and 20.8 us, 2 MB 26.6 and 20.5, 8 MB 27.1 and 31.2 us; with 2048 processes 2 MB 26.4 and 21.2, 4 MB 26.4 and
-// 28.8 us.
+// 28.8 us.  Up to 2048 processes: the plan takes 16 bytes of LDS a root, 33 KB, which leaves four workgroups on a compute unit;
+// a plan of more roots in every workgroup was not tried.
 constexpr uint32_t kRoundMaxP = 8 * kBlock;            // plan of all roots in LDS: 16 bytes a root
 constexpr int64_t kRoundMaxElements = 512 << 10;       // message elements up to which the repeated plan costs less
 

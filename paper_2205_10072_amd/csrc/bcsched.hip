@@ -4,8 +4,8 @@
 // One lane owns one rank.  Everything is 32-bit integer work on the vector ALU; block sets are
 // 32-bit masks (q <= 31); the skips of a uniform-p launch live in scalar registers.
 //
-// The per-rank construction is in bcs_rows.h (its definition by windows in bcs_core.h), the kernels in bcs_kernels_*.h; this file holds the launch and
-// timing helpers, the host logic and the C ABI.
+// The per-rank construction is in bcs_rows.h (its definition by windows in bcs_core.h), the kernels in bcs_kernels_*.h; this
+// file holds the launch and timing helpers, the host logic and the C ABI.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 #include <stdint.h>
@@ -497,8 +497,10 @@ constexpr uint64_t kExpandWsMinR = 256;
 inline bool expand_ws_applies(int32_t rows, int q, uint64_t R) {
     return q >= (int)kExpMinQ && R >= kExpandWsMinR && rows > 0;
 }
-// ... and tables up to kTogetherBytes are better off without: with byte rows (four launches) against without (one), block
-// tables of 7.7 MB 17.9 and 9.3 us, 81 MB 31.9 and 30.2, 161 MB 52.9 and 53.0, 266 MB 83 and 88, 1078 MB 300 and 319 us
+// ... and tables up to kTogetherBytes are better off without.  Both tables, with byte rows (four launches) against without
+// (one): block tables of 7.7 MB 17.9 and 9.3 us, 81 MB 31.9 and 30.2, 161 MB 52.9 and 53.0, 266 MB 83 and 88, 1078 MB 300 and
+// 319 us.  One table (two launches against one): 7.7 MB 6.7 and 4.2 us, 25 MB 8.3 and 6.1, 81 MB 16.1 and 14.8, 122 MB 21.7
+// and 21.1, 137 MB 26.2 and 23.1
 inline bool expand_ws_pays(int32_t rows, uint64_t R) { return (uint64_t)rows * R * sizeof(int32_t) > kTogetherBytes; }
 // rows converted and expanded at a time: their byte table fits kByteRowsMax; a multiple of 4, so that every
 // chunk's piece of the output starts on a 16-byte boundary
