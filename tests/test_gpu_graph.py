@@ -13,7 +13,7 @@ def test_graph_replays_of_the_no_allocation_calls(oracle):
         pytest.skip("no GPU")
     import paper_2205_10072_amd as bcs
     bcs.lib()
-    p, root, n = 70001, 4242, 300          # byte-row path; the allgather tables and a pack round ride along
+    p, root, n = 70001, 4242, 300          # byte rows of both tables; one table by bcs_expand; allgather tables
     q, R = bcs.bcs_q(p), bcs.bcs_rounds(p, n)
     recv = torch.zeros((p, q), dtype=torch.int32, device="cuda")
     send = torch.zeros_like(recv)
@@ -115,3 +115,68 @@ def test_graph_replays_of_planned_pack_and_unpack_rounds(oracle):
         for i, omsg in enumerate(want_msgs):
             assert np.array_equal(got[i, :len(omsg)], omsg) and (got[i, len(omsg):] == -3 - replay).all(), (replay, i)
         assert np.array_equal(d_copy.cpu().numpy(), want_copy), replay
+
+
+def test_graph_replays_of_the_other_calls_that_allocate_nothing():
+    """Byte rows of the caller's tables (above 128 MB), a batch, the static call, partner tables, and a round packed and
+    unpacked by one launch each, against the same calls made eagerly before."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2205_10072_amd as bcs
+    from paper_2205_10072_amd import synth
+    p, n = 1000, 34000
+    q, R = bcs.bcs_q(p), bcs.bcs_rounds(p, n)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    sched = torch.empty((p, q), **i32)
+    bcs.bcs_sched(p, 0, p, sched, None)
+    ws = torch.empty(bcs.bcs_expand_workspace_bytes(p, n, 0, p), dtype=torch.uint8, device="cuda")
+    triples = [torch.from_numpy(a).cuda() for a in synth.batch_triples(3001)]
+    pp, m, blocks = 1152, 1 << 20, 40
+    sizes, displs = synth.irregular_sizes(pp, m)
+    displs = torch.from_numpy(displs).cuda()
+    tables = [torch.empty((bcs.bcs_rounds(pp, blocks), pp), **i32) for _ in range(2)]
+    bcs.bcs_allgather_tables(pp, blocks, 5, *tables)
+    row_out, row_in = (t[20].contiguous() for t in tables)
+    data = torch.arange(m, **i32)
+    pws = torch.empty(bcs.bcs_pack_workspace_bytes(pp), dtype=torch.uint8, device="cuda")
+    outs = dict(rb=torch.empty((p, R), **i32), brecv=torch.empty((3001, 32), **i32), bsend=torch.empty((3001, 32), **i32),
+                q=torch.empty(3001, **i32), srecv=torch.empty((p, q), **i32), ssend=torch.empty((p, q), **i32),
+                to=torch.empty((p, q), **i32), frm=torch.empty((p, q), **i32), message=torch.empty(m // blocks + 4 * pp, **i32),
+                buffers=torch.empty(m, **i32))
+    offs = [torch.empty(pp + 1, dtype=torch.int64, device="cuda") for _ in range(2)]
+    length = outs["message"].numel()
+
+    def work():
+        bcs.bcs_expand_ws(p, n, 0, p, sched, None, outs["rb"], None, ws)
+        bcs.bcs_sched_batch(*triples, outs["brecv"], outs["bsend"], outs["q"])
+        bcs.bcs_sched_rooted_static(p, 7, 0, p, outs["srecv"], outs["ssend"])
+        bcs.bcs_census_partners(p, 0, p, outs["to"], outs["frm"])
+        bcs.bcs_pack_round(blocks, row_out, displs, data, outs["message"], offs[0], pws)
+        bcs.bcs_unpack_round(blocks, row_in, displs, outs["buffers"], outs["message"], length, offs[1], pws)
+
+    def blank(value):
+        for t in list(outs.values()) + offs:
+            t.fill_(value)
+        torch.cuda.synchronize()
+
+    side = torch.cuda.Stream()
+    blank(-5)
+    with torch.cuda.stream(side):
+        bcs.bcs_timing_begin()
+        work()
+        side.synchronize()
+        assert {"k_rows_to_bytes", "k_expand_rows", "k_batch", "k_sched", "k_partner_tables"} <= set(bcs.bcs_timing_end())
+    want = {k: t.clone() for k, t in outs.items()}
+    want_offs = [t.clone() for t in offs]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            work()
+    for replay in range(4):
+        blank(-5)
+        graph.replay()
+        torch.cuda.synchronize()
+        for k, t in outs.items():
+            assert torch.equal(t, want[k]), (replay, k)
+        assert all(torch.equal(a, b) for a, b in zip(offs, want_offs)), replay
