@@ -23,7 +23,7 @@ def test_round_in_one_launch(p, mean, n):
     d_idx, d_displs = torch.from_numpy(idx).cuda(), torch.from_numpy(displs).cuda()
     ws = torch.empty(bcs.bcs_pack_workspace_bytes(p), dtype=torch.uint8, device="cuda")
     for shift in (0, 1):
-        for capacity in {length + 5, length, max(length - 3, 0)}:
+        for capacity in {length + 5, length, max(length - 3, 0), 512 << 10, (512 << 10) + 1}:       # the last: two launches
             offsets = torch.full((p + 1,), -1, dtype=torch.int64, device="cuda")
             buf = torch.full((capacity + 8,), 777, dtype=torch.int32, device="cuda")
             bcs.bcs_pack_round(n, d_idx, d_displs, torch.from_numpy(data).cuda(), buf[shift:shift + capacity], offsets, ws)

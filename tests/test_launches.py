@@ -201,3 +201,13 @@ S.stub_reset()
 L.bcs_sched_expand_ws(p, 0, n, T(1), T(2), T(3), T(4), T(5), L.bcs_sched_workspace_bytes(p, 0, p, 1), None)
 """ % (p, n))
     assert [e["name"] for e in launches(log)] == ["k_sched", "k_expand"]
+
+
+@pytest.mark.parametrize("p,capacity,want", [(2048, 512 << 10, ["k_pack_round"]), (1, 1, ["k_pack_round"]),
+                                             (2048, (512 << 10) + 1, ["k_pack_plan_one", "k_pack_copy"]),
+                                             (2049, 1000, ["k_pack_plan_one", "k_pack_copy"]),
+                                             (8192, 1000, ["k_pack_plan_one", "k_pack_copy"]), (2048, 0, ["k_pack_plan_one"]),
+                                             (8193, 0, ["k_pack_plan_local", "k_pack_plan_totals", "k_pack_plan_finish"])])
+def test_launches_of_a_packed_round(tmp_path, p, capacity, want):
+    log = run(tmp_path, "show(L.bcs_pack_round(%d, 4, T(1), T(2), T(3), T(4), %d, T(5), T(6), 1 << 20, None))" % (p, capacity))
+    assert shown(log) == [0] and [e["name"] for e in launches(log)] == want
